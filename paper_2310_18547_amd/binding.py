@@ -2,7 +2,8 @@
 
 The functions have the C names and the C argument order.  Pointer arguments
 accept a ``torch`` tensor (its ``data_ptr()`` is taken), an ``int`` address or
-``None``; nothing is copied, converted or computed here.
+``None``; nothing is copied, converted or computed here.  The calls that a decode
+loop makes for every layer (the add-on and its two steps) come from a C module.
 """
 from __future__ import annotations
 
@@ -169,58 +170,24 @@ def sgmv_validate_segments(host_seg_starts, n_segs: int, n_tokens: int) -> int:
     return lib.sgmv_validate_segments(_addr(host_seg_starts), n_segs, n_tokens)
 
 
-def sgmv_shrink(p: SgmvProblem, v, x, A_ptrs, seg_starts, n_segs: int, layer_idx: int,
-                stream=None, check: bool = True) -> int:
-    rc = lib.sgmv_shrink(ctypes.byref(p), _addr(v), _addr(x), _addr(A_ptrs), _addr(seg_starts),
-                         n_segs, layer_idx, _stream(stream))
-    if check and rc != 0:
-        raise SgmvError(rc, "sgmv_shrink")
-    return rc
-
-
-def sgmv_expand(p: SgmvProblem, y, v, B_ptrs, seg_starts, n_segs: int, layer_idx: int,
-                scale: float, stream=None, check: bool = True) -> int:
-    rc = lib.sgmv_expand(ctypes.byref(p), _addr(y), _addr(v), _addr(B_ptrs), _addr(seg_starts),
-                         n_segs, layer_idx, scale, _stream(stream))
-    if check and rc != 0:
-        raise SgmvError(rc, "sgmv_expand")
-    return rc
-
-
-def sgmv_add_lora(p: SgmvProblem, y, x, A_ptrs, B_ptrs, seg_starts, n_segs: int, layer_idx: int,
-                  scale: float, stream=None, check: bool = True) -> int:
-    rc = lib.sgmv_add_lora(ctypes.byref(p), _addr(y), _addr(x), _addr(A_ptrs), _addr(B_ptrs),
-                           _addr(seg_starts), n_segs, layer_idx, scale, _stream(stream))
-    if check and rc != 0:
-        raise SgmvError(rc, "sgmv_add_lora")
-    return rc
-
-
-def sgmv_add_lora_static(p: SgmvProblem, y, x, A_ptrs, B_ptrs, seg_starts, n_segs: int,
-                         layer_idx: int, scale: float, stream=None, check: bool = True) -> int:
-    rc = lib.sgmv_add_lora_static(ctypes.byref(p), _addr(y), _addr(x), _addr(A_ptrs), _addr(B_ptrs),
-                                  _addr(seg_starts), n_segs, layer_idx, scale, _stream(stream))
-    if check and rc != 0:
-        raise SgmvError(rc, "sgmv_add_lora_static")
-    return rc
-
-
 STATIC_SCRATCH_BYTES = 9 << 20
 STATIC_MAX_WORKSPACE_BYTES = 8 << 20
 
 
-def sgmv_add_lora_multi(p: SgmvProblem, ys, xs, A_ptrs, B_ptrs, seg_starts, n_segs: int,
-                        layer_idx: int, scale: float, stream=None, check: bool = True) -> int:
-    """``ys, xs, A_ptrs, B_ptrs`` are sequences of equal length (one entry per add-on)."""
-    n = len(ys)
-    arr = ctypes.c_void_p * n
-    rc = lib.sgmv_add_lora_multi(
-        ctypes.byref(p), n, arr(*[_addr(a) for a in ys]), arr(*[_addr(a) for a in xs]),
-        arr(*[_addr(a) for a in A_ptrs]), arr(*[_addr(a) for a in B_ptrs]), _addr(seg_starts),
-        n_segs, layer_idx, scale, _stream(stream))
-    if check and rc != 0:
-        raise SgmvError(rc, "sgmv_add_lora_multi")
-    return rc
+def _calls():
+    """The per-layer calls, marshalled in C (csrc/call_module.c)."""
+    try:
+        from . import _sgmv_call as module
+    except ImportError as e:
+        raise ImportError(f"{_HERE}/_sgmv_call.so is missing or does not fit this interpreter: build it with "
+                          "`python -m paper_2310_18547_amd.build`") from e
+    names = ("sgmv_shrink", "sgmv_expand", "sgmv_add_lora", "sgmv_add_lora_static", "sgmv_add_lora_multi")
+    size = module.bind(SgmvProblem, SgmvError, *(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names))
+    assert size == ctypes.sizeof(SgmvProblem)
+    return [getattr(module, n) for n in names]
+
+
+sgmv_shrink, sgmv_expand, sgmv_add_lora, sgmv_add_lora_static, sgmv_add_lora_multi = _calls()
 
 
 def sgmv_plan_expand(p: SgmvProblem, n_segs: int, check: bool = True):

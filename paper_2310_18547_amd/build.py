@@ -1,4 +1,4 @@
-"""Build libsgmv.so (HIP, gfx950) in-tree with hipcc.
+"""Build libsgmv.so (HIP, gfx950) with hipcc and the binding's _sgmv_call.so with gcc, in-tree.
 
     python -m paper_2310_18547_amd.build
 """
@@ -8,10 +8,12 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsgmv.so")
+CALLS = os.path.join(HERE, "_sgmv_call.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -28,8 +30,21 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def build_calls(verbose: bool = True) -> str:
+    """Compile csrc/call_module.c, the binding's CPython module (host code, no GPU code in it)."""
+    tmp = CALLS + f".tmp{os.getpid()}"
+    cmd = ["gcc", "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
+           "-o", tmp, os.path.join(CSRC, "call_module.c")]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, CALLS)
+    return CALLS
+
+
 def build(verbose: bool = True, extra=(), trace: bool = False) -> str:
-    """Compile every csrc/*.hip to an object (in parallel) and link libsgmv.so.
+    """Compile every csrc/*.hip to an object (in parallel) and link libsgmv.so; the binding's
+    module comes with it.
 
     ``trace=True`` builds the tuning variant libsgmv_trace.so instead: the same sources with
     -DSGMV_TRACE, whose single-launch kernels record an in-kernel timeline (csrc/trace.h)."""
@@ -40,6 +55,7 @@ def build(verbose: bool = True, extra=(), trace: bool = False) -> str:
     if trace:
         extra = tuple(extra) + ("-DSGMV_TRACE",)
     os.makedirs(objdir, exist_ok=True)
+    build_calls(verbose)
     flags = [f for f in HIPCC_FLAGS if f != "-shared"]
 
     def compile_one(src):
