@@ -153,6 +153,8 @@ namespace sgmv {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr uint32_t kOutOfRange = 0x80000000u;
+// AUX of an access whose whole cache lines are touched once and not again by this launch (nt bit).
+constexpr int kNonTemporal = 2;
 constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit data format
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_buffer(const void* base, uint32_t bytes) {
@@ -171,25 +173,29 @@ __device__ __forceinline__ uint4 buffer_load128_at(__amdgpu_buffer_rsrc_t rsrc, 
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+template <int AUX = 0>
 __device__ __forceinline__ uint2 buffer_load64(__amdgpu_buffer_rsrc_t rsrc, uint32_t byte_off) {
-  u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)byte_off, 0, 0);
+  u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)byte_off, 0, AUX);
   return make_uint2(v.x, v.y);
 }
 // 64-bit accesses with a wave-uniform byte offset added to the lane's
+template <int AUX = 0>
 __device__ __forceinline__ uint2 buffer_load64_at(__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_byte_off,
                                                   uint32_t uniform_byte_off) {
-  u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)lane_byte_off, (int)uniform_byte_off, 0);
+  u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)lane_byte_off, (int)uniform_byte_off, AUX);
   return make_uint2(v.x, v.y);
 }
+template <int AUX = 0>
 __device__ __forceinline__ void buffer_store64_at(__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_byte_off,
                                                   uint32_t uniform_byte_off, const uint2& q) {
   u32x2 v = {q.x, q.y};
-  __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, (int)lane_byte_off, (int)uniform_byte_off, 0);
+  __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, (int)lane_byte_off, (int)uniform_byte_off, AUX);
 }
+template <int AUX = 0>
 __device__ __forceinline__ void buffer_store64(__amdgpu_buffer_rsrc_t rsrc, uint32_t byte_off,
                                                const uint2& q) {
   u32x2 v = {q.x, q.y};
-  __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, (int)byte_off, 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, (int)byte_off, 0, AUX);
 }
 __device__ __forceinline__ void buffer_store128(__amdgpu_buffer_rsrc_t rsrc, uint32_t byte_off,
                                                 const uint4& q) {

@@ -33,8 +33,11 @@
 //           v is the first operand and the strip of B_i (kept in registers) the second,
 //           tile t of a wave holding columns 4 n + t, so a lane ends with four
 //           consecutive columns (8 bytes) of four rows and every 64-bit access of y by
-//           a wave covers four rows x 128 contiguous bytes.  v stays fp32 in the
-//           workspace between the kernels; it enters the matrix cores as the two 16-bit
+//           a wave covers four rows x 128 contiguous bytes, loaded and stored
+//           non-temporally: whole cache lines that nothing here reads again (a plain
+//           read-modify-write of 80 MB in this pattern: 31.2 us, 27.0 us with both hints, 5.9 TB/s;
+//           the hint on one side only changes nothing; the add-on on 4814 rows of 8192, rank 16:
+//           61.4 -> 56.2 us).  v stays fp32 in the workspace between the kernels; it enters the matrix cores as the two 16-bit
 //           parts (two MFMAs, 16 significant bits for bfloat16, 22 for binary16).
 //   expand_rowwise_kernel  the same product with the operands' homes exchanged, for rank 64
 //           and for binary16: a wave owns sixteen rows of the block, keeps their v in
@@ -590,7 +593,7 @@ __global__ __launch_bounds__(256, (R <= 32 ? 4 : 3) - (std::is_same<DT, F16>::va
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = r0 + 4 * g + i;
-      T.yq[i] = buffer_load64(rY, row < ylim ? (uint32_t)(row * h_out + cw) * 2u : kOutOfRange);
+      T.yq[i] = buffer_load64<kNonTemporal>(rY, row < ylim ? (uint32_t)(row * h_out + cw) * 2u : kOutOfRange);
     }
     const int vrow = r0 + n;  // first operand: row n of the tile, k = 32 ks + 8 g .. + 7
 #pragma unroll
@@ -687,7 +690,7 @@ __global__ __launch_bounds__(256, (R <= 32 ? 4 : 3) - (std::is_same<DT, F16>::va
       for (int t = 0; t < CT; ++t) o[t] = yf[t] + sc * acc[t][i];
       const uint2 out = make_uint2(pack2<DT>(o[0], o[1]), pack2<DT>(o[2], o[3]));
       const int row = r0 + 4 * g + i;
-      buffer_store64(rY, row < ylim ? (uint32_t)(row * h_out + cw) * 2u : kOutOfRange, out);
+      buffer_store64<kNonTemporal>(rY, row < ylim ? (uint32_t)(row * h_out + cw) * 2u : kOutOfRange, out);
     }
   };
 
@@ -829,7 +832,7 @@ __global__ __launch_bounds__(256, 4) void expand_rowwise_kernel(
       const int ylim = j < groups_ok ? rows : 0;  // one compare per access
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        yq[j][i] = buffer_load64_at(rY, 4 * g + i < ylim ? yoff[i] : kOutOfRange, (uint32_t)j * (16 * CT * 2));
+        yq[j][i] = buffer_load64_at<kNonTemporal>(rY, 4 * g + i < ylim ? yoff[i] : kOutOfRange, (uint32_t)j * (16 * CT * 2));
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -909,7 +912,7 @@ __global__ __launch_bounds__(256, 4) void expand_rowwise_kernel(
 #pragma unroll
         for (int t = 0; t < CT; ++t) o[t] = yf[t] + sc * acc[t][i];
         const uint2 out = make_uint2(pack2<DT>(o[0], o[1]), pack2<DT>(o[2], o[3]));
-        buffer_store64_at(rY, 4 * g + i < ylim ? yoff[i] : kOutOfRange, (uint32_t)j * (16 * CT * 2), out);
+        buffer_store64_at<kNonTemporal>(rY, 4 * g + i < ylim ? yoff[i] : kOutOfRange, (uint32_t)j * (16 * CT * 2), out);
       }
     }
     // next block of this workgroup (only when the grid is smaller than the longest segment needs)
