@@ -167,9 +167,10 @@ __device__ __forceinline__ uint4 buffer_load128(__amdgpu_buffer_rsrc_t rsrc, uin
 }
 // The same with a wave-uniform byte offset added to the lane's (kept in a scalar register, so
 // that many loads of one lane share a single offset register).
+template <int AUX = 0>
 __device__ __forceinline__ uint4 buffer_load128_at(__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_byte_off,
                                                    uint32_t uniform_byte_off) {
-  u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)lane_byte_off, (int)uniform_byte_off, 0);
+  u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)lane_byte_off, (int)uniform_byte_off, AUX);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -202,6 +203,14 @@ __device__ __forceinline__ void buffer_store128(__amdgpu_buffer_rsrc_t rsrc, uin
   u32x4 v = {q.x, q.y, q.z, q.w};
   __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)byte_off, 0, 0);
 }
+
+// What the items of a single-row kernel's grid are (template argument MODE): the segments, or the
+// rows of the batch, each looking its segment up (kPerRow); and whether the weights are read past the
+// caches (non-temporal, kStreamed), which pays where a launch reads many of them once (launch.h,
+// stream_weights).
+constexpr int kPerSegment = 0, kPerRow = 1, kStreamed = 2;
+constexpr bool by_row(int mode) { return (mode & kPerRow) != 0; }
+constexpr int weights_aux(int mode) { return (mode & kStreamed) != 0 ? kNonTemporal : 0; }
 
 // Per-row launches: the segment that holds row `row`, i.e. the number of segment ends at or
 // before it (empty segments count themselves out); n_segs when the row lies behind the last end.

@@ -55,15 +55,16 @@ namespace sgmv {
 // G  = lane groups of the expand phase: group g multiplies weight rows
 //      g*R/G .. (g+1)*R/G-1; the groups are summed through LDS.
 // RB = rows handled per pass over the weights (1 when every segment is one row).
-// BY_ROW: `seg` is a row of the batch, not a segment: the workgroup serves that one row and
+// MODE with kPerRow: `seg` is a row of the batch, not a segment: the workgroup serves that one row and
 //      looks its segment up in seg_starts (n_segs of them).
-template <class DT, int R, int G, int RB, bool BY_ROW = false>
+template <class DT, int R, int G, int RB, int MODE = kPerSegment>
 __device__ __forceinline__ void add_lora_fused_body(
     const int32_t* __restrict__ seg_starts, const uint16_t* const* __restrict__ A_ptrs,
     const uint16_t* const* __restrict__ B_ptrs, const uint16_t* __restrict__ x,
     uint16_t* __restrict__ y, int kslice, int cslice, int h_in, int h_out, int n_tokens, int S,
     long long offA, long long offB, unsigned long long* exch, unsigned long long* header,
     float scale, int spin_limit, int seg, int s, int n_segs = 0) {
+  constexpr int kWeights = weights_aux(MODE);
   constexpr int NT = 256, NW = 4, U = 8;  // stream threads / waves, A loads per lane and batch
   constexpr int LPR = R / 8;
   constexpr int CPW = NT / G;  // 8-column chunks per pass
@@ -88,7 +89,7 @@ __device__ __forceinline__ void add_lora_fused_body(
   SGMV_TRACE_POINT(0);
   int lo, hi;
   const uint16_t *A, *B;
-  if constexpr (BY_ROW) {
+  if constexpr (by_row(MODE)) {
     const int found = segment_of_row(seg_starts, n_segs, seg, lane);
     lo = seg;
     hi = found < n_segs ? seg + 1 : seg;  // a row behind the last segment end: nothing to do
@@ -188,7 +189,7 @@ __device__ __forceinline__ void add_lora_fused_body(
   }
   uint4 a[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) a[u] = buffer_load128(rA, (uint32_t)(u * NT + tid) * 16u);
+  for (int u = 0; u < U; ++u) a[u] = buffer_load128<kWeights>(rA, (uint32_t)(u * NT + tid) * 16u);
   __builtin_amdgcn_sched_barrier(0);  // keep x and A ahead of B and y in the memory pipe
   uint4 b[JL];
   uint4 yq[RB];
@@ -197,7 +198,7 @@ __device__ __forceinline__ void add_lora_fused_body(
       const bool active = cc * 8 < ncols;
 #pragma unroll
       for (int j = 0; j < JL; ++j)
-        b[j] = buffer_load128(rB, active ? b_row0 + (uint32_t)j * row_bytes_out + (uint32_t)cc * 16u : kOutOfRange);
+        b[j] = buffer_load128<kWeights>(rB, active ? b_row0 + (uint32_t)j * row_bytes_out + (uint32_t)cc * 16u : kOutOfRange);
     }
     {
       const __amdgpu_buffer_rsrc_t rY = make_buffer(
@@ -241,7 +242,7 @@ __device__ __forceinline__ void add_lora_fused_body(
     for (int base = 0; base < nchunks; base += NT * U) {
       if (!first || base != 0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = buffer_load128(rA, (uint32_t)(base + u * NT + tid) * 16u);
+        for (int u = 0; u < U; ++u) a[u] = buffer_load128<kWeights>(rA, (uint32_t)(base + u * NT + tid) * 16u);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -300,7 +301,7 @@ __device__ __forceinline__ void add_lora_fused_body(
         if (npass > 1) {
 #pragma unroll
           for (int j = 0; j < JL; ++j)
-            b[j] = buffer_load128(rB, active ? b_row0 + (uint32_t)j * row_bytes_out + (uint32_t)c * 16u : kOutOfRange);
+            b[j] = buffer_load128<kWeights>(rB, active ? b_row0 + (uint32_t)j * row_bytes_out + (uint32_t)c * 16u : kOutOfRange);
         }
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
@@ -384,7 +385,7 @@ __device__ __forceinline__ void add_lora_fused_body(
 }
 
 // One add-on per launch.
-template <class DT, int R, int G, int RB, bool BY_ROW>
+template <class DT, int R, int G, int RB, int MODE>
 __global__ __launch_bounds__(320) void add_lora_fused_kernel(
     // the first sixteen dwords are preloaded into SGPRs at wave launch: keep what the
     // first dependent loads need at the front
@@ -395,16 +396,16 @@ __global__ __launch_bounds__(320) void add_lora_fused_kernel(
     float scale, int spin_limit, int n_segs) {
   // grid (fused_grid_x, S, rows): blockIdx.x is the fastest-varying part of the linear id by
   // which workgroups are dealt to the XCDs, so the S workgroups of a segment share an XCD
-  // BY_ROW: the items of the grid are the rows of the batch instead of its segments, and an XCD
+  // MODE with kPerRow: the items of the grid are the rows of the batch instead of its segments, and an XCD
   // (blockIdx.x) takes a run of consecutive rows, so that rows of one segment find its weights
   // in their XCD's L2 (dealt round the XCDs, eight-row segments were read by all eight of them:
   // 16 segments of 8 rows 8.8 us)
-  const int seg = BY_ROW ? blockIdx.x * gridDim.z + blockIdx.z : blockIdx.z * gridDim.x + blockIdx.x;
-  if (seg >= (BY_ROW ? n_tokens : n_segs)) {  // the grid is padded to whole rows of segments
+  const int seg = by_row(MODE) ? blockIdx.x * gridDim.z + blockIdx.z : blockIdx.z * gridDim.x + blockIdx.x;
+  if (seg >= (by_row(MODE) ? n_tokens : n_segs)) {  // the grid is padded to whole rows of segments
     if (threadIdx.x < 64) leave_launch_idle(header, (int)(gridDim.x * gridDim.y * gridDim.z), (int)threadIdx.x);
     return;
   }
-  add_lora_fused_body<DT, R, G, RB, BY_ROW>(seg_starts, A_ptrs, B_ptrs, x, y, kslice, cslice, h_in, h_out,
+  add_lora_fused_body<DT, R, G, RB, MODE>(seg_starts, A_ptrs, B_ptrs, x, y, kslice, cslice, h_in, h_out,
                                             n_tokens, S, offA, offB, exch, header, scale, spin_limit, seg,
                                             (int)blockIdx.y, n_segs);
 }
@@ -413,7 +414,7 @@ __global__ __launch_bounds__(320) void add_lora_fused_kernel(
 // the projection's x, y and pointer arrays; each projection exchanges through its own
 // stretch of the workspace.  Used while all workgroups of the launch are resident together
 // (small batches); larger launches take the pipelined kernel in fused_multi_kernel.hip.
-template <class DT, int R, int G, bool BY_ROW>
+template <class DT, int R, int G, int MODE>
 __global__ __launch_bounds__(320) void add_lora_fused_side_kernel(
     const int32_t* __restrict__ seg_starts, int kslice, int cslice, int h_in, int h_out, int n_tokens,
     int S, long long offA, long long offB, unsigned long long* exch, unsigned long long* header,
@@ -421,13 +422,13 @@ __global__ __launch_bounds__(320) void add_lora_fused_side_kernel(
   // grid (segments of a row, S, rows of segments x projections), as for the single add-on
   const int row = __builtin_amdgcn_readfirstlane((int)(((float)blockIdx.z + 0.5f) / (float)n_proj));
   const int z = (int)blockIdx.z - row * n_proj;
-  // BY_ROW: items are rows of the batch, an XCD (blockIdx.x) taking a run of consecutive rows
-  const int seg = BY_ROW ? blockIdx.x * ((int)gridDim.z / n_proj) + row : row * gridDim.x + blockIdx.x;
-  if (seg >= (BY_ROW ? n_tokens : n_segs)) {  // the grid is padded to whole rows of segments
+  // MODE with kPerRow: items are rows of the batch, an XCD (blockIdx.x) taking a run of consecutive rows
+  const int seg = by_row(MODE) ? blockIdx.x * ((int)gridDim.z / n_proj) + row : row * gridDim.x + blockIdx.x;
+  if (seg >= (by_row(MODE) ? n_tokens : n_segs)) {  // the grid is padded to whole rows of segments
     if (threadIdx.x < 64) leave_launch_idle(header, (int)(gridDim.x * gridDim.y * gridDim.z), (int)threadIdx.x);
     return;
   }
-  add_lora_fused_body<DT, R, G, 1, BY_ROW>(
+  add_lora_fused_body<DT, R, G, 1, MODE>(
       seg_starts, reinterpret_cast<const uint16_t* const*>(tab.A_ptrs[z]),
       reinterpret_cast<const uint16_t* const*>(tab.B_ptrs[z]),
       reinterpret_cast<const uint16_t*>(tab.x[z]), reinterpret_cast<uint16_t*>(tab.y[z]), kslice, cslice,
@@ -457,10 +458,10 @@ hipError_t launch_workspace_init(void* p, size_t bytes, size_t header_offset, hi
   return hipGetLastError();
 }
 
-template <class DT, int R, int G, int RB, bool BY_ROW>
+template <class DT, int R, int G, int RB, int MODE>
 static hipError_t launch_fused_t(const FusedArgs& a, hipStream_t st) {
-  const int items = BY_ROW ? a.n_tokens : a.n_segs;
-  hipLaunchKernelGGL((add_lora_fused_kernel<DT, R, G, RB, BY_ROW>),
+  const int items = by_row(MODE) ? a.n_tokens : a.n_segs;
+  hipLaunchKernelGGL((add_lora_fused_kernel<DT, R, G, RB, MODE>),
                      dim3((unsigned)fused_grid_x(items), (unsigned)a.S,
                           (unsigned)((items + fused_grid_x(items) - 1) / fused_grid_x(items))),
                      dim3(320), 0, st, a.seg_starts, (const uint16_t* const*)a.A_ptrs,
@@ -470,10 +471,10 @@ static hipError_t launch_fused_t(const FusedArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <class DT, int R, int G, bool BY_ROW>
+template <class DT, int R, int G, int MODE>
 static hipError_t launch_fused_side_t(const FusedArgs& a, hipStream_t st) {
-  const int items = BY_ROW ? a.n_tokens : a.n_segs;
-  hipLaunchKernelGGL((add_lora_fused_side_kernel<DT, R, G, BY_ROW>),
+  const int items = by_row(MODE) ? a.n_tokens : a.n_segs;
+  hipLaunchKernelGGL((add_lora_fused_side_kernel<DT, R, G, MODE>),
                      dim3((unsigned)fused_grid_x(items), (unsigned)a.S,
                           (unsigned)(fused_grid_items(items) / fused_grid_x(items) * a.n_proj)),
                      dim3(320), 0, st, a.seg_starts, a.kslice, a.cslice, a.h_in, a.h_out, a.n_tokens, a.S,
@@ -483,9 +484,14 @@ static hipError_t launch_fused_side_t(const FusedArgs& a, hipStream_t st) {
 
 template <class DT, int R, int G>
 static hipError_t launch_fused_rb(const FusedArgs& a, hipStream_t st) {
-  if (a.n_proj > 0) return a.by_rows ? launch_fused_side_t<DT, R, G, true>(a, st) : launch_fused_side_t<DT, R, G, false>(a, st);
-  if (a.by_rows) return launch_fused_t<DT, R, G, 1, true>(a, st);
-  return launch_fused_t<DT, R, G, 1, false>(a, st);
+  const bool streamed = stream_weights(a.by_rows, a.n_tokens, a.n_segs, a.r, (long long)a.h_in + a.h_out);
+  if (a.n_proj > 0) {
+    if (!a.by_rows) return launch_fused_side_t<DT, R, G, kPerSegment | kStreamed>(a, st);  // ahead at every size (seven segments: 8.4 -> 7.9 us)
+    return streamed ? launch_fused_side_t<DT, R, G, kPerRow | kStreamed>(a, st) : launch_fused_side_t<DT, R, G, kPerRow>(a, st);
+  }
+  if (a.by_rows)
+    return streamed ? launch_fused_t<DT, R, G, 1, kPerRow | kStreamed>(a, st) : launch_fused_t<DT, R, G, 1, kPerRow>(a, st);
+  return streamed ? launch_fused_t<DT, R, G, 1, kPerSegment | kStreamed>(a, st) : launch_fused_t<DT, R, G, 1, kPerSegment>(a, st);
 }
 
 template <class DT, int R>

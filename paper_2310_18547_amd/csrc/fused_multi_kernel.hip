@@ -243,7 +243,7 @@ __global__ __launch_bounds__(320) void add_lora_fused_multi_kernel(
     const __amdgpu_buffer_rsrc_t rA = make_buffer(A + offA + (long long)k0 * R, (uint32_t)nchunks * 16u);
     r.xr = buffer_load128(rX, tid < cpr ? (uint32_t)tid * 16u : kOutOfRange);
 #pragma unroll
-    for (int u = 0; u < U; ++u) r.a[u] = buffer_load128(rA, (uint32_t)(u * NT + tid) * 16u);
+    for (int u = 0; u < U; ++u) r.a[u] = buffer_load128<kNonTemporal>(rA, (uint32_t)(u * NT + tid) * 16u);
     __builtin_amdgcn_sched_barrier(0);
   };
   auto issue_b_at = [&](BRegs& r, int row, const uint16_t* yp, const uint16_t* B) {
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(320) void add_lora_fused_multi_kernel(
     const __amdgpu_buffer_rsrc_t rY = make_buffer(yp + (long long)row * h_out + col_lo, (uint32_t)ncols * 2u);
 #pragma unroll
     for (int j = 0; j < JL; ++j)
-      r.b[j] = buffer_load128(rB, col_active ? b_row0 + (uint32_t)j * row_bytes_out + (uint32_t)cc * 16u : kOutOfRange);
+      r.b[j] = buffer_load128<kNonTemporal>(rB, col_active ? b_row0 + (uint32_t)j * row_bytes_out + (uint32_t)cc * 16u : kOutOfRange);
     r.yq = buffer_load128(rY, (cg == 0 && col_active) ? (uint32_t)cc * 16u : kOutOfRange);
     __builtin_amdgcn_sched_barrier(0);
   };

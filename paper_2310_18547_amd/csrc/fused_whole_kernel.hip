@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void add_lora_whole_kernel(
       const bool active = cc * 8 < ncols;
 #pragma unroll
       for (int j = 0; j < JL; ++j)
-        b[j] = buffer_load128(rB, active ? b_row0 + (uint32_t)j * row_bytes_out + (uint32_t)cc * 16u : kOutOfRange);
+        b[j] = buffer_load128<BY_ROW ? 0 : kNonTemporal>(rB, active ? b_row0 + (uint32_t)j * row_bytes_out + (uint32_t)cc * 16u : kOutOfRange);
       yq = buffer_load128(rY, (cg == 0 && active) ? (uint32_t)cc * 16u : kOutOfRange);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void add_lora_whole_kernel(
       if (pass != 0) {
 #pragma unroll
         for (int j = 0; j < JL; ++j)
-          b[j] = buffer_load128(rB, active ? b_row0 + (uint32_t)j * row_bytes_out + (uint32_t)c * 16u : kOutOfRange);
+          b[j] = buffer_load128<BY_ROW ? 0 : kNonTemporal>(rB, active ? b_row0 + (uint32_t)j * row_bytes_out + (uint32_t)c * 16u : kOutOfRange);
         yq = buffer_load128(rY, (cg == 0 && active) ? (uint32_t)c * 16u : kOutOfRange);
       }
       float o[8];

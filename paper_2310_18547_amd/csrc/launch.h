@@ -160,6 +160,18 @@ inline long long fused_grid_items(long long items) {
   return (items + gx - 1) / gx * gx;
 }
 
+// Whether a launch of the single-row kernels reads its weights past the caches (kStreamed): from 8 MB
+// of weights on (`width` = input and output width together, or the one a step reads), and per row
+// of the batch only where an adapter serves at most three rows on average.  Measured, plain against
+// streamed, us per call: 4096 -> 4096, rank 16, 64 segments 6.35 -> 5.81; 13824 -> 5120, rank 64, 64 segments
+// 36.2 -> 33.1; 13824-wide shrink, 64 rows of 39 adapters 7.45 -> 7.08; 45 rows of 18 adapters, 5120 wide,
+// rank 32 10.6 -> 10.3; but three segments of 4096 -> 12424, rank 32 (3 MB) 6.51 -> 6.73, 13 segments of a
+// 4096-wide rank-64 shrink (7 MB) 5.37 -> 5.45, and 90 rows of one adapter 11.2 -> 14.2, which the hint
+// takes out of the caches before the next row wants it.
+inline bool stream_weights(bool by_rows, int n_tokens, int n_segs, int r, long long width) {
+  return n_segs * width * r >= (4LL << 20) && (!by_rows || n_tokens <= 3LL * n_segs);
+}
+
 size_t tile_lds_bytes(int r, int kslice, int cslice);
 hipError_t launch_add_lora_whole(const WholeArgs& a, hipStream_t st);
 hipError_t launch_add_lora_tile(const TileArgs& a, hipStream_t st);

@@ -17,10 +17,10 @@ namespace sgmv {
 
 // grid (fused_grid_x, S, rows of segments), 320 threads: four stream waves, one exchange wave.
 //   exch   [S][n_tokens][R] 64-bit words {fp32 value (high), tag (low)}
-// BY_ROW: the grid's items are the n_tokens rows of the batch, not its segments; a row's
+// MODE with kPerRow: the grid's items are the n_tokens rows of the batch, not its segments; a row's
 // workgroups look the row's segment up in seg_starts, so segments may have any length, and an
 // XCD (blockIdx.x) takes a run of consecutive rows (as in the add-on kernel, fused_kernel.hip).
-template <class DT, int R, bool BY_ROW>
+template <class DT, int R, int MODE>
 __global__ __launch_bounds__(320) void shrink_handoff_kernel(
     const int32_t* __restrict__ seg_starts, const uint16_t* const* __restrict__ A_ptrs,
     const uint16_t* __restrict__ x, float* __restrict__ v, int kslice, int h_in, int n_tokens, int S,
@@ -35,15 +35,15 @@ __global__ __launch_bounds__(320) void shrink_handoff_kernel(
   const int n_workgroups = (int)(gridDim.x * gridDim.y * gridDim.z);
   // blockIdx.x is the fastest-varying part of the linear id by which workgroups are dealt to
   // the XCDs, so the S workgroups of a segment share an XCD
-  const int item = BY_ROW ? blockIdx.x * gridDim.z + blockIdx.z : blockIdx.z * gridDim.x + blockIdx.x;
+  const int item = by_row(MODE) ? blockIdx.x * gridDim.z + blockIdx.z : blockIdx.z * gridDim.x + blockIdx.x;
   const int s = blockIdx.y;
-  if (item >= (BY_ROW ? n_tokens : n_segs)) {  // the grid is padded to whole rows of items
+  if (item >= (by_row(MODE) ? n_tokens : n_segs)) {  // the grid is padded to whole rows of items
     if (wave == 0) leave_launch_idle(header, n_workgroups, lane);
     return;
   }
   int lo, hi;
   const uint16_t* A;
-  if constexpr (BY_ROW) {
+  if constexpr (by_row(MODE)) {
     const int found = segment_of_row(seg_starts, n_segs, item, lane);
     lo = item;
     hi = found < n_segs ? item + 1 : item;  // a row behind the last segment end: nothing to do
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(320) void shrink_handoff_kernel(
     const uint4 xr = buffer_load128(rX, tid < cpr ? (uint32_t)tid * 16u : kOutOfRange);
     uint4 a[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = buffer_load128(rA, (uint32_t)(u * NT + tid) * 16u);
+    for (int u = 0; u < U; ++u) a[u] = buffer_load128<weights_aux(MODE)>(rA, (uint32_t)(u * NT + tid) * 16u);
     if (row != lo) lds_barrier();  // (a) xs / red free
     // chunks that do not exist arrive as zeros, so xs is always fully defined
     store128(&xs[tid * 8], xr);
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(320) void shrink_handoff_kernel(
     for (int base = 0; base < nchunks; base += NT * U) {
       if (base != 0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = buffer_load128(rA, (uint32_t)(base + u * NT + tid) * 16u);
+        for (int u = 0; u < U; ++u) a[u] = buffer_load128<weights_aux(MODE)>(rA, (uint32_t)(base + u * NT + tid) * 16u);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -142,11 +142,11 @@ __global__ __launch_bounds__(320) void shrink_handoff_kernel(
   }
 }
 
-template <class DT, int R, bool BY_ROW>
+template <class DT, int R, int MODE>
 static hipError_t launch_shrink_handoff_b(const FusedArgs& a, float* v, hipStream_t st) {
-  const int items = BY_ROW ? a.n_tokens : a.n_segs;
+  const int items = by_row(MODE) ? a.n_tokens : a.n_segs;
   const int gx = fused_grid_x(items);
-  hipLaunchKernelGGL((shrink_handoff_kernel<DT, R, BY_ROW>), dim3((unsigned)gx, (unsigned)a.S, (unsigned)((items + gx - 1) / gx)),
+  hipLaunchKernelGGL((shrink_handoff_kernel<DT, R, MODE>), dim3((unsigned)gx, (unsigned)a.S, (unsigned)((items + gx - 1) / gx)),
                      dim3(320), 0, st, a.seg_starts, (const uint16_t* const*)a.A_ptrs, (const uint16_t*)a.x, v,
                      a.kslice, a.h_in, a.n_tokens, a.S, a.offA, a.exch, a.header, a.spin_limit, a.n_segs);
   return hipGetLastError();
@@ -154,7 +154,11 @@ static hipError_t launch_shrink_handoff_b(const FusedArgs& a, float* v, hipStrea
 
 template <class DT, int R>
 static hipError_t launch_shrink_handoff_t(const FusedArgs& a, float* v, hipStream_t st) {
-  return a.by_rows ? launch_shrink_handoff_b<DT, R, true>(a, v, st) : launch_shrink_handoff_b<DT, R, false>(a, v, st);
+  const bool streamed = stream_weights(a.by_rows, a.n_tokens, a.n_segs, a.r, a.h_in);
+  if (a.by_rows)
+    return streamed ? launch_shrink_handoff_b<DT, R, kPerRow | kStreamed>(a, v, st) : launch_shrink_handoff_b<DT, R, kPerRow>(a, v, st);
+  return streamed ? launch_shrink_handoff_b<DT, R, kPerSegment | kStreamed>(a, v, st)
+                  : launch_shrink_handoff_b<DT, R, kPerSegment>(a, v, st);
 }
 
 template <class DT>

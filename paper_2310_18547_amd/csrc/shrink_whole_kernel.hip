@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) void shrink_whole_kernel(
     for (int i = 0; i < XL; ++i) xr[i] = buffer_load128(rX, (uint32_t)(i * NT + tid) * 16u);  // zeros beyond the row
     uint4 a[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = buffer_load128_at(rA, a_lane, (uint32_t)u * (NT * 16u));
+    for (int u = 0; u < U; ++u) a[u] = buffer_load128_at<BY_ROW ? 0 : kNonTemporal>(rA, a_lane, (uint32_t)u * (NT * 16u));
     const float before = tid < R ? v[(long long)row * R + tid] : 0.f;
 #pragma unroll
     for (int i = 0; i < XL; ++i) store128(&xs[(i * NT + tid) * 8], xr[i]);
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void shrink_whole_kernel(
     for (int batch = 0; batch < nbatch; ++batch) {
       if (batch != 0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = buffer_load128_at(rA, a_lane, (uint32_t)(batch * U + u) * (NT * 16u));
+        for (int u = 0; u < U; ++u) a[u] = buffer_load128_at<BY_ROW ? 0 : kNonTemporal>(rA, a_lane, (uint32_t)(batch * U + u) * (NT * 16u));
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
