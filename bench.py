@@ -59,11 +59,6 @@ PAPER_A100_US = {"distinct_b64": [116.0, 75.0], "distinct_b1": [37.0, 42.0]}
 KERNEL_NAMES = None  # filled after the binding is imported
 
 
-def expand_kernel_name(w) -> str:
-    """The MFMA expand kernel the library runs for this workload (rank 64 and binary16 with segments of at least a 64-row block: row-wise)."""
-    return "expand_rowwise_kernel" if (w.r > 32 or w.dtype == "f16") and w.max_seg_len >= 64 else "expand_matrix_kernel"
-
-
 def make_workload(name: str, seed: int, layers: int = 0):
     """Named workloads.  Generic decode shapes: distinct_b{B}[_h{H}][_o{H_OUT}][_r{R}][_{dtype}]."""
     import sgmv_workloads as wl
@@ -332,7 +327,7 @@ def run_timeline(args):
         if op == "shrink":
             kernel, call = "shrink_stream_kernel", lambda layer, k: d.shrink(v, layer, k)
         else:
-            kernel, call = expand_kernel_name(w), lambda layer, k: d.expand(v, layer, k)
+            kernel, call = "expand_matrix_kernel", lambda layer, k: d.expand(v, layer, k)
     trace = torch.zeros(n_wg * 10, dtype=torch.int64, device="cuda:0")
     for i in range(64):                       # warm, untraced
         call(i % w.num_layers, i % args.sets)
@@ -461,8 +456,6 @@ def bench_one(args, op, d, w, probe):
     if op == "add_lora":
         plan = B.sgmv_plan_add_lora(d.problem, w.n_segs, P)
         kernel, launches, slices, workgroups = KERNEL_NAMES[plan.kernel], plan.launches, plan.slices, plan.workgroups
-        if plan.kernel == B.KERNEL_MATRIX:
-            kernel = kernel.replace("expand_matrix_kernel", expand_kernel_name(w))
     else:
         if op == "shrink":  # asked of the library
             sp = B.sgmv_plan_shrink(d.problem, w.n_segs)
@@ -473,7 +466,7 @@ def bench_one(args, op, d, w, probe):
         kernel = {("shrink", False): "shrink_vector_kernel + shrink_reduce_kernel",
                   ("shrink", True): "shrink_stream_kernel + shrink_reduce_kernel",
                   ("expand", False): "expand_vector_kernel",
-                  ("expand", True): "finalize_v_kernel + " + expand_kernel_name(w)}[(op, long_segments)]
+                  ("expand", True): "finalize_v_kernel + expand_matrix_kernel"}[(op, long_segments)]
         launches, slices, workgroups = (1 if kernel == "expand_vector_kernel" else 2), None, None
         if op == "expand" and not long_segments and ep.lds_bytes >= 6144:   # the partial sums of three waves are in LDS
             kernel = "expand_split_kernel"

@@ -310,12 +310,11 @@ int sgmv_add_lora_static(const sgmv_problem* p, void* y, const void* x,
  * segments (per row, as under SGMV_PATH_ROWS) and segments of a few rows
  * (max_seg_len from 2 up to what the single-launch MFMA kernel takes) while the
  * workgroups of all add-ons fit on the chip together, and in groups of as many
- * as fit beyond that.  On long segments (the MFMA
- * kernels) two or three add-ons whose x_i are the same buffer share the shrink's
- * pass over x when the workspace has the size of sgmv_workspace_bytes_multi
- * (ranks up to 32).  Otherwise the call is the same as n_proj calls of
- * sgmv_add_lora in order (sgmv_plan_add_lora reports this case: it does not
- * know whether the x_i coincide).  The result of every add-on
+ * as fit beyond that.  On long segments (the MFMA kernels) up to three add-ons
+ * go into one launch of each kernel when the workspace has the size of
+ * sgmv_workspace_bytes_multi, and those whose x_i are the same buffer share the
+ * shrink's pass over x.  Otherwise the call is the same as n_proj calls of
+ * sgmv_add_lora in order (sgmv_plan_add_lora reports which).  The result of every add-on
  * equals that of a separate sgmv_add_lora call up to the order in which the
  * fp32 sums are taken (the single-launch kernels split the same sums over
  * lanes differently). */

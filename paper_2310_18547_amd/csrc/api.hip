@@ -91,7 +91,7 @@ constexpr int kMatrixMinSegLen = 6;
 // segment on while the segments are few (32 segments of 2 / 4 rows: 21.7 / 21.9 us against 23.1 /
 // 31.4; the Uniform mix of 39 segments: 26.3 against 34.6; 64 segments of 4 rows: 36.9 against 34.0).
 constexpr int kMatrixFewSegments = 48;
-constexpr int kMatrixWorkgroups = 448; // workgroups the MFMA shrink aims for
+constexpr int kMatrixWaves = 4096;     // waves the MFMA shrink aims for (four per SIMD)
 
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -182,18 +182,25 @@ bool expand_use_matrix(const sgmv_problem* p, int n_segs) {
   return len >= 2;
 }
 
-// Split-K shape of the MFMA shrink: row blocks of 64 rows times ksplit slices should
-// give every compute unit a workgroup; slices are multiples of the MFMA depth (32).
-void choose_split_matrix(const sgmv_problem* p, int n_segs, int* ksplit, int* kslice) {
+// Split-K shape of the MFMA shrink of n_proj add-ons: about kMatrixWaves waves in flight, a power of two
+// slices, so that a slice's workgroups (consecutive ids) meet on the same XCDs and its part of A_i in
+// their L2s (8192 wide, rank 16, 4814 rows, 8 / 11 / 16 slices: 18.6 / 19.9 / 17.4 us), and no more than leaves
+// the partial sums, written and read again, half the bytes of x (11432 wide, rank 64, three add-ons of 724
+// rows, the whole call at 4 / 8 / 15 slices: 45.0 / 32.3 / 33.1 us; 3272 wide, 3254 rows, 2 / 4 / 13: 61.3 / 62.4 / 67.1).
+void choose_split_matrix(const sgmv_problem* p, int n_segs, int n_proj, bool same_x, int* ksplit, int* kslice) {
   const int cap = split_cap(p->n_tokens);
-  const int blocks = p->n_tokens / 64 + (n_segs + 1) / 2;
-  int s = p->ksplit > 0 ? p->ksplit : ceil_div(kMatrixWorkgroups, blocks > 0 ? blocks : 1);
-  const int most = p->h_in / 256 > 0 ? p->h_in / 256 : 1;  // keep slices >= one LDS chunk
+  int s = p->ksplit;
+  if (s == 0) {
+    const bool shared = same_x && shrink_shared_fits(p->r, n_proj);
+    const int rows = shrink_stream_rows(p->r, shared ? n_proj : 1);
+    const long long blocks = (p->n_tokens / rows + (n_segs + 1) / 2) * (long long)(shared ? 1 : n_proj);
+    const long long waves = (blocks > 0 ? blocks : 1) * (rows / 16);
+    const long long by_partials = p->h_in / (8LL * p->r * n_proj);
+    s = 1;
+    while (s * 3 * waves <= 2LL * kMatrixWaves && (s < 4 || s * 3 <= 2 * by_partials)) s *= 2;
+  }
+  const int most = p->h_in / 128 > 0 ? p->h_in / 128 : 1;  // keep slices of at least one chunk
   if (s > most) s = most;
-  // slices no deeper than what stays resident in LDS (the streaming shrink), if the
-  // workspace has room for that many partial sums
-  const int need = ceil_div(p->h_in, 512);
-  if (p->ksplit == 0 && s < need) s = need;
   if (s > cap) s = cap;
   if (s < 1) s = 1;
   const int len = ceil_div(ceil_div(p->h_in, s), 32) * 32;
@@ -512,7 +519,11 @@ ShrinkArgs make_shrink(const sgmv_problem* p, const Scratch& sc, const void* x,
   a.seg_starts = seg_starts;
   a.partials = sc.partials;
   a.header = sc.header;
-  a.n_shared = 0;
+  a.n_proj = 1;
+  a.same_x = false;
+  a.xs[0] = x;
+  a.As[0] = A_ptrs;
+  a.partials_of[0] = sc.partials;
   return a;
 }
 
@@ -537,7 +548,6 @@ ExpandArgs make_expand(const sgmv_problem* p, void* y, const float* v_parts, int
   a.scale = scale;
   a.vh = a.vl = nullptr;
   a.undo = nullptr;
-  a.operands_ready = false;
   a.header = nullptr;
   a.by_rows = false;
   return a;
@@ -665,7 +675,7 @@ int plan_single(const sgmv_problem* p, int n_segs, SinglePlan* pl) {
     if (p->path == SGMV_PATH_FUSED) return SGMV_ERR_UNSUPPORTED;
   }
   if (use_matrix(p, n_segs)) {
-    choose_split_matrix(p, n_segs, &pl->ksplit, &pl->kslice);
+    choose_split_matrix(p, n_segs, 1, false, &pl->ksplit, &pl->kslice);
     pl->kernel = SGMV_KERNEL_MATRIX;
     return SGMV_OK;
   }
@@ -750,7 +760,7 @@ int plan_shrink(const sgmv_problem* p, int n_segs, ShrinkPlan* pl) {
     return SGMV_OK;
   }
   if (use_matrix(p, n_segs)) {
-    choose_split_matrix(p, n_segs, &pl->ksplit, &pl->kslice);
+    choose_split_matrix(p, n_segs, 1, false, &pl->ksplit, &pl->kslice);
     pl->kernel = SGMV_KERNEL_MATRIX;
     return SGMV_OK;
   }
@@ -970,7 +980,7 @@ int sgmv_expand(const sgmv_problem* p, void* y, const float* v, const void* cons
     if (launch_expand_vector(a, st) != hipSuccess) return SGMV_ERR_LAUNCH;
   } else if (have_ws && expand_use_matrix(p, n_segs)) {
     set_operands(&a, caller_scratch(p), p->n_tokens, p->r);
-    if (launch_expand_matrix(a, st) != hipSuccess) return SGMV_ERR_LAUNCH;
+    if (launch_expand_matrix(&a, 1, st) != hipSuccess) return SGMV_ERR_LAUNCH;
   } else {
     if (launch_expand_vector(a, st) != hipSuccess) return SGMV_ERR_LAUNCH;
   }
@@ -1051,7 +1061,7 @@ int add_lora_launch(const sgmv_problem* p, const Scratch& sc, void* y, const voi
       ExpandArgs e = make_expand(p, y, sa.partials, sa.ksplit, A_ptrs, B_ptrs, seg_starts, n_segs,
                                  layer_idx, scale);
       set_operands(&e, sc, p->n_tokens, p->r);
-      return launch_expand_matrix(e, st) == hipSuccess ? SGMV_OK : SGMV_ERR_LAUNCH;
+      return launch_expand_matrix(&e, 1, st) == hipSuccess ? SGMV_OK : SGMV_ERR_LAUNCH;
     }
     default: {
       ShrinkArgs sa = make_shrink(p, sc, x, A_ptrs, seg_starts, n_segs, layer_idx);
@@ -1207,50 +1217,42 @@ int sgmv_add_lora_multi(const sgmv_problem* p, int32_t n_proj, void* const* ys,
                                                             : launch_add_lora_fused_multi(f, st);
     return err == hipSuccess ? SGMV_OK : SGMV_ERR_LAUNCH;
   }
-  // Long segments on the MFMA kernels, all add-ons reading the same x (q / k / v or gate / up of a
-  // prefill batch): their shrinks share one pass over x, which is most of a shrink's bytes; then
-  // every add-on's operand preparation and expand in turn.  Needs the larger workspace of
-  // sgmv_workspace_bytes_multi for the partial sums of the second and third add-on.
-  {
-    bool same_x = n_proj >= 2 && n_proj <= kSharedShrinkMost;
-    for (int i = 1; i < n_proj && same_x; ++i) same_x = xs[i] == xs[0];
-    SinglePlan pl;
-    if (same_x && plan_single(p, n_segs, &pl) == SGMV_OK && pl.kernel == SGMV_KERNEL_MATRIX) {
-      const Scratch sc = caller_scratch(p);
-      ShrinkArgs sa = make_shrink(p, sc, xs[0], A_ptrs[0], seg_starts, n_segs, layer_idx);
-      sa.ksplit = pl.ksplit;
-      sa.kslice = pl.kslice;
-      if (shrink_shared_fits(sa, n_proj) &&
-          p->workspace_bytes >= sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj)) {
-        // the first add-on's partial sums where a single call keeps them, the others' behind the
-        // single-call workspace (the exchange words in between are left alone: the single-launch
-        // kernels rely on what their tags say)
-        const size_t parts = partial_bytes(p->n_tokens, p->r);
-        char* const extra = static_cast<char*>(p->workspace) + sgmv_workspace_bytes(p->n_tokens, p->r);
-        sa.n_shared = n_proj;
-        for (int i = 0; i < n_proj; ++i) {
-          sa.A_shared[i] = A_ptrs[i];
-          sa.partials_shared[i] = i == 0 ? sc.partials : reinterpret_cast<float*>(extra + (size_t)(i - 1) * parts);
-        }
-        if (launch_shrink_matrix_shared(sa, st) != hipSuccess) return SGMV_ERR_LAUNCH;
-        // operand pairs of all add-ons in one launch (the first add-on's where a single call keeps
-        // them, the others' behind the extra partial sums), then the expands
-        ExpandArgs es[kSharedShrinkMost];
-        const size_t ops = operand_bytes(p->n_tokens, p->r);
-        for (int i = 0; i < n_proj; ++i) {
-          es[i] = make_expand(p, ys[i], sa.partials_shared[i], sa.ksplit, A_ptrs[i], B_ptrs[i], seg_starts, n_segs,
-                              layer_idx, scale);
-          Scratch own = sc;
-          if (i > 0) own.operands = extra + (size_t)(n_proj - 1) * parts + (size_t)(i - 1) * ops;
-          set_operands(&es[i], own, p->n_tokens, p->r);
-          es[i].operands_ready = true;
-        }
-        if (launch_finalize_shared(es, n_proj, st) != hipSuccess) return SGMV_ERR_LAUNCH;
-        for (int i = 0; i < n_proj; ++i)
-          if (launch_expand_matrix(es[i], st) != hipSuccess) return SGMV_ERR_LAUNCH;
-        return SGMV_OK;
+  // Long segments on the MFMA kernels: up to three add-ons per launch of each kernel (one pass over x
+  // where they read the same one).  Needs the larger workspace of sgmv_workspace_bytes_multi for the
+  // partial sums and operands of the second and third add-on.
+  SinglePlan pl;
+  if (n_proj >= 2 && plan_single(p, n_segs, &pl) == SGMV_OK && pl.kernel == SGMV_KERNEL_MATRIX &&
+      p->workspace_bytes >= sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj)) {
+    const Scratch sc = caller_scratch(p);
+    // the first add-on's partial sums and operands where a single call keeps them, the others' behind the
+    // single-call workspace (the exchange words in between are left alone: the single-launch kernels
+    // rely on what their tags say)
+    const size_t parts = partial_bytes(p->n_tokens, p->r), ops = operand_bytes(p->n_tokens, p->r);
+    char* const extra = static_cast<char*>(p->workspace) + sgmv_workspace_bytes(p->n_tokens, p->r);
+    for (int first = 0; first < n_proj; first += kSharedShrinkMost) {
+      const int count = n_proj - first < kSharedShrinkMost ? n_proj - first : kSharedShrinkMost;
+      ShrinkArgs sa = make_shrink(p, sc, xs[first], A_ptrs[first], seg_starts, n_segs, layer_idx);
+      sa.n_proj = count;
+      sa.same_x = true;
+      for (int i = 0; i < count; ++i) {
+        sa.same_x = sa.same_x && xs[first + i] == xs[first];
+        sa.xs[i] = xs[first + i];
+        sa.As[i] = A_ptrs[first + i];
+        if (i > 0) sa.partials_of[i] = reinterpret_cast<float*>(extra + (size_t)(i - 1) * (parts + ops));
       }
+      choose_split_matrix(p, n_segs, count, sa.same_x, &sa.ksplit, &sa.kslice);
+      if (launch_shrink_matrix(sa, st) != hipSuccess) return SGMV_ERR_LAUNCH;
+      ExpandArgs es[kSharedShrinkMost];
+      for (int i = 0; i < count; ++i) {
+        es[i] = make_expand(p, ys[first + i], sa.partials_of[i], sa.ksplit, A_ptrs[first + i], B_ptrs[first + i], seg_starts,
+                            n_segs, layer_idx, scale);
+        Scratch own = sc;
+        if (i > 0) own.operands = extra + (size_t)(i - 1) * (parts + ops) + parts;
+        set_operands(&es[i], own, p->n_tokens, p->r);
+      }
+      if (launch_expand_matrix(es, count, st) != hipSuccess) return SGMV_ERR_LAUNCH;
     }
+    return SGMV_OK;
   }
   // any other shape: one add-on after the other
   for (int i = 0; i < n_proj; ++i) {
@@ -1381,7 +1383,14 @@ int sgmv_plan_add_lora(const sgmv_problem* p, int32_t n_segs, int32_t n_proj, sg
       plan->workgroups = pl.ksplit * n_segs;
       break;
   }
-  plan->launches *= n_proj;  // a multi-projection call that is not batched runs them in turn
+  if (pl.kernel == SGMV_KERNEL_MATRIX && n_proj > 1 &&
+      p->workspace_bytes >= sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj)) {
+    plan->launches *= ceil_div(n_proj, kSharedShrinkMost);
+    // as for add-ons on one x, which a caller of several projections usually has
+    choose_split_matrix(p, n_segs, n_proj < kSharedShrinkMost ? n_proj : kSharedShrinkMost, true, &pl.ksplit, &pl.kslice);
+    plan->slices = pl.ksplit;
+  } else
+    plan->launches *= n_proj;  // a multi-projection call that is not batched runs them in turn
   return SGMV_OK;
 }
 

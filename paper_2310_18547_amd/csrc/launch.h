@@ -24,7 +24,7 @@ constexpr size_t kWorkspaceHeader = kWorkspaceErrorOffset + 256;
 // Upper bound of the split-K factor.
 constexpr int kMaxKSplit = 64;
 
-// Most add-ons whose MFMA shrinks share one pass over a common x.
+// Most add-ons one launch of the MFMA kernels takes.
 constexpr int kSharedShrinkMost = 3;
 
 struct ShrinkArgs {
@@ -39,11 +39,13 @@ struct ShrinkArgs {
   const int32_t* seg_starts;
   float* partials;           // [ksplit][n_tokens][r]
   unsigned long long* header;// workspace header or nullptr (only trace builds look at it)
-  // launch_shrink_matrix_shared only: n_shared add-ons on the same x, each with its pointer array
-  // and its own partial sums
-  int n_shared;
-  const void* const* A_shared[kSharedShrinkMost];
-  float* partials_shared[kSharedShrinkMost];
+  // launch_shrink_matrix only: n_proj add-ons in one launch, each with its input, pointer array and
+  // partial sums (same_x: all inputs are the same, one pass over it where the slices of A_i fit)
+  int n_proj;
+  bool same_x;
+  const void* xs[kSharedShrinkMost];
+  const void* const* As[kSharedShrinkMost];
+  float* partials_of[kSharedShrinkMost];
 };
 
 // ExpandArgs::threads value that selects expand_split_kernel (256 threads whose four waves divide
@@ -67,7 +69,6 @@ struct ExpandArgs {
   uint16_t* vh;
   uint16_t* vl;
   float* undo;
-  bool operands_ready;       // vh / vl / undo are already written (launch_finalize_shared)
   unsigned long long* header;// workspace header or nullptr (only trace builds look at it)
 };
 
@@ -188,12 +189,10 @@ hipError_t launch_shrink_vector(const ShrinkArgs& a, hipStream_t st);
 hipError_t launch_shrink_reduce(float* v, const ShrinkArgs& a, hipStream_t st);
 hipError_t launch_expand_vector(const ExpandArgs& a, hipStream_t st);
 hipError_t launch_shrink_matrix(const ShrinkArgs& a, hipStream_t st);
-// True when n_shared add-ons' slices of A_i fit in LDS side by side (launch_shrink_matrix_shared applies).
-bool shrink_shared_fits(const ShrinkArgs& a, int n_shared);
-// The MFMA shrink of a.n_shared add-ons on the same x in one pass (A_shared, partials_shared).
-hipError_t launch_shrink_matrix_shared(const ShrinkArgs& a, hipStream_t st);
-// v -> operand pairs of the n add-ons of a shared shrink in one launch (each es[i] with its own vh / vl / undo).
-hipError_t launch_finalize_shared(const ExpandArgs* es, int n, hipStream_t st);
-hipError_t launch_expand_matrix(const ExpandArgs& a, hipStream_t st);
+// Whether one pass over a common x serves n_shared add-ons, and the rows a workgroup then takes.
+bool shrink_shared_fits(int r, int n_shared);
+int shrink_stream_rows(int r, int n_shared);
+// v -> operand pairs, then y += v B_i, for n add-ons of one shape (each es[i] with its own operands).
+hipError_t launch_expand_matrix(const ExpandArgs* es, int n, hipStream_t st);
 
 }  // namespace sgmv

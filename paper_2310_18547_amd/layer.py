@@ -33,7 +33,7 @@ class LoraLayer:
         self.shapes = projection_shapes(h, ffn)
         self.A_ptrs, self.B_ptrs = A_ptrs, B_ptrs
         self.seg_starts, self.n_segs = seg_starts, n_segs
-        self.ws_bytes = max(B.sgmv_workspace_bytes(n_tokens, r), 256)
+        self.ws_bytes = max(B.sgmv_workspace_bytes_multi(n_tokens, r, max(len(g) for g in GROUPS)), 256)
         self.workspace = torch.empty(self.ws_bytes, dtype=torch.uint8, device=device)
         B.sgmv_workspace_init(self.workspace, self.ws_bytes)
         torch.cuda.synchronize(device)
