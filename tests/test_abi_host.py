@@ -535,3 +535,42 @@ def test_static_entry_point_rejects_before_touching_a_device():
     assert sg.sgmv_add_lora_static(small, 16, 16, 16, 16, 16, 4, 3, 1.0, check=False) == 6    # layer out of range
     assert sg.sgmv_add_lora_static(small, 16, 16, 16, 16, 16, 0, 0, 1.0, check=False) == 0    # nothing to do
     assert sg.STATIC_SCRATCH_BYTES == 9 << 20
+
+
+# The per-layer calls come from a C module: what it takes and what it refuses.
+def test_calls_take_positional_and_keyword_arguments():
+    p = sg.make_problem(sg.F16, 256, 256, 8, 1, 4, workspace_bytes=1 << 20)
+    host = np.zeros(64, np.int64)
+    # no rows' pointers: the library's own answer, as an exception or as a status
+    assert sg.sgmv_add_lora(p, None, host, host, host, host, 1, 0, 1.0, None, False) == 1
+    assert sg.sgmv_add_lora(p, None, host, host, host, host, n_segs=1, layer_idx=0, scale=1, check=False) == 1
+    assert sg.sgmv_shrink(p, v=None, x=16, A_ptrs=16, seg_starts=16, n_segs=np.int64(1), layer_idx=0, check=False) == 1
+    assert sg.sgmv_expand(p, None, 16, 16, 16, 1, 0, 1.0, check=False) == 1
+    assert sg.sgmv_add_lora_static(p, None, 16, 16, 16, 16, 1, 0, 1.0, check=False) == 1
+    with pytest.raises(sg.SgmvError, match="sgmv_add_lora"):
+        sg.sgmv_add_lora(p, None, host, host, host, host, 1, 0, 1.0)
+    for n in (9, 65):                                   # more add-ons than a call takes
+        assert sg.sgmv_add_lora_multi(p, *[[16] * n] * 4, 16, 1, 0, 1.0, check=False) == 2
+    args = [p, 16, 16, 16, 16, 16, 1, 0, 1.0]
+    for bad, kwargs in [(args[:-1], {}), (args + [None, True, 1], {}), (args, {"p": p}), (args, {"streams": None}),
+                        (["p"] + args[1:], {}), ([p, "y"] + args[2:], {}), (args[:6] + [1.5] + args[7:], {}),
+                        (args[:8] + ["1"], {})]:
+        with pytest.raises(TypeError):
+            sg.sgmv_add_lora(*bad, **kwargs)
+    with pytest.raises(AttributeError):                 # a stream is None, an int or has cuda_stream
+        sg.sgmv_add_lora(*args, stream=host)
+    with pytest.raises(IndexError):                     # one entry per add-on
+        sg.sgmv_add_lora_multi(p, [16, 16], [16, 16, 16], [16, 16], [16, 16], 16, 1, 0, 1.0)
+
+
+def test_long_segments_put_up_to_three_add_ons_into_a_launch():
+    for r in (16, 64):
+        room = sg.sgmv_workspace_bytes_multi(2000, r, 8)
+        for n_proj, launches in [(1, 3), (2, 3), (3, 3), (4, 6), (8, 9)]:
+            p = sg.make_problem(sg.BF16, 4096, 4096, r, 1, 2000, workspace=256, workspace_bytes=room, max_seg_len=500,
+                                workspace_ready=1)
+            rc, plan = sg.sgmv_plan_add_lora(p, 4, n_proj, check=False)
+            assert rc == 0 and plan.kernel == sg.KERNEL_MATRIX and plan.launches == launches
+            p.workspace_bytes = sg.sgmv_workspace_bytes(2000, r)     # room for one: in turn
+            rc, plan = sg.sgmv_plan_add_lora(p, 4, n_proj, check=False)
+            assert rc == 0 and plan.launches == 3 * n_proj

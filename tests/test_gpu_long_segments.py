@@ -1,0 +1,82 @@
+"""The MFMA kernels where their lists of work have edges, and the rounding of bfloat16 stores."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import sgmv_workloads as wl
+from helpers import decode64
+from test_gpu_parity import _dev, assert_parity
+
+pytestmark = pytest.mark.gpu
+
+# both sides of: a few-row segment (4 rows), a tile (16), two and four tiles of a block, a block (64) and the rows of
+# a shrink workgroup (64, 128); empty segments; more segments than a wave looks at in one round (64)
+LENS = [1, 4, 5, 0, 16, 17, 2, 32, 33, 63, 64, 65, 3, 128, 129] + [1] * 48 + [70, 0, 6]
+
+
+@pytest.mark.parametrize("dtype,r,P,same_x,h_in,h_out", [
+    ("f16", 8, 1, True, 136, 264), ("bf16", 16, 1, True, 1032, 2056), ("f16", 64, 1, True, 264, 256),   # one add-on
+    ("bf16", 8, 3, True, 520, 264), ("f16", 16, 2, True, 136, 2056), ("bf16", 32, 3, True, 1032, 264),  # one pass over x
+    ("f16", 64, 3, True, 264, 520), ("bf16", 16, 3, False, 520, 776),                                   # side by side
+    ("f16", 32, 4, True, 264, 264), ("bf16", 64, 5, False, 136, 264)])                                  # in groups of three
+def test_every_edge_of_the_work_lists(dtype, r, P, same_x, h_in, h_out):
+    from paper_2310_18547_amd import binding as B
+    n = len(LENS)
+    ws = [wl.custom(LENS, h_in, h_out, r, dtype, seed=900 + r + k, num_layers=2, scale=0.5,
+                    seg_adapter=[-1 if k == P - 1 and i in (6, 11, n - 1) else i for i in range(n)]) for k in range(P)]
+    ds = [_dev(w, path=B.PATH_MATRIX, n_proj=P) for w in ws]
+    xs = [ds[0 if same_x else k].x[0] for k in range(P)]
+    if P == 1:
+        ds[0].add_lora(1)
+    else:
+        B.sgmv_add_lora_multi(ds[0].problem, [d.y[0] for d in ds], xs, [d.A_ptrs for d in ds], [d.B_ptrs for d in ds],
+                              ds[0].seg_starts, n, 1, 0.5)
+    got = [d.y_bits() for d in ds]
+    for k, w in enumerate(ws):
+        if same_x:
+            w.x[...] = ws[0].x
+        assert_parity(got[k], oracle.run_workload(w, layer_idx=1, n_threads=8), dtype, f"add-on {k} of {P}")
+
+
+# Every kernel that stores y, by path and segment lengths: with one term per sum the fp32 result is exact, so that y is
+# its rounding to nearest even, bit for bit (the operands lie within a factor of four: many ties).
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("path,lens", [("PATH_VECTOR", [1, 3, 2]), ("PATH_MATRIX", [1, 3, 2, 5, 40, 64]), ("PATH_FUSED", [1, 1, 1]),
+                                       ("PATH_FUSED", [4, 20]), ("PATH_WHOLE", [1, 1, 1]), ("PATH_ROWS", [1, 3, 2])])
+def test_y_is_rounded_to_nearest_even(path, lens, dtype):
+    from paper_2310_18547_amd import binding as B
+    w = wl.custom(lens, 256, 2056, 16, dtype, seed=31)
+    rng = np.random.Generator(np.random.PCG64(32))
+
+    def values(shape):
+        sign = rng.choice([-1.0, 1.0], shape)
+        return wl.encode((sign * rng.uniform(0.5, 2.0, shape)).astype(np.float32), dtype)
+
+    one = wl.encode(np.ones(1, np.float32), dtype)[0]
+    w.x[...] = one
+    for a in w.A:
+        a[...] = 0
+        a[0, 5, 3] = one
+    for b in w.B:
+        b[...] = values(b.shape)
+    w.y0[...] = values(w.y0.shape)
+    d = _dev(w, path=getattr(B, path))
+    d.add_lora()
+    assert np.array_equal(d.y_bits(), oracle.run_workload(w))
+
+
+# Adding nothing keeps every value of the type, subnormals, infinities and NaN (as a NaN) among them.
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("path,lens", [("PATH_VECTOR", [1, 7]), ("PATH_MATRIX", [2, 6]), ("PATH_FUSED", [1] * 8)])
+def test_adding_nothing_keeps_every_value(path, lens, dtype):
+    from paper_2310_18547_amd import binding as B
+    w = wl.custom(lens, 256, 8192, 16, dtype, seed=33)
+    w.y0[...] = np.arange(1 << 16, dtype=np.uint32).astype(np.uint16).reshape(8, 8192)
+    for b in w.B:
+        b[...] = 0
+    d = _dev(w, path=getattr(B, path))
+    d.add_lora()
+    with np.errstate(invalid="ignore"):
+        got, kept = decode64(d.y_bits(), dtype), decode64(w.y0, dtype)
+    assert np.array_equal(got, kept, equal_nan=True)    # -0 + 0 is +0, which compares equal
