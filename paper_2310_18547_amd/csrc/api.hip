@@ -243,6 +243,30 @@ void set_operands(ExpandArgs* a, const Scratch& sc, int n_tokens, int r) {
   a->undo = reinterpret_cast<float*>(base + 2 * half);
 }
 
+// Lane groups of the hand-off kernel's expand phase: as many as give every lane a chunk of the column slice, and
+// enough that a lane holds at most sixteen weight rows.  A single add-on at ranks up to 16 stops
+// at two (the pair of neighbouring lanes that needs no LDS to add up, fused_kernel.hip) even
+// where that leaves lanes without a chunk: measured at h = 4096, r = 16, 1 / 8 / 16 / 32 segments:
+// 4.02 / 4.42 / 4.43 / 4.83 us against 4.07 / 4.54 / 4.59 / 5.01 us; at ranks 32 and 64 and in
+// the multi-projection launches the wider groups are faster (16 segments at rank 32: 5.02
+// against 5.46 us).
+int fused_lane_groups(int r, int cslice, bool single_add_on) {
+  const int chunks = cslice / 8;
+  const int most = single_add_on && r <= 16 ? 2 : 8;
+  int g = 1;
+  while (g * 2 <= most && 256 / (g * 2) >= chunks) g *= 2;
+  if (most == 2 && g == 1 && chunks <= 128) g = 2;
+  while (r / g > 16) g *= 2;
+  return g;
+}
+
+// Memory round trips of a workgroup at s slices: batches of 2048 128-bit loads of A_i, then passes over
+// its columns of B_i.
+int fused_round_trips(const sgmv_problem* p, int s, bool single_add_on) {
+  const int kslice = ceil_div(ceil_div(p->h_in, s), 8) * 8, cslice = ceil_div(ceil_div(p->h_out, s), 8) * 8;
+  return ceil_div(kslice * (p->r / 8), 2048) + ceil_div(cslice, 256 / fused_lane_groups(p->r, cslice, single_add_on) * 8);
+}
+
 // Launch shape of the single-launch path; false when it does not apply.
 // by_rows: the launch's items are the rows of the batch (pass n_tokens for n_segs), each looking its
 // segment up on the device, so the segments may have any length.
@@ -293,13 +317,33 @@ bool choose_fused(const sgmv_problem* p, int n_segs, FusedArgs* f, bool single_a
   if (s > kFusedMaxWorkgroups / n_segs) s = kFusedMaxWorkgroups / n_segs;
   if (s < need) s = need;
   if (s < 1) s = 1;
-  // a slice count forced by a wide input to five, six or seven: eight instead, where the launch
-  // has room (measured at 64 segments, h_in = 11008, six -> eight slices: rank 64 31.9 -> 27.5 us,
-  // rank 16 9.79 -> 9.53; h_in = 13824, seven -> eight: no difference)
-  if (p->ksplit == 0 && single_add_on && s == need && s > 4 && s < 8 &&
-      8LL * ceil_div(n_segs, fused_grid_x(n_segs)) * fused_grid_x(n_segs) <= kFusedMaxWorkgroups && 8 <= cap &&
-      8 <= wide / 64)
+  // A single add-on whose workgroups, padding included (an XCD takes whole items), leave units free: the
+  // count from s up to seven with the fewest memory round trips, the smallest of equals.  Measured, four
+  // (or what was taken before) -> this many slices, us: 45 rows of 18 adapters, bfloat16, h = 5120, five slices: rank 16
+  // 6.0 -> 5.1, rank 32 9.8 -> 7.6, rank 64 14.1 -> 11.8; 40 segments, 4096 -> 11008, six slices: rank 16
+  // 7.4 -> 6.3, rank 32 12.1 -> 11.3, rank 64 19.6 -> 17.7; 11008 -> 4096, six slices: 8.0 -> 6.8, 14.4 -> 10.3 and
+  // 22.2 -> 17.0.  One workgroup too many for an XCD costs more than that (51 segments, h = 5120, rank 32, 280
+  // workgroups: 10.8 -> 13.5), and with equal or hardly fewer round trips more slices gain nothing (h = 4096, ranks
+  // 16 and 32: level; h = 8192, rank 64, 47 segments, eleven round trips for twelve: 21.2 -> 21.5).
+  const long long padded = fused_grid_items(n_segs);
+  const bool spread = p->ksplit == 0 && single_add_on && s < kFusedSlices && s * padded <= lim.fused_workgroups;
+  if (spread) {
+    int trips = fused_round_trips(p, s, true);
+    for (int t = s + 1; t < kFusedSlices && t * padded <= lim.fused_workgroups && t <= cap && t <= wide / 64; ++t)
+      if (10 * fused_round_trips(p, t, true) <= 9 * trips) {
+        s = t;
+        trips = fused_round_trips(p, t, true);
+      }
+  }
+  // a slice count forced by a wide input to five, six or seven on more workgroups than units: eight
+  // instead, where the launch has room (measured at 64 segments, h_in = 11008, six -> eight slices: rank 64
+  // 31.9 -> 27.5 us, rank 16 9.79 -> 9.53; h_in = 13824, seven -> eight: no difference)
+  bool eight = false;
+  if (p->ksplit == 0 && single_add_on && !spread && s == need && s > 4 && s < 8 && 8 * padded <= kFusedMaxWorkgroups &&
+      8 <= cap && 8 <= wide / 64) {
     s = 8;
+    eight = true;
+  }
   // the grid is padded to whole rows of segments (launch.h, fused_grid_x)
   const int gx = fused_grid_x(n_segs);
   if ((long long)s * ceil_div(n_segs, gx) * gx > kFusedMaxWorkgroups) return false;
@@ -314,7 +358,12 @@ bool choose_fused(const sgmv_problem* p, int n_segs, FusedArgs* f, bool single_a
   // 24.3 against 19.1 / 22.1 us, rank 64 36.3 / 40.1 against 30.7 / 35.2; h = 8192, four slices,
   // 96 segments: 27.8 against 24.7 and 45.2 against 41.5; 512 workgroups are fine: 128 segments
   // at h = 4096, rank 32: 18.0 against 19.6)
-  if (p->path == SGMV_PATH_AUTO && p->ksplit == 0 && p->r >= 32 && (long long)s * n_segs > lim.fused_workgroups) {
+  // (not so eight slices, whose shares are small: 11008 -> 4096, 51 segments, the launch that took over
+  // against eight slices: rank 32 17.5 / 12.5 us, rank 64 26.6 / 23.2; 45 rows of 18 adapters, bfloat16:
+  // 13.7 / 10.7 and 37.3 / 16.9; but at rank 64 up to 40 segments, 320 workgroups, keep what they had: 13824 ->
+  // 5120, 35 segments 24.8 / 26.3)
+  if (p->path == SGMV_PATH_AUTO && p->ksplit == 0 && p->r >= 32 &&
+      !(eight && (by_rows || p->r < 64 || padded > 40)) && (long long)s * n_segs > lim.fused_workgroups) {
     const long long wg = (long long)s * n_segs;
     const long long rounds = ceil_div((int)wg, lim.fused_workgroups);
     if (rounds * lim.fused_workgroups * 5 > wg * 6) return false;  // more than 20 % of the slots idle
@@ -328,20 +377,7 @@ bool choose_fused(const sgmv_problem* p, int n_segs, FusedArgs* f, bool single_a
   f->S = s;
   f->kslice = ceil_div(ceil_div(p->h_in, s), 8) * 8;
   f->cslice = ceil_div(ceil_div(p->h_out, s), 8) * 8;
-  const int chunks = f->cslice / 8;
-  // Lane groups of the expand phase: as many as give every lane a chunk of the column slice, and
-  // enough that a lane holds at most sixteen weight rows.  A single add-on at ranks up to 16 stops
-  // at two (the pair of neighbouring lanes that needs no LDS to add up, fused_kernel.hip) even
-  // where that leaves lanes without a chunk: measured at h = 4096, r = 16, 1 / 8 / 16 / 32 segments:
-  // 4.02 / 4.42 / 4.43 / 4.83 us against 4.07 / 4.54 / 4.59 / 5.01 us; at ranks 32 and 64 and in
-  // the multi-projection launches the wider groups are faster (16 segments at rank 32: 5.02
-  // against 5.46 us).
-  const int most = single_add_on && p->r <= 16 ? 2 : 8;
-  int g = 1;
-  while (g * 2 <= most && 256 / (g * 2) >= chunks) g *= 2;
-  if (most == 2 && g == 1 && chunks <= 128) g = 2;
-  while (p->r / g > 16) g *= 2;
-  f->G = g;
+  f->G = fused_lane_groups(p->r, f->cslice, single_add_on);
   f->rows_per_pass = 1;
   return true;
 }
