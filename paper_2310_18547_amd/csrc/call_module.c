@@ -227,6 +227,8 @@ static PyObject* call_add_lora_static(PyObject* self, PyObject* const* args, Py_
 }
 
 // The addresses of a sequence's `n` elements; more than the library takes are left for it to refuse.
+// An element's data_ptr() is Python code and may change the very list that is read: the size is looked up
+// again and the element kept alive around each one, and what is no longer there counts as NULL.
 #define MOST_ADD_ONS 64
 static int addresses_of(PyObject* seq, Py_ssize_t n, void** out) {
   PyObject* fast = PySequence_Fast(seq, "expected a sequence");
@@ -236,7 +238,14 @@ static int addresses_of(PyObject* seq, Py_ssize_t n, void** out) {
     PyErr_SetString(PyExc_IndexError, "sequences of pointers differ in length");
     rc = -1;
   }
-  for (Py_ssize_t i = 0; i < n && rc == 0; ++i) rc = address_of(PySequence_Fast_GET_ITEM(fast, i), &out[i]);
+  for (Py_ssize_t i = 0; i < n && rc == 0; ++i) {
+    out[i] = NULL;
+    if (i >= PySequence_Fast_GET_SIZE(fast)) continue;
+    PyObject* element = PySequence_Fast_GET_ITEM(fast, i);
+    Py_INCREF(element);
+    rc = address_of(element, &out[i]);
+    Py_DECREF(element);
+  }
   Py_DECREF(fast);
   return rc;
 }

@@ -563,6 +563,20 @@ def test_calls_take_positional_and_keyword_arguments():
         sg.sgmv_add_lora_multi(p, [16, 16], [16, 16, 16], [16, 16], [16, 16], 16, 1, 0, 1.0)
 
 
+def test_pointer_lists_that_change_while_they_are_read():
+    p = sg.make_problem(sg.F16, 256, 256, 8, 1, 4)
+    pointers = []
+
+    class Shrinking:
+        def data_ptr(self):
+            pointers.clear()
+            return 16
+
+    pointers += [Shrinking() for _ in range(4)]
+    # the elements that are gone count as NULL
+    assert sg.sgmv_add_lora_multi(p, [16] * 4, pointers, [16] * 4, [16] * 4, 16, 1, 0, 1.0, check=False) == 1
+
+
 def test_long_segments_put_up_to_three_add_ons_into_a_launch():
     for r in (16, 64):
         room = sg.sgmv_workspace_bytes_multi(2000, r, 8)
