@@ -174,15 +174,68 @@ STATIC_SCRATCH_BYTES = 9 << 20
 STATIC_MAX_WORKSPACE_BYTES = 8 << 20
 
 
+class ArgumentError(ctypes.ArgumentError, TypeError):
+    """An argument of a per-layer call that has no C value."""
+
+
+def _call(name: str, check, *args) -> int:
+    try:
+        rc = getattr(lib, name)(*args)
+    except ctypes.ArgumentError as e:
+        raise ArgumentError(*e.args) from None
+    if check and rc != 0:
+        raise SgmvError(rc, name)
+    return rc
+
+
+class _General:
+    """The per-layer calls for every form of argument that ctypes converts."""
+
+    @staticmethod
+    def sgmv_shrink(p: SgmvProblem, v, x, A_ptrs, seg_starts, n_segs: int, layer_idx: int, stream=None,
+                    check: bool = True) -> int:
+        return _call("sgmv_shrink", check, ctypes.byref(p), _addr(v), _addr(x), _addr(A_ptrs), _addr(seg_starts), n_segs,
+                     layer_idx, _stream(stream))
+
+    @staticmethod
+    def sgmv_expand(p: SgmvProblem, y, v, B_ptrs, seg_starts, n_segs: int, layer_idx: int, scale: float, stream=None,
+                    check: bool = True) -> int:
+        return _call("sgmv_expand", check, ctypes.byref(p), _addr(y), _addr(v), _addr(B_ptrs), _addr(seg_starts), n_segs,
+                     layer_idx, scale, _stream(stream))
+
+    @staticmethod
+    def sgmv_add_lora(p: SgmvProblem, y, x, A_ptrs, B_ptrs, seg_starts, n_segs: int, layer_idx: int, scale: float,
+                      stream=None, check: bool = True) -> int:
+        return _call("sgmv_add_lora", check, ctypes.byref(p), _addr(y), _addr(x), _addr(A_ptrs), _addr(B_ptrs),
+                     _addr(seg_starts), n_segs, layer_idx, scale, _stream(stream))
+
+    @staticmethod
+    def sgmv_add_lora_static(p: SgmvProblem, y, x, A_ptrs, B_ptrs, seg_starts, n_segs: int, layer_idx: int, scale: float,
+                             stream=None, check: bool = True) -> int:
+        return _call("sgmv_add_lora_static", check, ctypes.byref(p), _addr(y), _addr(x), _addr(A_ptrs), _addr(B_ptrs),
+                     _addr(seg_starts), n_segs, layer_idx, scale, _stream(stream))
+
+    @staticmethod
+    def sgmv_add_lora_multi(p: SgmvProblem, ys, xs, A_ptrs, B_ptrs, seg_starts, n_segs: int, layer_idx: int, scale: float,
+                            stream=None, check: bool = True) -> int:
+        """``ys, xs, A_ptrs, B_ptrs`` are sequences, one entry per add-on."""
+        n = len(ys)
+        arr = ctypes.c_void_p * n
+        return _call("sgmv_add_lora_multi", check, ctypes.byref(p), n, arr(*[_addr(a) for a in ys]),
+                     arr(*[_addr(a) for a in xs]), arr(*[_addr(a) for a in A_ptrs]), arr(*[_addr(a) for a in B_ptrs]),
+                     _addr(seg_starts), n_segs, layer_idx, scale, _stream(stream))
+
+
 def _calls():
-    """The per-layer calls, marshalled in C (csrc/call_module.c)."""
+    """The per-layer calls, their usual arguments marshalled in C (csrc/call_module.c)."""
     try:
         from . import _sgmv_call as module
     except ImportError as e:
         raise ImportError(f"{_HERE}/_sgmv_call.so is missing or does not fit this interpreter: build it with "
                           "`python -m paper_2310_18547_amd.build`") from e
     names = ("sgmv_shrink", "sgmv_expand", "sgmv_add_lora", "sgmv_add_lora_static", "sgmv_add_lora_multi")
-    size = module.bind(SgmvProblem, SgmvError, *(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names))
+    size = module.bind(SgmvProblem, SgmvError, tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names),
+                       tuple(getattr(_General, n) for n in names))
     assert size == ctypes.sizeof(SgmvProblem)
     return [getattr(module, n) for n in names]
 

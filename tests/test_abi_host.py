@@ -577,6 +577,33 @@ def test_pointer_lists_that_change_while_they_are_read():
     assert sg.sgmv_add_lora_multi(p, [16] * 4, pointers, [16] * 4, [16] * 4, 16, 1, 0, 1.0, check=False) == 1
 
 
+def test_calls_take_every_form_of_argument_that_ctypes_takes():
+    p = sg.make_problem(sg.F16, 256, 256, 8, 1, 4)
+    i32, f32 = ctypes.c_int32, ctypes.c_float
+    rest = (16, i32(1), i32(0))
+    assert sg.sgmv_shrink(p, None, 16, 16, *rest, check=False) == 1
+    assert sg.sgmv_expand(p, None, 16, 16, *rest, f32(1), check=False) == 1
+    assert sg.sgmv_add_lora(p, None, 16, 16, 16, *rest, f32(1), check=False) == 1
+    assert sg.sgmv_add_lora_static(p, None, 16, 16, 16, *rest, f32(1), None, False) == 1
+    with pytest.raises(sg.SgmvError, match="sgmv_add_lora_static"):
+        sg.sgmv_add_lora_static(p, None, 16, 16, 16, *rest, f32(1))
+    assert sg.sgmv_add_lora_multi(p, [None], [16], (16,), [16], *rest, f32(1), check=False) == 1
+    # what has no C value
+    for bad in ((1.5, 0, 1.0), (1, "0", 1.0), (1, 0, "1"), (1, 0, None)):
+        with pytest.raises(ctypes.ArgumentError):
+            sg.sgmv_add_lora(p, 16, 16, 16, 16, 16, *bad)
+    with pytest.raises(ctypes.ArgumentError):
+        sg.sgmv_add_lora(sg.binding.SgmvPlan(), 16, 16, 16, 16, 16, 1, 0, 1.0)
+    # pointer lists: any iterable; entries that are not there are NULL
+    for short in ([16], (16,), iter([16])):
+        args = (p, [16, 16], [16, 16], [16, 16], short, 16, 1, 0, 1.0)
+        assert sg.sgmv_add_lora_multi(*args, check=False) == 1
+    with pytest.raises(sg.SgmvError):
+        sg.sgmv_add_lora_multi(p, [16, 16], [16], [16, 16], [16, 16], 16, 1, 0, 1.0)
+    # both pointers there: on to the next check, the missing workspace
+    assert sg.sgmv_add_lora_multi(p, [16, 32], iter([16, 16]), [16, 16], (16, 16), 16, 1, 0, 1.0, check=False) == 5
+
+
 def test_long_segments_put_up_to_three_add_ons_into_a_launch():
     for r in (16, 64):
         room = sg.sgmv_workspace_bytes_multi(2000, r, 8)
