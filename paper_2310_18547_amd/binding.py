@@ -231,7 +231,7 @@ def _calls():
     try:
         from . import _sgmv_call as module
     except ImportError as e:
-        raise ImportError(f"{_HERE}/_sgmv_call.so is missing or does not fit this interpreter: build it with "
+        raise ImportError(f"{_HERE} holds no _sgmv_call module for this interpreter: build it with "
                           "`python -m paper_2310_18547_amd.build`") from e
     names = ("sgmv_shrink", "sgmv_expand", "sgmv_add_lora", "sgmv_add_lora_static", "sgmv_add_lora_multi")
     size = module.bind(SgmvProblem, SgmvError, tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names),

@@ -1,4 +1,4 @@
-"""Build libsgmv.so (HIP, gfx950) with hipcc and the binding's _sgmv_call.so with gcc, in-tree.
+"""Build libsgmv.so (HIP, gfx950) with hipcc and the binding's _sgmv_call module with gcc, in-tree.
 
     python -m paper_2310_18547_amd.build
 """
@@ -13,7 +13,8 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsgmv.so")
-CALLS = os.path.join(HERE, "_sgmv_call.so")
+# the suffix names the interpreter and its ABI: another one does not find the module instead of crashing in it
+CALLS = os.path.join(HERE, "_sgmv_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -11,10 +11,9 @@ if ROOT not in sys.path:
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs a real MI355X (run with -m gpu)")
     # load what is built; build only if nothing is there
-    built = [os.path.join(ROOT, "paper_2310_18547_amd", name) for name in ("libsgmv.so", "_sgmv_call.so")]
-    if not all(os.path.exists(lib) for lib in built):
-        from paper_2310_18547_amd.build import build
-        build(verbose=False)
+    from paper_2310_18547_amd import build
+    if not all(os.path.exists(lib) for lib in (build.LIB, build.CALLS)):
+        build.build(verbose=False)
 
 
 def _gpu_present() -> bool:

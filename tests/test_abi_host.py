@@ -3,6 +3,8 @@ symbol the header declares, and rejects bad arguments before touching a device."
 import ctypes
 import os
 import re
+import sys
+import sysconfig
 
 import numpy as np
 import pytest
@@ -602,6 +604,11 @@ def test_calls_take_every_form_of_argument_that_ctypes_takes():
         sg.sgmv_add_lora_multi(p, [16, 16], [16], [16, 16], [16, 16], 16, 1, 0, 1.0)
     # both pointers there: on to the next check, the missing workspace
     assert sg.sgmv_add_lora_multi(p, [16, 32], iter([16, 16]), [16, 16], (16, 16), 16, 1, 0, 1.0, check=False) == 5
+
+
+def test_the_call_module_names_the_interpreter_it_was_built_for():
+    path = sys.modules["paper_2310_18547_amd._sgmv_call"].__file__
+    assert path.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and sys.implementation.cache_tag in path
 
 
 def test_long_segments_put_up_to_three_add_ons_into_a_launch():
