@@ -170,6 +170,14 @@ constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit data format
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_buffer(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, kBufferWord3);
 }
+// The same where base and size, equal in all lanes, come from vector registers (a division or a float
+// conversion in their making is enough): moved to scalar registers here, once.  Left where they are, every access
+// of the buffer becomes a loop over the lanes' different buffers and holds four vector registers.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_uniform_buffer(const void* base, uint32_t bytes) {
+  const uint64_t v = reinterpret_cast<uint64_t>(base);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+  return make_buffer(reinterpret_cast<const void*>(((uint64_t)hi << 32) | lo), (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes));
+}
 template <int AUX = 0>
 __device__ __forceinline__ uint4 buffer_load128(__amdgpu_buffer_rsrc_t rsrc, uint32_t byte_off) {
   u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)byte_off, 0, AUX);

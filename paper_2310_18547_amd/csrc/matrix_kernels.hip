@@ -224,7 +224,7 @@ __global__ __launch_bounds__((64 * ShrinkShape<R, P>::kWaves), 4) void shrink_st
 
   const int row0 = block_row + wave * 16;
   const int rows = max(0, min(16, at_seg.hi - row0));  // rows past the segment read as zeros
-  const __amdgpu_buffer_rsrc_t rX = make_buffer(
+  const __amdgpu_buffer_rsrc_t rX = make_uniform_buffer(
       tab.x[p0] + (long long)(rows > 0 ? row0 : block_row) * h_in + k0, rows > 0 ? (uint32_t)((rows - 1) * h_in + klen) * 2u : 0u);
   const uint32_t x_lane = (uint32_t)(m * h_in + g * 8) * 2u;
   const int k_end = m < rows ? klen - g * 8 : 0;
@@ -238,7 +238,7 @@ __global__ __launch_bounds__((64 * ShrinkShape<R, P>::kWaves), 4) void shrink_st
   __amdgpu_buffer_rsrc_t rA[P];  // an add-on without an adapter for this segment: an empty buffer, zeros
 #pragma unroll
   for (int p = 0; p < P; ++p)
-    rA[p] = make_buffer(A[p] != nullptr ? A[p] + layer_off + (long long)k0 * R : tab.x[p0],
+    rA[p] = make_uniform_buffer(A[p] != nullptr ? A[p] + layer_off + (long long)k0 * R : tab.x[p0],
                         A[p] != nullptr ? (uint32_t)klen * R * 2u : 0u);
   uint4 a0[ITEMS], a1[ITEMS];
   auto load_a = [&](int c) {
@@ -468,14 +468,14 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
       const int c = it.index * kFewCols + tid * 8;
       const uint32_t off = c < h_out ? (uint32_t)c * 2u : kOutOfRange;
       constexpr int JC = 8;  // weight rows in flight
-      const __amdgpu_buffer_rsrc_t rB = make_buffer(B + layer_off, (uint32_t)((long long)R * h_out * 2));
+      const __amdgpu_buffer_rsrc_t rB = make_uniform_buffer(B + layer_off, (uint32_t)((long long)R * h_out * 2));
       for (int row = it.lo; row < it.hi; row += 2) {
         asm volatile("" ::: "memory");  // the weights are read again for every pair of rows, not kept (R / 2 registers per lane)
         const bool two = row + 1 < it.hi;
         uint4 b[JC];
 #pragma unroll
         for (int j = 0; j < JC; ++j) b[j] = buffer_load128<kNonTemporal>(rB, off + (uint32_t)(j * h_out) * 2u);
-        const __amdgpu_buffer_rsrc_t rY = make_buffer(y + (long long)row * h_out, (uint32_t)(two ? 2 : 1) * h_out * 2u);
+        const __amdgpu_buffer_rsrc_t rY = make_uniform_buffer(y + (long long)row * h_out, (uint32_t)(two ? 2 : 1) * h_out * 2u);
         const uint4 y0 = buffer_load128<kNonTemporal>(rY, off);
         const uint4 y1 = buffer_load128<kNonTemporal>(rY, off + (uint32_t)h_out * 2u);
         // lane j: v[row][j], v[row + 1][j]
@@ -527,7 +527,7 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
       // ---- the strip's loads first (L2 hits mostly), so that placing it does not wait for y
       const int cg = tid % (NC / 8), kq = tid / (NC / 8);
       const bool stages = (ITEMS == 256 || tid < ITEMS);
-      const __amdgpu_buffer_rsrc_t rB = make_buffer(B + layer_off + c0, (uint32_t)((long long)(R - 1) * h_out + ncols) * 2u);
+      const __amdgpu_buffer_rsrc_t rB = make_uniform_buffer(B + layer_off + c0, (uint32_t)((long long)(R - 1) * h_out + ncols) * 2u);
       uint4 w[KR];
 #pragma unroll
       for (int i = 0; i < KR; ++i)
@@ -536,8 +536,8 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
       // ---- v: row n of the tile; rows past the segment read as zeros
       uint4 v_hi[KSTEPS], v_lo[KSTEPS];
       {
-        const __amdgpu_buffer_rsrc_t rH = make_buffer(vh + (long long)r0 * R, (uint32_t)(rows * R) * 2u);
-        const __amdgpu_buffer_rsrc_t rL = make_buffer(vl + (long long)r0 * R, (uint32_t)(rows * R) * 2u);
+        const __amdgpu_buffer_rsrc_t rH = make_uniform_buffer(vh + (long long)r0 * R, (uint32_t)(rows * R) * 2u);
+        const __amdgpu_buffer_rsrc_t rL = make_uniform_buffer(vl + (long long)r0 * R, (uint32_t)(rows * R) * 2u);
         if constexpr (PAIRED) {  // k blocks 0 .. KB - 1 the high part, KB .. 2 KB - 1 the low one
           v_hi[0] = buffer_load128(rH, g < KB ? (uint32_t)(n * R + g * 8) * 2u : kOutOfRange);
           v_lo[0] = buffer_load128(rL, g >= KB && g < 2 * KB ? (uint32_t)(n * R + (g - KB) * 8) * 2u : kOutOfRange);
@@ -554,11 +554,17 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
       for (int i = 0; i < 4; ++i)
         un[i] = std::is_same<DT, F16>::value && rows > 0 ? undo[r0 + min(4 * g + i, rows - 1)] : 1.f;
 
-      // FULL: every column of the strip is inside h_out
-      auto rest = [&](auto full_tag) {
+      // FULL: every column of the strip is inside h_out.  GROUPS: the most column groups this wave takes, so that
+      // only their part of y is loaded and held.  (Loads from an empty buffer for the groups that other waves take cost
+      // their issue all the same: expand to 13824 of 40 / 200 segments of 8 rows, rank 16, 15.9 / 62.1 -> 12.4 / 45.7 us.
+      // One code for all counts kept up to nine registers of rank 64 in scratch memory: 8192 -> 28672, 4800 rows,
+      // 134.6 -> 131.6 us.)
+      auto rest = [&](auto full_tag, auto groups_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
-        // rows past the segment lie past the end of the buffer, which is empty for the groups other waves take
-        uint2 yq[NG][4];
+        constexpr int GROUPS = decltype(groups_tag)::value;
+        auto mine = [&](int j) { return GROUPS == NG || j < tiles; };
+        // rows past the segment lie past the end of the buffer
+        uint2 yq[GROUPS][4];
         uint32_t yoff[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) yoff[i] = (uint32_t)((4 * g + i) * h_out + c0 + group0 * (16 * CT) + n * CT) * 2u;
@@ -566,11 +572,11 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
         uint16_t* const y_at = y + (long long)(rows > 0 ? r0 : row0) * h_out;
         auto in_strip = [&](int j) { return FULL || (group0 + j) * (16 * CT) + n * CT < ncols; };
 #pragma unroll
-        for (int j = 0; j < NG; ++j) {
-          const __amdgpu_buffer_rsrc_t rY = make_buffer(y_at, j < tiles ? y_bytes : 0u);
+        for (int j = 0; j < GROUPS; ++j) {
+          const __amdgpu_buffer_rsrc_t rY = make_uniform_buffer(y_at, y_bytes);
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            yq[j][i] = buffer_load64_at<kNonTemporal>(rY, in_strip(j) ? yoff[i] : kOutOfRange, (uint32_t)j * (16 * CT * 2));
+            if (mine(j)) yq[j][i] = buffer_load64_at<kNonTemporal>(rY, in_strip(j) ? yoff[i] : kOutOfRange, (uint32_t)j * (16 * CT * 2));
         }
 
         // ---- place the strip: dword d of a slot holds rows 2 d and 2 d + 1 of the k block
@@ -604,8 +610,8 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
         };
         const uint4 v_pair = make_uint4(v_hi[0].x | v_lo[0].x, v_hi[0].y | v_lo[0].y, v_hi[0].z | v_lo[0].z, v_hi[0].w | v_lo[0].w);
 #pragma unroll
-        for (int j = 0; j < NG; ++j) {
-          if (j < tiles) {
+        for (int j = 0; j < GROUPS; ++j) {
+          if (mine(j)) {
             asm volatile("" ::: "memory");  // a group's operands are read where they are used: together they would spill
             f32x4 acc[CT];
 #pragma unroll
@@ -630,7 +636,7 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
               }
             }
             // acc[t][i] is column 64 (group0 + j) + 4 n + t of row 4 g + i
-            const __amdgpu_buffer_rsrc_t rY = make_buffer(y_at, y_bytes);
+            const __amdgpu_buffer_rsrc_t rY = make_uniform_buffer(y_at, y_bytes);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
               buffer_store64_at<kNonTemporal>(rY, in_strip(j) ? yoff[i] : kOutOfRange, (uint32_t)j * (16 * CT * 2),
@@ -638,10 +644,17 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
           }
         }
       };
-      if (ncols == NC)
-        rest(std::true_type{});
+      auto by_columns = [&](auto groups_tag) {
+        if (ncols == NC)
+          rest(std::true_type{}, groups_tag);
+        else
+          rest(std::false_type{}, groups_tag);
+      };
+      static_assert(NG == 4, "a wave takes four, two or one of the column groups");
+      if (tiles == 4)
+        by_columns(std::integral_constant<int, 4>{});
       else
-        rest(std::false_type{});
+        by_columns(std::integral_constant<int, 2>{});
     }
   }
   SGMV_TRACE_POINT(6);

@@ -622,3 +622,17 @@ def test_long_segments_put_up_to_three_add_ons_into_a_launch():
             p.workspace_bytes = sg.sgmv_workspace_bytes(2000, r)     # room for one: in turn
             rc, plan = sg.sgmv_plan_add_lora(p, 4, n_proj, check=False)
             assert rc == 0 and plan.launches == 3 * n_proj
+
+
+def test_no_kernel_keeps_registers_in_scratch_memory():
+    """From the kernels' metadata in the built library: each says how much scratch a lane needs."""
+    data = open(sg.library_path(), "rb").read()
+    key = b".private_segment_fixed_size"
+    sizes = {}
+    for name in re.finditer(rb"\.name(?:[\xa0-\xbf]|\xd9.|\xda..)(_ZN4sgmv\w+)", data, re.S):
+        at = data.index(key, name.start()) + len(key)
+        kind = data[at]                                 # MessagePack: the value itself below 128, else its size
+        width = {0xCC: 1, 0xCD: 2, 0xCE: 4}.get(kind, 0)
+        sizes[name[1].decode()] = int.from_bytes(data[at + 1:at + 1 + width], "big") if width else kind
+    assert len(sizes) > 100
+    assert [n for n, size in sizes.items() if size] == []
