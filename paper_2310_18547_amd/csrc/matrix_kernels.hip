@@ -200,7 +200,9 @@ __global__ __launch_bounds__((64 * ShrinkShape<R, P>::kWaves), 4) void shrink_st
   SGMV_TRACE_POINT(0);
   // eight (slice, block) pairs, one per XCD, times the groups of add-ons: the groups that read the same
   // part of x run on one XCD at the same time and find it in its L2
-  const unsigned row_of_eight = blockIdx.x / (8 * (unsigned)groups), in_row = blockIdx.x - row_of_eight * 8 * (unsigned)groups;
+  unsigned id = blockIdx.x;
+  if (blockIdx.y != 0) id += blockIdx.y * gridDim.x;  // (reading the grid's size costs a memory latency)
+  const unsigned row_of_eight = id / (8 * (unsigned)groups), in_row = id - row_of_eight * 8 * (unsigned)groups;
   const unsigned pair = row_of_eight * 8 + in_row % 8;
   const int s = pair % (unsigned)slices;
   const Found at_seg = find_item(seg_starts, n_segs, (int)(pair / (unsigned)slices), lane,
@@ -384,7 +386,7 @@ struct ExpandTable {
   const uint16_t* const* B_ptrs[kSharedShrinkMost];
 };
 
-// grid = (items, add-ons); vh / vl / undo come from finalize_v_kernel.  The list of items: for a segment
+// grid = (items, add-ons, further items); vh / vl / undo come from finalize_v_kernel.  The list of items: for a segment
 // of more than kFewRows rows (few_strips = 0: of any length) its 64-row blocks x strips of 256 columns, for a shorter one its strips of 2048
 // columns.
 //
@@ -457,7 +459,9 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
   SGMV_TRACE_DECL
   SGMV_TRACE_POINT(0);
 
-  const Found it = find_item(seg_starts, n_segs, (int)blockIdx.x, lane, [=](int rows) {
+  unsigned index = blockIdx.x;
+  if (blockIdx.z != 0) index += blockIdx.z * gridDim.x;
+  const Found it = find_item(seg_starts, n_segs, (int)index, lane, [=](int rows) {
     return few_strips > 0 && rows <= kFewRows ? few_strips : (rows + kExpandRows - 1) / kExpandRows * strips;
   });
   if (it.seg < 0) return;
@@ -669,6 +673,10 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
 
 // ---------------------------------------------------------------- launchers
 
+// Along one dimension of a grid, which holds fewer than 2^32 threads (512 per workgroup here at most); a longer list
+// goes on in the next dimension.
+constexpr long long kMostWorkgroups = 1 << 22;
+
 // Whether one pass over x serves n add-ons (their chunks of A_i side by side in LDS).
 bool shrink_shared_fits(int r, int n_shared) { return n_shared == 1 || (n_shared >= 2 && n_shared <= kSharedShrinkMost && r <= 32); }
 
@@ -687,9 +695,11 @@ static hipError_t launch_shrink_matrix_p(const ShrinkArgs& a, hipStream_t st) {
     tab.partials[i] = a.partials_of[k];
   }
   const int groups = a.n_proj / P;
-  const long long pairs = (long long)a.ksplit * most_blocks(a.n_tokens, a.n_segs, Shape::kRows);
-  hipLaunchKernelGGL((shrink_stream_kernel<DT, R, P>), dim3((unsigned)((pairs + 7) / 8 * 8 * groups)), dim3(64 * Shape::kWaves), 0, st,
-                     a.seg_starts, a.n_segs, a.ksplit, groups, a.h_in, a.kslice, a.n_tokens, a.layer_off, a.header, tab);
+  const long long blocks = most_blocks(a.n_tokens, a.n_segs, Shape::kRows);
+  const long long wgs = (a.ksplit * blocks + 7) / 8 * 8 * groups;
+  const dim3 grid((unsigned)(wgs < kMostWorkgroups ? wgs : kMostWorkgroups), (unsigned)((wgs + kMostWorkgroups - 1) / kMostWorkgroups));
+  hipLaunchKernelGGL((shrink_stream_kernel<DT, R, P>), grid, dim3(64 * Shape::kWaves), 0, st, a.seg_starts, a.n_segs, a.ksplit,
+                     groups, a.h_in, a.kslice, a.n_tokens, a.layer_off, a.header, tab);
   return hipGetLastError();
 }
 
@@ -749,8 +759,11 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, hipStream_
   int few = (a.h_out + kFewCols - 1) / kFewCols;
   if ((long long)a.n_segs * few * n < 4 * R) few = 0;
   const long long blocks = most_blocks(a.n_tokens, a.n_segs, kExpandRows);
-  hipLaunchKernelGGL((expand_matrix_kernel<DT, R>), dim3((unsigned)(strips * blocks), (unsigned)n), dim3(256), 0, st, a.seg_starts,
-                     a.n_segs, strips, few, a.h_out, a.layer_off, a.scale, a.header, tab);
+  const long long wgs = strips * blocks;
+  const dim3 grid((unsigned)(wgs < kMostWorkgroups ? wgs : kMostWorkgroups), (unsigned)n,
+                  (unsigned)((wgs + kMostWorkgroups - 1) / kMostWorkgroups));
+  hipLaunchKernelGGL((expand_matrix_kernel<DT, R>), grid, dim3(256), 0, st, a.seg_starts, a.n_segs, strips, few, a.h_out, a.layer_off,
+                     a.scale, a.header, tab);
   return hipGetLastError();
 }
 

@@ -80,3 +80,22 @@ def test_adding_nothing_keeps_every_value(path, lens, dtype):
     with np.errstate(invalid="ignore"):
         got, kept = decode64(d.y_bits(), dtype), decode64(w.y0, dtype)
     assert np.array_equal(got, kept, equal_nan=True)    # -0 + 0 is +0, which compares equal
+
+
+def test_more_workgroups_than_one_dimension_of_a_grid_holds():
+    """65535 segments x 257 strips of columns x 256 threads is more than 2^32."""
+    from paper_2310_18547_amd import binding as B
+    n, h_in, h_out, r = 65535, 8, 257 * 256, 8
+    gen = torch.Generator("cuda:0").manual_seed(3)
+    x, A, Bw = (torch.empty(s, dtype=torch.bfloat16, device="cuda:0").normal_(generator=gen) for s in ((n, h_in), (h_in, r), (r, h_out)))
+    y = torch.ones(n, h_out, dtype=torch.bfloat16, device="cuda:0")
+    seg_starts = torch.arange(n + 1, dtype=torch.int32, device="cuda:0")
+    A_ptrs, B_ptrs = (torch.full((n,), t.data_ptr(), dtype=torch.int64, device="cuda:0") for t in (A, Bw))
+    size = B.sgmv_workspace_bytes(n, r)
+    workspace = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+    p = B.make_problem(B.BF16, h_in, h_out, r, 1, n, workspace=workspace, workspace_bytes=size, path=B.PATH_MATRIX)
+    B.sgmv_add_lora(p, y, x, A_ptrs, B_ptrs, seg_starts, n, 0, 0.25)
+    rows = torch.arange(0, n, 37, device="cuda:0")
+    want = 1 + 0.25 * (x[rows].double() @ A.double() @ Bw.double())
+    # y is rounded once to 8 bits; v keeps 16
+    assert torch.all((y[rows].double() - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -13 * 8 * 4)
