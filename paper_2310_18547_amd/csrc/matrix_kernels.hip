@@ -47,45 +47,132 @@ constexpr int kExpandRows = 64;    // rows per expand workgroup and step (sixtee
 // The work of a launch is the list of row blocks of all segments: segment 0's blocks of ROWS rows,
 // then segment 1's, and so on.  A workgroup is handed an index into that list and finds its block
 // itself, so the grid has no more workgroups than there can be blocks (n_tokens / ROWS + n_segs,
-// those behind the end of the list leave at once) whatever the lengths are -- a grid of (longest
+// those that find none leave at once) whatever the lengths are -- a grid of (longest
 // segment) x (segments) is mostly empty when a few prompts run beside the decode rows of everybody
 // else (44 segments, 3 of them long: 352 blocks for 61).
+//
+// Up to kDenseSegments a wave looks at all of them in one round of loads (from 65 on, four per lane) and adds
+// up the list, which has no gaps.  Beyond that segment i's part starts at block (seg_starts[i] + i (ROWS - 1)) / ROWS,
+// which needs no sum over the segments before it and leaves room for its ceil(rows / ROWS) blocks: a
+// workgroup looks among the 64 segments around the place that equal lengths would give, and if its own is not
+// among them searches sixty-four ways, three rounds at most for 65535 segments.  (Adding the blocks up from segment 0
+// took a round per 64 segments in front of every workgroup: 256 / 1024 / 4096 / 16384 segments of 8 rows, 4096 -> 4096 at
+// rank 16, 34.7 / 149 / 1044 / 12376 us against 29.9 / 82.9 / 314 / 1232.  The search from 65 segments on: 3 prompts beside
+// 125 one-row segments at rank 64 51.4 against 42.7 us, because workgroups that find nothing stand between the others,
+// not behind them; 200 segments of 8 rows at rank 16 29.0 against 29.8.)
 struct Found {
-  int seg, lo, hi;   // segment and its rows; seg < 0: the list ends before `index`
+  int seg, lo, hi;   // segment and its rows; seg < 0: nothing at this place
   int index;         // place in the segment's part of the list
 };
-// Called by whole waves; count(rows) is what a segment of that many rows (at least one) contributes
-// to the list.  One memory latency per 64 segments.
-template <class Count>
-__device__ __forceinline__ Found find_item(const int32_t* __restrict__ seg_starts, int n_segs, int index, int lane,
-                                           Count count) {
-  for (int base = 0; base < n_segs; base += 64) {
-    const int i = min(base + lane, n_segs - 1);
-    const int lo = seg_starts[i], hi = base + lane < n_segs ? seg_starts[i + 1] : lo;
-    const int mine = hi > lo ? count(hi - lo) : 0;
-    // inclusive prefix sum over the wave by data-parallel-primitive moves
-    int sum = mine;
-    sum += __builtin_amdgcn_update_dpp(0, sum, 0x111, 0xF, 0xF, false);  // row_shr 1
-    sum += __builtin_amdgcn_update_dpp(0, sum, 0x112, 0xF, 0xF, false);  // row_shr 2
-    sum += __builtin_amdgcn_update_dpp(0, sum, 0x114, 0xF, 0xF, false);  // row_shr 4
-    sum += __builtin_amdgcn_update_dpp(0, sum, 0x118, 0xF, 0xF, false);  // row_shr 8
-    sum += __builtin_amdgcn_update_dpp(0, sum, 0x142, 0xA, 0xF, false);  // row_bcast 15 into rows 1 and 3
-    sum += __builtin_amdgcn_update_dpp(0, sum, 0x143, 0xC, 0xF, false);  // row_bcast 31 into rows 2 and 3
-    const int total = __builtin_amdgcn_readlane(sum, 63);
-    if (index < total) {
-      const int at = __builtin_ctzll(__ballot(sum > index));
-      return Found{base + at, __builtin_amdgcn_readlane(lo, at), __builtin_amdgcn_readlane(hi, at),
-                   index - __builtin_amdgcn_readlane(sum, at) + __builtin_amdgcn_readlane(mine, at)};
-    }
-    index -= total;
-  }
-  return Found{-1, 0, 0, 0};
+constexpr int kDensePerLane = 4, kDenseSegments = 64 * kDensePerLane;
+
+// Inclusive prefix sum over the wave by data-parallel-primitive moves.
+__device__ __forceinline__ int prefix_sum(int sum) {
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x111, 0xF, 0xF, false);  // row_shr 1
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x112, 0xF, 0xF, false);  // row_shr 2
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x114, 0xF, 0xF, false);  // row_shr 4
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x118, 0xF, 0xF, false);  // row_shr 8
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x142, 0xA, 0xF, false);  // row_bcast 15 into rows 1 and 3
+  sum += __builtin_amdgcn_update_dpp(0, sum, 0x143, 0xC, 0xF, false);  // row_bcast 31 into rows 2 and 3
+  return sum;
 }
-// Blocks there can be at most.
+
+// Called by whole waves.  A segment of that many rows (at least one) has count(rows) items, per_block for each of its
+// blocks or, if it has a single one, fewer.  item: the place in the list, or beyond kDenseSegments, place `item
+// % per_block` of block `item / per_block`.  turn: the items of a segment that has fewer.  guess: segments per block on average.
+template <int ROWS, class Count>
+__device__ __forceinline__ Found find_item(const int32_t* __restrict__ seg_starts, int n_segs, unsigned item, int per_block,
+                                           int turn, float guess, int lane, Count count) {
+  int base = 0;
+  int lo, hi;
+  auto look = [&]() {  // lane l: segment base + l
+    const int i = min(base + lane, n_segs - 1);
+    lo = seg_starts[i];
+    hi = seg_starts[i + 1];
+  };
+  auto take = [&](int at) {
+    lo = __builtin_amdgcn_readlane(lo, at);
+    hi = __builtin_amdgcn_readlane(hi, at);
+  };
+  // told to be wave-uniform, what is derived from these stays in scalar registers
+  auto found = [&](int seg, int index) {
+    return Found{__builtin_amdgcn_readfirstlane(seg), __builtin_amdgcn_readfirstlane(lo), __builtin_amdgcn_readfirstlane(hi),
+                 __builtin_amdgcn_readfirstlane(index)};
+  };
+  if (n_segs <= 64) {
+    look();
+    const int items = lane < n_segs && hi > lo ? count(hi - lo) : 0, sum = prefix_sum(items);
+    const int index = (int)item;
+    if (index >= __builtin_amdgcn_readlane(sum, 63)) return Found{-1, 0, 0, 0};
+    const int at = __builtin_ctzll(__ballot(sum > index));
+    take(at);
+    return found(at, index - __builtin_amdgcn_readlane(sum, at) + __builtin_amdgcn_readlane(items, at));
+  }
+  if (n_segs <= kDenseSegments) {  // lane l: segments 4 l .. 4 l + 3, those past the end empty
+    int start[kDensePerLane + 1], items[kDensePerLane], mine_all = 0;
+#pragma unroll
+    for (int k = 0; k <= kDensePerLane; ++k) start[k] = seg_starts[min(kDensePerLane * lane + k, n_segs)];
+#pragma unroll
+    for (int k = 0; k < kDensePerLane; ++k) {
+      items[k] = start[k + 1] > start[k] ? count(start[k + 1] - start[k]) : 0;
+      mine_all += items[k];
+    }
+    const int sum = prefix_sum(mine_all);
+    int index = (int)item;
+    if (index >= __builtin_amdgcn_readlane(sum, 63)) return Found{-1, 0, 0, 0};
+    const int at = __builtin_ctzll(__ballot(sum > index));
+    index -= __builtin_amdgcn_readlane(sum, at) - __builtin_amdgcn_readlane(mine_all, at);
+    int seg = kDensePerLane * at;
+    lo = __builtin_amdgcn_readlane(start[0], at);
+    hi = __builtin_amdgcn_readlane(start[1], at);
+    int before = __builtin_amdgcn_readlane(items[0], at);  // items of the lane's segments up to `seg`
+#pragma unroll
+    for (int k = 1; k < kDensePerLane; ++k) {
+      const int more = __builtin_amdgcn_readlane(items[k], at);
+      const int next = __builtin_amdgcn_readlane(start[k + 1], at);
+      if (index >= before) {
+        index -= before;
+        before = more;
+        seg = kDensePerLane * at + k;
+        lo = hi;
+        hi = next;
+      }
+    }
+    return found(seg, index);
+  }
+  // first block of segment i (n_tokens + 65535 * 127 fits 32 bits)
+  auto first_of = [](int start, int i) { return ((unsigned)start + (unsigned)i * (ROWS - 1)) / ROWS; };
+  const unsigned block = item / (unsigned)per_block;
+  // the last segment whose part starts at or before the block
+  base = min(max((int)((float)block * guess) - 32, 0), n_segs - 64);
+  look();
+  int at = __popcll(__ballot(first_of(lo, base + lane) <= block)) - 1;
+  if (at < 0 || (at == 63 && base + 64 < n_segs && first_of(__builtin_amdgcn_readlane(hi, 63), base + 64) <= block)) {
+    int from = at < 0 ? 0 : base + 64, to = at < 0 ? base : n_segs;  // among these, and `from` starts at or before
+    while (to - from > 64) {
+      const int step = (to - from + 63) / 64, i = from + lane * step;
+      const bool before = i < to && first_of(seg_starts[min(i, n_segs)], i) <= block;
+      from += (__popcll(__ballot(before)) - 1) * step;
+      to = min(to, from + step);
+    }
+    base = from;
+    look();
+    at = __popcll(__ballot(base + lane < to && first_of(lo, base + lane) <= block)) - 1;
+  }
+  take(at);
+  // a segment with fewer items than places takes other places in every block: workgroup ids go round the eight
+  // XCDs, so that always the first places of a multiple of eight would be always the same XCDs
+  int part = (int)(item - block * (unsigned)per_block) + (int)(block * (unsigned)turn % (unsigned)per_block);
+  if (part >= per_block) part -= per_block;
+  const int index = (int)(block - first_of(lo, base + at)) * per_block + part;
+  return found(hi > lo && index < count(hi - lo) ? base + at : -1, index);
+}
+// Length of the list at most; `guess` for find_item.
 static long long most_blocks(int n_tokens, int n_segs, int rows) {
   const long long b = ((long long)n_tokens + (long long)n_segs * (rows - 1)) / rows;
-  return b < n_tokens ? b : n_tokens;
+  return n_segs <= kDenseSegments && b > n_tokens ? n_tokens : b;
 }
+static float segments_per_block(int n_segs, long long blocks) { return (float)n_segs / (float)blocks; }
 
 // Sum of the split-K parts of four consecutive k of one row (ascending order), then the two
 // 16-bit operand parts of the MFMA expand and the row's range factor: binary16 has a narrow
@@ -178,8 +265,8 @@ struct ShrinkTable {
 
 template <class DT, int R, int P>
 __global__ __launch_bounds__((64 * ShrinkShape<R, P>::kWaves), 4) void shrink_stream_kernel(
-    const int32_t* __restrict__ seg_starts, int n_segs, int slices, int groups, int h_in, int kslice, int n_tokens,
-    long long layer_off, unsigned long long* header, ShrinkTable tab) {
+    const int32_t* __restrict__ seg_starts, int n_segs, float guess, int slices, int groups, int h_in, int kslice,
+    int n_tokens, long long layer_off, unsigned long long* header, ShrinkTable tab) {
   using Shape = ShrinkShape<R, P>;
   constexpr int NT = 64 * Shape::kWaves;
   constexpr int NTILE = Shape::kTiles;
@@ -205,8 +292,8 @@ __global__ __launch_bounds__((64 * ShrinkShape<R, P>::kWaves), 4) void shrink_st
   const unsigned row_of_eight = id / (8 * (unsigned)groups), in_row = id - row_of_eight * 8 * (unsigned)groups;
   const unsigned pair = row_of_eight * 8 + in_row % 8;
   const int s = pair % (unsigned)slices;
-  const Found at_seg = find_item(seg_starts, n_segs, (int)(pair / (unsigned)slices), lane,
-                                 [](int rows) { return (rows + Shape::kRows - 1) / Shape::kRows; });
+  const Found at_seg = find_item<Shape::kRows>(seg_starts, n_segs, pair / (unsigned)slices, 1, 0, guess, lane,
+                                               [](int rows) { return (rows + Shape::kRows - 1) / Shape::kRows; });
   if (at_seg.seg < 0) return;
   const int block_row = at_seg.lo + at_seg.index * Shape::kRows;
   const int p0 = (int)(in_row / 8) * P;
@@ -432,8 +519,8 @@ __device__ __forceinline__ uint2 add4(const uint2& y, float scale, const f32x4 (
 
 template <class DT, int R>
 __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
-    const int32_t* __restrict__ seg_starts, int n_segs, int strips, int few_strips, int h_out, long long layer_off,
-    float scale, unsigned long long* header, ExpandTable tab) {
+    const int32_t* __restrict__ seg_starts, int n_segs, float guess, int strips, int few_strips, int h_out,
+    long long layer_off, float scale, unsigned long long* header, ExpandTable tab) {
   constexpr int NC = kExpandCols;        // columns of a strip
   constexpr int CT = 4;                  // 16-column tiles (and columns per lane) of a group
   constexpr int NG = NC / (16 * CT);     // column groups of the strip
@@ -461,7 +548,7 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
 
   unsigned index = blockIdx.x;
   if (blockIdx.z != 0) index += blockIdx.z * gridDim.x;
-  const Found it = find_item(seg_starts, n_segs, (int)index, lane, [=](int rows) {
+  const Found it = find_item<kExpandRows>(seg_starts, n_segs, index, strips, few_strips, guess, lane, [=](int rows) {
     return few_strips > 0 && rows <= kFewRows ? few_strips : (rows + kExpandRows - 1) / kExpandRows * strips;
   });
   if (it.seg < 0) return;
@@ -698,8 +785,8 @@ static hipError_t launch_shrink_matrix_p(const ShrinkArgs& a, hipStream_t st) {
   const long long blocks = most_blocks(a.n_tokens, a.n_segs, Shape::kRows);
   const long long wgs = (a.ksplit * blocks + 7) / 8 * 8 * groups;
   const dim3 grid((unsigned)(wgs < kMostWorkgroups ? wgs : kMostWorkgroups), (unsigned)((wgs + kMostWorkgroups - 1) / kMostWorkgroups));
-  hipLaunchKernelGGL((shrink_stream_kernel<DT, R, P>), grid, dim3(64 * Shape::kWaves), 0, st, a.seg_starts, a.n_segs, a.ksplit,
-                     groups, a.h_in, a.kslice, a.n_tokens, a.layer_off, a.header, tab);
+  hipLaunchKernelGGL((shrink_stream_kernel<DT, R, P>), grid, dim3(64 * Shape::kWaves), 0, st, a.seg_starts, a.n_segs,
+                     segments_per_block(a.n_segs, blocks), a.ksplit, groups, a.h_in, a.kslice, a.n_tokens, a.layer_off, a.header, tab);
   return hipGetLastError();
 }
 
@@ -762,8 +849,8 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, hipStream_
   const long long wgs = strips * blocks;
   const dim3 grid((unsigned)(wgs < kMostWorkgroups ? wgs : kMostWorkgroups), (unsigned)n,
                   (unsigned)((wgs + kMostWorkgroups - 1) / kMostWorkgroups));
-  hipLaunchKernelGGL((expand_matrix_kernel<DT, R>), grid, dim3(256), 0, st, a.seg_starts, a.n_segs, strips, few, a.h_out, a.layer_off,
-                     a.scale, a.header, tab);
+  hipLaunchKernelGGL((expand_matrix_kernel<DT, R>), grid, dim3(256), 0, st, a.seg_starts, a.n_segs,
+                     segments_per_block(a.n_segs, blocks), strips, few, a.h_out, a.layer_off, a.scale, a.header, tab);
   return hipGetLastError();
 }
 

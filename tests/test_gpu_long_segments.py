@@ -82,6 +82,36 @@ def test_adding_nothing_keeps_every_value(path, lens, dtype):
     assert np.array_equal(got, kept, equal_nan=True)    # -0 + 0 is +0, which compares equal
 
 
+# How a workgroup finds its segment: 64 segments in one round of a wave, 256 at four per lane, a search beyond, whose
+# first guess is right for equal lengths and whose further rounds take 64 and 4096 segments at once
+MANY = {
+    "65": [3] * 65, "256": [1, 0, 7, 2] * 64, "257": [1, 0, 70, 2] * 64 + [5], "equal": [9] * 300, "empty": [0] * 400 + [20] + [0] * 200,
+    "front": [3000] + [2] * 700, "back": [1, 0, 3] * 250 + [2500, 4], "far": [0, 1, 2] * 1500 + [4000] + [3, 80] * 100,
+}
+
+
+@pytest.mark.parametrize("lens,dtype,r,P,h_in,h_out", [
+    ("65", "f16", 8, 3, 136, 264), ("65", "bf16", 64, 1, 264, 4104), ("256", "bf16", 16, 1, 136, 2056), ("256", "f16", 64, 2, 264, 264),
+    ("257", "f16", 16, 1, 264, 4104), ("257", "bf16", 32, 3, 136, 264), ("equal", "bf16", 8, 1, 136, 520), ("empty", "f16", 32, 2, 136, 264),
+    ("front", "bf16", 64, 1, 136, 264), ("front", "f16", 16, 3, 136, 2048), ("back", "f16", 64, 1, 264, 2048), ("back", "bf16", 16, 1, 136, 264),
+    ("far", "bf16", 8, 1, 136, 264), ("far", "f16", 64, 2, 136, 264)])
+def test_many_segments(lens, dtype, r, P, h_in, h_out):
+    from paper_2310_18547_amd import binding as B
+    lens = MANY[lens]
+    n = len(lens)
+    # five adapters, one segment in seven has none
+    ws = [wl.custom(lens, h_in, h_out, r, dtype, seed=60 + r + k, scale=0.5,
+                    seg_adapter=[-1 if i % 7 == 3 else (i * 3 + k) % 5 for i in range(n)]) for k in range(P)]
+    ds = [_dev(w, path=B.PATH_MATRIX, n_proj=P) for w in ws]
+    if P == 1:
+        ds[0].add_lora()
+    else:
+        B.sgmv_add_lora_multi(ds[0].problem, [d.y[0] for d in ds], [d.x[0] for d in ds], [d.A_ptrs for d in ds],
+                              [d.B_ptrs for d in ds], ds[0].seg_starts, n, 0, 0.5)
+    for k, (d, w) in enumerate(zip(ds, ws)):
+        assert_parity(d.y_bits(), oracle.run_workload(w, n_threads=8), dtype, f"add-on {k} of {P}")
+
+
 def test_more_workgroups_than_one_dimension_of_a_grid_holds():
     """65535 segments x 257 strips of columns x 256 threads is more than 2^32."""
     from paper_2310_18547_amd import binding as B
