@@ -474,7 +474,7 @@ struct ExpandTable {
 };
 
 // grid = (items, add-ons, further items); vh / vl / undo come from finalize_v_kernel.  The list of items: for a segment
-// of more than kFewRows rows (few_strips = 0: of any length) its 64-row blocks x strips of 256 columns, for a shorter one its strips of 2048
+// of more than few_rows rows its 64-row blocks x strips of 256 columns, for a shorter one its strips of 2048
 // columns.
 //
 // Block items.  The product is taken as D = v B_i with the token rows in the first operand: lane
@@ -501,9 +501,10 @@ struct ExpandTable {
 // Strip items (one or two rows, where there are enough of them: launch_expand_matrix_t): nothing to reuse, a row
 // of B_i is streamed to the vector ALUs, eight columns per lane, eight rows of it in flight (three projections of
 // 4096 -> 4096, 41 decode rows beside three prompts of 1152 rows, rank 16: 22.5 -> 17.0 us).  Three and four rows are
-// blocks: taken in pairs, each pair reading B_i past the caches again, they cost up to twice as much (expand to
-// 13824 at rank 64 of 8 / 40 / 100 segments of three rows 21.6 / 33.3 / 68.3 us against 8.7 / 21.9 / 47.6).
-constexpr int kFewRows = 2;
+// taken in pairs, each pair reading B_i again, and cost up to twice as much as blocks (expand to 13824 at rank 64
+// of 8 / 40 / 100 segments of three rows 21.6 / 33.3 / 68.3 us against 8.7 / 21.9 / 47.6) -- except at rank 8, where B_i is one
+// batch of loads, and where they are many (expand to 13824 of 100, 700 items, 15.0 against 19.0; add-on 4096 -> 4096 of 100,
+// 200 items, 17.0 against 18.3, of 40, 80 items, 13.7 against 13.0).
 constexpr int kFewCols = 2048;
 
 // y[0 .. 3] of one row: y + scale * sum
@@ -519,7 +520,7 @@ __device__ __forceinline__ uint2 add4(const uint2& y, float scale, const f32x4 (
 
 template <class DT, int R>
 __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
-    const int32_t* __restrict__ seg_starts, int n_segs, float guess, int strips, int few_strips, int h_out,
+    const int32_t* __restrict__ seg_starts, int n_segs, float guess, int strips, int few_rows, int few_strips, int h_out,
     long long layer_off, float scale, unsigned long long* header, ExpandTable tab) {
   constexpr int NC = kExpandCols;        // columns of a strip
   constexpr int CT = 4;                  // 16-column tiles (and columns per lane) of a group
@@ -549,7 +550,7 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
   unsigned index = blockIdx.x;
   if (blockIdx.z != 0) index += blockIdx.z * gridDim.x;
   const Found it = find_item<kExpandRows>(seg_starts, n_segs, index, strips, few_strips, guess, lane, [=](int rows) {
-    return few_strips > 0 && rows <= kFewRows ? few_strips : (rows + kExpandRows - 1) / kExpandRows * strips;
+    return rows <= few_rows ? few_strips : (rows + kExpandRows - 1) / kExpandRows * strips;
   });
   if (it.seg < 0) return;
   const uint16_t* B = tab.B_ptrs[z][it.seg];
@@ -557,55 +558,57 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
   if (tab.A_ptrs[z] != nullptr && tab.A_ptrs[z][it.seg] == nullptr) return;
   SGMV_TRACE_POINT(8);
   {
-    if (few_strips > 0 && it.hi - it.lo <= kFewRows) {
+    if (it.hi - it.lo <= few_rows) {
       const int c = it.index * kFewCols + tid * 8;
       const uint32_t off = c < h_out ? (uint32_t)c * 2u : kOutOfRange;
       constexpr int JC = 8;  // weight rows in flight
       const __amdgpu_buffer_rsrc_t rB = make_uniform_buffer(B + layer_off, (uint32_t)((long long)R * h_out * 2));
-      const int row = it.lo;
-      const bool two = row + 1 < it.hi;
-      uint4 b[JC];
+      for (int row = it.lo; row < it.hi; row += 2) {
+        const bool two = row + 1 < it.hi;
+        uint4 b[JC];
 #pragma unroll
-      for (int j = 0; j < JC; ++j) b[j] = buffer_load128<kNonTemporal>(rB, off + (uint32_t)(j * h_out) * 2u);
-      const __amdgpu_buffer_rsrc_t rY = make_uniform_buffer(y + (long long)row * h_out, (uint32_t)(two ? 2 : 1) * h_out * 2u);
-      const uint4 y0 = buffer_load128<kNonTemporal>(rY, off);
-      const uint4 y1 = buffer_load128<kNonTemporal>(rY, off + (uint32_t)h_out * 2u);
-      // lane j: v[row][j], v[row + 1][j]
-      const int vj = min(lane, R - 1), second = two ? R : 0;
-      const uint16_t *const h = vh + (long long)row * R + vj, *const l = vl + (long long)row * R + vj;
-      const float u0 = std::is_same<DT, F16>::value ? undo[row] : 1.f;
-      const float u1 = std::is_same<DT, F16>::value ? undo[two ? row + 1 : row] : 1.f;
-      const int v0 = __float_as_int((decode1<DT>(h[0]) + decode1<DT>(l[0])) * (scale * u0));
-      const int v1 = __float_as_int((decode1<DT>(h[second]) + decode1<DT>(l[second])) * (scale * u1));
-      float s0[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, s1[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < JC; ++j) b[j] = buffer_load128<kNonTemporal>(rB, off + (uint32_t)(j * h_out) * 2u);
+        const __amdgpu_buffer_rsrc_t rY = make_uniform_buffer(y + (long long)row * h_out, (uint32_t)(two ? 2 : 1) * h_out * 2u);
+        const uint4 y0 = buffer_load128<kNonTemporal>(rY, off);
+        const uint4 y1 = buffer_load128<kNonTemporal>(rY, off + (uint32_t)h_out * 2u);
+        // lane j: v[row][j], v[row + 1][j]
+        const int vj = min(lane, R - 1), second = two ? R : 0;
+        const uint16_t *const h = vh + (long long)row * R + vj, *const l = vl + (long long)row * R + vj;
+        const float u0 = std::is_same<DT, F16>::value ? undo[row] : 1.f;
+        const float u1 = std::is_same<DT, F16>::value ? undo[two ? row + 1 : row] : 1.f;
+        const int v0 = __float_as_int((decode1<DT>(h[0]) + decode1<DT>(l[0])) * (scale * u0));
+        const int v1 = __float_as_int((decode1<DT>(h[second]) + decode1<DT>(l[second])) * (scale * u1));
+        float s0[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, s1[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-      for (int jc = 0; jc < R; jc += JC) {
+        for (int jc = 0; jc < R; jc += JC) {
 #pragma unroll
-        for (int j = 0; j < JC; ++j) {
-          // one row at a time: the compiler would widen all of them to fp32 first, and spill
-          asm volatile("" : "+v"(b[j].x), "+v"(b[j].y), "+v"(b[j].z), "+v"(b[j].w), "+v"(s0[7]), "+v"(s1[7]));
-          float w[8];
-          unpack8<DT>(b[j], w);
-          // its register takes the row that follows eight later (none: past the end of the buffer): the
-          // loads in flight never run dry
-          if (R > JC) b[j] = buffer_load128<kNonTemporal>(rB, off + (uint32_t)((jc + JC + j) * h_out) * 2u);
-          const float f0 = __int_as_float(__builtin_amdgcn_readlane(v0, jc + j));
-          const float f1 = __int_as_float(__builtin_amdgcn_readlane(v1, jc + j));
+          for (int j = 0; j < JC; ++j) {
+            // one row at a time: the compiler would widen all of them to fp32 first, and spill
+            asm volatile("" : "+v"(b[j].x), "+v"(b[j].y), "+v"(b[j].z), "+v"(b[j].w), "+v"(s0[7]), "+v"(s1[7]));
+            float w[8];
+            unpack8<DT>(b[j], w);
+            // its register takes the row that follows eight later (none: past the end of the buffer): the
+            // loads in flight never run dry
+            if (R > JC) b[j] = buffer_load128<kNonTemporal>(rB, off + (uint32_t)((jc + JC + j) * h_out) * 2u);
+            const float f0 = __int_as_float(__builtin_amdgcn_readlane(v0, jc + j));
+            const float f1 = __int_as_float(__builtin_amdgcn_readlane(v1, jc + j));
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            s0[e] = fmaf(f0, w[e], s0[e]);
-            s1[e] = fmaf(f1, w[e], s1[e]);
+            for (int e = 0; e < 8; ++e) {
+              s0[e] = fmaf(f0, w[e], s0[e]);
+              s1[e] = fmaf(f1, w[e], s1[e]);
+            }
           }
         }
+        auto put = [&](const uint4& q, const float (&sum)[8], uint32_t at) {
+          float f[8];
+          unpack8<DT>(q, f);
+          buffer_store128<kNonTemporal>(rY, at, make_uint4(pack2<DT>(f[0] + sum[0], f[1] + sum[1]), pack2<DT>(f[2] + sum[2], f[3] + sum[3]),
+                                                           pack2<DT>(f[4] + sum[4], f[5] + sum[5]), pack2<DT>(f[6] + sum[6], f[7] + sum[7])));
+        };
+        put(y0, s0, off);
+        if (two) put(y1, s1, off + (uint32_t)h_out * 2u);
+        if (R > 8) break;  // two rows at most
       }
-      auto put = [&](const uint4& q, const float (&sum)[8], uint32_t at) {
-        float f[8];
-        unpack8<DT>(q, f);
-        buffer_store128<kNonTemporal>(rY, at, make_uint4(pack2<DT>(f[0] + sum[0], f[1] + sum[1]), pack2<DT>(f[2] + sum[2], f[3] + sum[3]),
-                                                         pack2<DT>(f[4] + sum[4], f[5] + sum[5]), pack2<DT>(f[6] + sum[6], f[7] + sum[7])));
-      };
-      put(y0, s0, off);
-      if (two) put(y1, s1, off + (uint32_t)h_out * 2u);
     } else {
       const int block = it.index / strips, strip = it.index - block * strips;
       const int row0 = it.lo + block * kExpandRows, left = it.hi - row0;
@@ -831,8 +834,8 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, hipStream_
     tab.A_ptrs[i] = (const uint16_t* const*)e.A_ptrs;
     tab.B_ptrs[i] = (const uint16_t* const*)e.B_ptrs;
   }
-  const long long items = (long long)a.n_tokens * (R / 4);
-  hipLaunchKernelGGL((finalize_v_kernel<DT, R>), dim3((unsigned)((items + 255) / 256), (unsigned)n), dim3(256), 0, st, a.nparts,
+  const long long quads = (long long)a.n_tokens * (R / 4);
+  hipLaunchKernelGGL((finalize_v_kernel<DT, R>), dim3((unsigned)((quads + 255) / 256), (unsigned)n), dim3(256), 0, st, a.nparts,
                      a.n_tokens, fin);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
@@ -844,13 +847,14 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, hipStream_
   // and 64, of 40 (80 items) 12.1 / 13.8, 14.5 / 15.2, 17.3 / 16.3 and 26.8 / 24.3; the expand to 13824 of 40 (280
   // items) 6.5 / 12.6, 8.4 / 13.3, 12.1 / 15.4 and 18.8 / 21.0.
   int few = (a.h_out + kFewCols - 1) / kFewCols;
-  if ((long long)a.n_segs * few * n < 4 * R) few = 0;
+  const long long items = (long long)a.n_segs * few * n;
+  const int few_rows = items < 4 * R ? 0 : R == 8 && items >= 200 ? 4 : 2;
   const long long blocks = most_blocks(a.n_tokens, a.n_segs, kExpandRows);
   const long long wgs = strips * blocks;
   const dim3 grid((unsigned)(wgs < kMostWorkgroups ? wgs : kMostWorkgroups), (unsigned)n,
                   (unsigned)((wgs + kMostWorkgroups - 1) / kMostWorkgroups));
   hipLaunchKernelGGL((expand_matrix_kernel<DT, R>), grid, dim3(256), 0, st, a.seg_starts, a.n_segs,
-                     segments_per_block(a.n_segs, blocks), strips, few, a.h_out, a.layer_off, a.scale, a.header, tab);
+                     segments_per_block(a.n_segs, blocks), strips, few_rows, few, a.h_out, a.layer_off, a.scale, a.header, tab);
   return hipGetLastError();
 }
 
