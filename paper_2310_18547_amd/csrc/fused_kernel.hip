@@ -384,9 +384,16 @@ __device__ __forceinline__ void add_lora_fused_body(
   SGMV_TRACE_FLUSH(tid == 0, 8, 8);
 }
 
+// Waves per SIMD that the registers must leave room for.  The per-row kernels of rank 32 with two lane groups serve up
+// to 480 workgroups of five waves; in bfloat16 the compiler takes 162 registers, three waves per SIMD, where 128 do
+// without spilling: 40 / 60 segments of 120 rows, 4096 -> 4096, 12.3 / 12.9 us against 10.5 / 11.0, one segment of 60
+// rows, 11008 -> 11008, 14.4 against 11.9.
+template <int R, int G, int MODE>
+constexpr int fused_waves = by_row(MODE) && R == 32 && G == 2 ? 4 : 1;
+
 // One add-on per launch.
 template <class DT, int R, int G, int RB, int MODE>
-__global__ __launch_bounds__(320) void add_lora_fused_kernel(
+__global__ __launch_bounds__(320, (fused_waves<R, G, MODE>)) void add_lora_fused_kernel(
     // the first sixteen dwords are preloaded into SGPRs at wave launch: keep what the
     // first dependent loads need at the front
     const int32_t* __restrict__ seg_starts, const uint16_t* const* __restrict__ A_ptrs,
@@ -415,7 +422,7 @@ __global__ __launch_bounds__(320) void add_lora_fused_kernel(
 // stretch of the workspace.  Used while all workgroups of the launch are resident together
 // (small batches); larger launches take the pipelined kernel in fused_multi_kernel.hip.
 template <class DT, int R, int G, int MODE>
-__global__ __launch_bounds__(320) void add_lora_fused_side_kernel(
+__global__ __launch_bounds__(320, (fused_waves<R, G, MODE>)) void add_lora_fused_side_kernel(
     const int32_t* __restrict__ seg_starts, int kslice, int cslice, int h_in, int h_out, int n_tokens,
     int S, long long offA, long long offB, unsigned long long* exch, unsigned long long* header,
     float scale, int spin_limit, int n_segs, int n_proj, FusedTable tab) {
