@@ -6,6 +6,8 @@
 // whole product of its segment (the shrink phase of fused_whole_kernel.hip: all of A_i in flight at
 // once, up to 32 128-bit loads per lane) and adds it to the caller's v itself: no partial sums,
 // no second launch that adds them up, no workspace.
+#include <type_traits>
+
 #include "device_common.h"
 #include "launch.h"
 
@@ -13,10 +15,10 @@ namespace sgmv {
 
 // grid = n_segs workgroups of 256 threads.  U = 128-bit loads of A_i per lane and batch, all in
 // flight together; the launch picks the largest U of 32 .. 1 with h_in * R / 8 a multiple of 256 * U.
-// BY_ROW: grid = the rows of the batch rounded up to a multiple of eight; a workgroup serves one row
+// MODE with kPerRow: grid = the rows of the batch rounded up to a multiple of eight; a workgroup serves one row
 // and looks the row's segment up (n_segs of them), blockIdx.x % 8, the XCD it lands on, taking a run
 // of consecutive rows, which then find their segment's A_i in one L2.
-template <class DT, int R, int U, bool BY_ROW>
+template <class DT, int R, int U, int MODE>
 __global__ __launch_bounds__(256) void shrink_whole_kernel(
     const int32_t* __restrict__ seg_starts, const uint16_t* const* __restrict__ A_ptrs,
     const uint16_t* __restrict__ x, float* __restrict__ v, int h_in, long long offA, int n_tokens, int n_segs) {
@@ -28,7 +30,7 @@ __global__ __launch_bounds__(256) void shrink_whole_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int seg = blockIdx.x, lo, hi;
-  if constexpr (BY_ROW) {
+  if constexpr (by_row(MODE)) {
     const int row = ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3);
     if (row >= n_tokens) return;
     seg = segment_of_row(seg_starts, n_segs, row, lane);
@@ -56,7 +58,7 @@ __global__ __launch_bounds__(256) void shrink_whole_kernel(
     for (int i = 0; i < XL; ++i) xr[i] = buffer_load128(rX, (uint32_t)(i * NT + tid) * 16u);  // zeros beyond the row
     uint4 a[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = buffer_load128_at<BY_ROW ? 0 : kNonTemporal>(rA, a_lane, (uint32_t)u * (NT * 16u));
+    for (int u = 0; u < U; ++u) a[u] = buffer_load128_at<weights_aux(MODE)>(rA, a_lane, (uint32_t)u * (NT * 16u));
     const float before = tid < R ? v[(long long)row * R + tid] : 0.f;
 #pragma unroll
     for (int i = 0; i < XL; ++i) store128(&xs[(i * NT + tid) * 8], xr[i]);
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(256) void shrink_whole_kernel(
     for (int batch = 0; batch < nbatch; ++batch) {
       if (batch != 0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = buffer_load128_at<BY_ROW ? 0 : kNonTemporal>(rA, a_lane, (uint32_t)(batch * U + u) * (NT * 16u));
+        for (int u = 0; u < U; ++u) a[u] = buffer_load128_at<weights_aux(MODE)>(rA, a_lane, (uint32_t)(batch * U + u) * (NT * 16u));
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -91,14 +93,17 @@ __global__ __launch_bounds__(256) void shrink_whole_kernel(
 
 template <class DT, int R, int U>
 static hipError_t launch_shrink_whole_t(const ShrinkArgs& a, hipStream_t st, float* v) {
+  const auto launch = [&](auto mode_tag, int workgroups) {
+    constexpr int MODE = decltype(mode_tag)::value;
+    hipLaunchKernelGGL((shrink_whole_kernel<DT, R, U, MODE>), dim3((unsigned)workgroups), dim3(256), 0, st, a.seg_starts,
+                       (const uint16_t* const*)a.A_ptrs, (const uint16_t*)a.x, v, a.h_in, a.layer_off, a.n_tokens, a.n_segs);
+  };
   if (a.by_rows)
-    hipLaunchKernelGGL((shrink_whole_kernel<DT, R, U, true>), dim3((unsigned)((a.n_tokens + 7) / 8 * 8)), dim3(256), 0, st,
-                       a.seg_starts, (const uint16_t* const*)a.A_ptrs, (const uint16_t*)a.x, v, a.h_in, a.layer_off,
-                       a.n_tokens, a.n_segs);
+    launch(std::integral_constant<int, kPerRow>{}, (a.n_tokens + 7) / 8 * 8);
+  else if (stream_weights(false, a.n_tokens, a.n_segs, R, a.h_in))
+    launch(std::integral_constant<int, kPerSegment | kStreamed>{}, a.n_segs);
   else
-    hipLaunchKernelGGL((shrink_whole_kernel<DT, R, U, false>), dim3((unsigned)a.n_segs), dim3(256), 0, st, a.seg_starts,
-                       (const uint16_t* const*)a.A_ptrs, (const uint16_t*)a.x, v, a.h_in, a.layer_off, a.n_tokens,
-                       a.n_segs);
+    launch(std::integral_constant<int, kPerSegment>{}, a.n_segs);
   return hipGetLastError();
 }
 
