@@ -260,11 +260,12 @@ int fused_lane_groups(int r, int cslice, bool single_add_on) {
   return g;
 }
 
-// Memory round trips of a workgroup at s slices: batches of 2048 128-bit loads of A_i, then passes over
-// its columns of B_i.
+// Memory round trips of a workgroup at s slices: batches of 2048 128-bit loads of A_i, then (h_out = 0: a shrink on
+// its own has none) passes over its columns of B_i.
 int fused_round_trips(const sgmv_problem* p, int s, bool single_add_on) {
   const int kslice = ceil_div(ceil_div(p->h_in, s), 8) * 8, cslice = ceil_div(ceil_div(p->h_out, s), 8) * 8;
-  return ceil_div(kslice * (p->r / 8), 2048) + ceil_div(cslice, 256 / fused_lane_groups(p->r, cslice, single_add_on) * 8);
+  const int batches = ceil_div(kslice * (p->r / 8), 2048);
+  return cslice == 0 ? batches : batches + ceil_div(cslice, 256 / fused_lane_groups(p->r, cslice, single_add_on) * 8);
 }
 
 // Launch shape of the single-launch path; false when it does not apply.
@@ -733,7 +734,7 @@ int plan_shrink(const sgmv_problem* p, int n_segs, ShrinkPlan* pl) {
   // it (measured at h = 4096, r = 16, 1 / 16 / 64 / 128 segments: 3.5 / 4.0 / 5.0 / 6.6 us against
   // 4.8 / 6.1 / 6.7 / 8.1 us for shrink + reduction; r = 64, 64 segments: 9.5 against 10.7)
   sgmv_problem shrink_only = *p;
-  shrink_only.h_out = p->h_in;  // the output width plays no part here (and need not be set by the caller)
+  shrink_only.h_out = 0;  // the output width plays no part here (and need not be set by the caller)
   // one workgroup per one-row segment computes the whole product: no Split-K, no second launch
   const bool whole_shape = p->ksplit == 0 && p->h_in <= kWholeMaxHin && (long long)p->h_in * (p->r / 8) % 256 == 0;
   const bool whole_fits = p->max_seg_len == 1 && whole_shape;

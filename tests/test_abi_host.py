@@ -624,10 +624,9 @@ def test_long_segments_put_up_to_three_add_ons_into_a_launch():
             assert rc == 0 and plan.launches == 3 * n_proj
 
 
-def test_no_kernel_keeps_registers_in_scratch_memory():
-    """From the kernels' metadata in the built library: each says how much scratch a lane needs."""
+def _kernel_metadata(key):
+    """A number of every kernel's metadata in the built library, by the kernel's mangled name."""
     data = open(sg.library_path(), "rb").read()
-    key = b".private_segment_fixed_size"
     sizes = {}
     for name in re.finditer(rb"\.name(?:[\xa0-\xbf]|\xd9.|\xda..)(_ZN4sgmv\w+)", data, re.S):
         at = data.index(key, name.start()) + len(key)
@@ -635,4 +634,25 @@ def test_no_kernel_keeps_registers_in_scratch_memory():
         width = {0xCC: 1, 0xCD: 2, 0xCE: 4}.get(kind, 0)
         sizes[name[1].decode()] = int.from_bytes(data[at + 1:at + 1 + width], "big") if width else kind
     assert len(sizes) > 100
-    assert [n for n, size in sizes.items() if size] == []
+    return sizes
+
+
+def test_no_kernel_keeps_registers_in_scratch_memory():
+    assert [n for n, size in _kernel_metadata(b".private_segment_fixed_size").items() if size] == []
+
+
+def test_per_row_kernels_of_rank_32_leave_room_for_four_waves_per_simd():
+    # names end in ... R, G[, RB], MODE and the parameters; an odd MODE is per row; 512 registers per SIMD and lane
+    rows = re.compile(r"add_lora_fused(_side)?_kernelINS_\w+?ELi32ELi2E(Li1E)?Li[13]EE")
+    registers = {n: v for n, v in _kernel_metadata(b".vgpr_count").items() if rows.search(n)}
+    assert len(registers) == 8 and max(registers.values()) <= 128, registers
+
+
+def test_slices_of_the_stand_alone_shrink_count_its_own_loads_only():
+    # one-row segments, eight XCDs: 40 and 48 workgroups a slice leave room for six and five slices of 256; rounds of 2048 loads at
+    # four / five / six slices: 10 / 8 / 7 (9984 wide) and 8 / 7 (8192 wide)
+    for n, h_in, slices in ((37, 9984, 6), (46, 8192, 5)):
+        room = sg.sgmv_workspace_bytes(n, 64)
+        p = sg.make_problem(sg.BF16, h_in, 0, 64, 1, n, workspace=256, workspace_bytes=room, max_seg_len=1, workspace_ready=1)
+        rc, plan = sg.sgmv_plan_shrink(p, n, check=False)
+        assert rc == 0 and (plan.kernel, plan.slices) == (sg.KERNEL_FUSED, slices)
