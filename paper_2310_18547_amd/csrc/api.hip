@@ -184,8 +184,10 @@ bool expand_use_matrix(const sgmv_problem* p, int n_segs) {
 
 // Split-K shape of the MFMA shrink of n_proj add-ons: about kMatrixWaves waves in flight, a power of two
 // slices, so that a slice's workgroups (consecutive ids) meet on the same XCDs and its part of A_i in
-// their L2s (8192 wide, rank 16, 4814 rows, 8 / 11 / 16 slices: 18.6 / 19.9 / 17.4 us), and no more than leaves
-// the partial sums, written and read again, half the bytes of x (11432 wide, rank 64, three add-ons of 724
+// their L2s (8192 wide, rank 16, 4814 rows, 8 / 11 / 16 slices: 18.6 / 19.9 / 17.4 us; the whole add-on to 4096, rank 16, 5120
+// and 8192 wide, 700 rows, 23 / 16 slices: 14.0 / 12.5 and 15.2 / 13.0, 11008 wide, 1000 rows, 17 / 16: 18.2 / 15.1; rank 64, 13824
+// wide, 700 rows, 23 / 16: 21.1 / 22.0), and from four slices on only as many as leave the partial sums of all add-ons,
+// written and read again, about half the bytes of one x, two thirds at most (11432 wide, rank 64, three add-ons of 724
 // rows, the whole call at 4 / 8 / 15 slices: 45.0 / 32.3 / 33.1 us; 3272 wide, 3254 rows, 2 / 4 / 13: 61.3 / 62.4 / 67.1).
 void choose_split_matrix(const sgmv_problem* p, int n_segs, int n_proj, bool same_x, int* ksplit, int* kslice) {
   const int cap = split_cap(p->n_tokens);
@@ -200,8 +202,8 @@ void choose_split_matrix(const sgmv_problem* p, int n_segs, int n_proj, bool sam
     while (s * 3 * waves <= 2LL * kMatrixWaves && (s < 4 || s * 3 <= 2 * by_partials)) s *= 2;
   }
   const int most = p->h_in / 128 > 0 ? p->h_in / 128 : 1;  // keep slices of at least one chunk
-  if (s > most) s = most;
-  if (s > cap) s = cap;
+  const int limit = most < cap ? most : cap;
+  while (s > limit) s = p->ksplit > 0 ? limit : s / 2;
   if (s < 1) s = 1;
   const int len = ceil_div(ceil_div(p->h_in, s), 32) * 32;
   *kslice = len;

@@ -656,3 +656,12 @@ def test_slices_of_the_stand_alone_shrink_count_its_own_loads_only():
         p = sg.make_problem(sg.BF16, h_in, 0, 64, 1, n, workspace=256, workspace_bytes=room, max_seg_len=1, workspace_ready=1)
         rc, plan = sg.sgmv_plan_shrink(p, n, check=False)
         assert rc == 0 and (plan.kernel, plan.slices) == (sg.KERNEL_FUSED, slices)
+
+
+def test_slices_of_long_segments_are_a_power_of_two():
+    # beside what the workspace holds (16384 / rows, 16 at least) and what leaves a slice 128 wide
+    for r, h_in, rows, slices in ((32, 11008, 1000, 16), (16, 5120, 700, 16), (16, 5120, 300, 32), (64, 13824, 700, 16), (8, 520, 130, 4)):
+        p = sg.make_problem(sg.BF16, h_in, 4096, r, 1, rows, workspace=256, workspace_bytes=sg.sgmv_workspace_bytes(rows, r),
+                            max_seg_len=rows // 2, path=sg.PATH_MATRIX)
+        rc, plan = sg.sgmv_plan_add_lora(p, 2, 1, check=False)
+        assert rc == 0 and (plan.kernel, plan.slices) == (sg.KERNEL_MATRIX, slices)
