@@ -167,6 +167,8 @@ typedef struct sgmv_plan {
   int32_t kernel;      /* sgmv_kernel of every add-on                                      */
   int32_t launches;    /* kernel launches of the whole call                                */
   int32_t slices;      /* workgroups per segment (single-launch kernels) or split-K factor */
+                       /* (several add-ons on the MFMA kernels: that of the first launch   */
+                       /* where its add-ons read one x)                                    */
   int32_t workgroups;  /* workgroups of the (first) launch; 0 where it depends on lengths  */
   int32_t lds_bytes;   /* dynamic LDS per workgroup (tile kernel), else 0                  */
   int32_t reserved[3];
@@ -181,11 +183,11 @@ const char* sgmv_status_string(int status);
  * function.  Returns 0 for n_tokens <= 0. */
 size_t sgmv_workspace_bytes(int32_t n_tokens, int32_t r);
 
-/* Workspace size that also lets sgmv_add_lora_multi share one pass over x between the shrinks
- * of up to three add-ons on long (prefill-shaped) segments that read the same x, e.g. q / k / v or
- * gate / up (the paper applies LoRA to all dense projections of a layer): the size of
- * sgmv_workspace_bytes plus room for the partial sums of the other add-ons.  A workspace of the
- * plain size works everywhere; such calls then run one add-on after the other. */
+/* Workspace size that also lets sgmv_add_lora_multi put up to three add-ons on long (prefill-shaped)
+ * segments into one launch of each kernel, e.g. q / k / v or gate / up (the paper applies LoRA to
+ * all dense projections of a layer), with one pass over x where they read the same one: the size
+ * of sgmv_workspace_bytes plus room for the partial sums and operands of the other add-ons.  A
+ * workspace of the plain size works everywhere; such calls then run one add-on after the other. */
 size_t sgmv_workspace_bytes_multi(int32_t n_tokens, int32_t r, int32_t n_proj);
 
 /* Prepare a workspace for the single-launch paths of sgmv_add_lora: clears it

@@ -33,7 +33,7 @@ constexpr int kTargetWorkgroups = 512; // about two workgroups per compute unit
 // that every (segment, sixteen-row block, slice) workgroup must be resident at once with its
 // weight slices in LDS (choose_tile): about 64 row blocks in all at h = 4096.
 constexpr int kTileMaxSegLen = 4096;
-constexpr int kMatrixMaxSegments = 65535;  // the MFMA kernels put the segment on a grid dimension limited to this
+constexpr int kMatrixMaxSegments = 65535;  // the MFMA kernels place a segment by 32-bit arithmetic that holds for this many (find_item)
 constexpr int kFusedSlices = 8;        // most slices per segment the single-launch kernels pick
 constexpr int kRowsMostSegments = 256;  // segments up to which SGMV_PATH_AUTO launches per row (four rounds of the look-up)
 constexpr long long kShrinkWholeMostElements = 48LL << 20;  // weights (96 MB) up to which the stand-alone shrink runs without Split-K
@@ -122,7 +122,7 @@ int check_common(const sgmv_problem* p, const int32_t* seg_starts, int32_t n_seg
   if (p->expand_threads != 0 && p->expand_threads != 64 && p->expand_threads != 128 &&
       p->expand_threads != 256 && !(p->expand_threads == kExpandSplit && p->r >= 32))
     return SGMV_ERR_UNSUPPORTED;
-  if (p->path == SGMV_PATH_MATRIX && n_segs > 65535) return SGMV_ERR_UNSUPPORTED;  // grid dimension of the MFMA kernels
+  if (p->path == SGMV_PATH_MATRIX && n_segs > kMatrixMaxSegments) return SGMV_ERR_UNSUPPORTED;
   if (layer_idx < 0 || layer_idx >= p->num_layers) return SGMV_ERR_RANGE;
   if (n_segs > 0 && p->n_tokens > 0 && seg_starts == nullptr) return SGMV_ERR_NULL;
   return SGMV_OK;
@@ -381,7 +381,6 @@ bool choose_fused(const sgmv_problem* p, int n_segs, FusedArgs* f, bool single_a
   f->kslice = ceil_div(ceil_div(p->h_in, s), 8) * 8;
   f->cslice = ceil_div(ceil_div(p->h_out, s), 8) * 8;
   f->G = fused_lane_groups(p->r, f->cslice, single_add_on);
-  f->rows_per_pass = 1;
   return true;
 }
 
@@ -576,7 +575,6 @@ ExpandArgs make_expand(const sgmv_problem* p, void* y, const float* v_parts, int
   a.n_tokens = p->n_tokens;
   a.n_segs = n_segs;
   a.threads = choose_expand_threads(p, n_segs);
-  a.max_seg_len = p->max_seg_len;
   a.layer_off = (long long)layer_idx * p->r * p->h_out;
   a.y = y;
   a.v_parts = v_parts;

@@ -163,7 +163,8 @@ namespace sgmv {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr uint32_t kOutOfRange = 0x80000000u;
-// AUX of an access whose whole cache lines are touched once and not again by this launch (nt bit).
+// AUX of an access whose whole cache lines are best left out of the caches: touched once by this launch, or so
+// seldom again that reading them twice costs less (nt bit).
 constexpr int kNonTemporal = 2;
 constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit data format
 
@@ -192,11 +193,6 @@ __device__ __forceinline__ uint4 buffer_load128_at(__amdgpu_buffer_rsrc_t rsrc, 
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-template <int AUX = 0>
-__device__ __forceinline__ uint2 buffer_load64(__amdgpu_buffer_rsrc_t rsrc, uint32_t byte_off) {
-  u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)byte_off, 0, AUX);
-  return make_uint2(v.x, v.y);
-}
 // 64-bit accesses with a wave-uniform byte offset added to the lane's
 template <int AUX = 0>
 __device__ __forceinline__ uint2 buffer_load64_at(__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_byte_off,
@@ -209,12 +205,6 @@ __device__ __forceinline__ void buffer_store64_at(__amdgpu_buffer_rsrc_t rsrc, u
                                                   uint32_t uniform_byte_off, const uint2& q) {
   u32x2 v = {q.x, q.y};
   __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, (int)lane_byte_off, (int)uniform_byte_off, AUX);
-}
-template <int AUX = 0>
-__device__ __forceinline__ void buffer_store64(__amdgpu_buffer_rsrc_t rsrc, uint32_t byte_off,
-                                               const uint2& q) {
-  u32x2 v = {q.x, q.y};
-  __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, (int)byte_off, 0, AUX);
 }
 template <int AUX = 0>
 __device__ __forceinline__ void buffer_store128(__amdgpu_buffer_rsrc_t rsrc, uint32_t byte_off,

@@ -493,7 +493,9 @@ template <class DT, int R, int G>
 static hipError_t launch_fused_rb(const FusedArgs& a, hipStream_t st) {
   const bool streamed = stream_weights(a.by_rows, a.n_tokens, a.n_segs, a.r, (long long)a.h_in + a.h_out);
   if (a.n_proj > 0) {
-    if (!a.by_rows) return launch_fused_side_t<DT, R, G, kPerSegment | kStreamed>(a, st);  // ahead at every size (seven segments: 8.4 -> 7.9 us)
+    // streamed at every size (seven segments: 8.4 -> 7.9 us); only segments that carry the same pointers lose by it (128
+    // of eight adapters, rank 64, three add-ons 34.2 -> 39.9), and such rows belong in one segment
+    if (!a.by_rows) return launch_fused_side_t<DT, R, G, kPerSegment | kStreamed>(a, st);
     return streamed ? launch_fused_side_t<DT, R, G, kPerRow | kStreamed>(a, st) : launch_fused_side_t<DT, R, G, kPerRow>(a, st);
   }
   if (a.by_rows)

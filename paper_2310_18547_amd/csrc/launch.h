@@ -56,7 +56,6 @@ struct ExpandArgs {
   int r, h_out, n_tokens, n_segs;
   int threads;               // vector path: workgroup size
   bool by_rows;              // vector path: a workgroup per row of the batch (it looks its segment up), not per segment
-  int max_seg_len;           // hint, 0 = unknown
   long long layer_off;       // elements to add to every B pointer
   void* y;
   const float* v_parts;      // [nparts][n_tokens][r]
@@ -88,7 +87,6 @@ struct FusedArgs {
   int S;                     // workgroups per segment = k-slices = column slices
   int kslice, cslice;        // elements per k-slice / columns per column slice
   int G;                     // lane groups of the expand phase (1, 2, 4 or 8)
-  int rows_per_pass;         // 1 when every segment is a single row, else 4
   bool by_rows;              // the grid's items are the n_tokens rows, each looking its segment up, not the segments
   int spin_limit;            // polls before a waiting workgroup gives up
   long long offA, offB;      // layer offsets in elements

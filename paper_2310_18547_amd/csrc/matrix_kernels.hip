@@ -24,9 +24,9 @@
 //   finalize_v_kernel      sums the partial sums in ascending order and writes v as a high and a
 //           low 16-bit part (16 significant bits for bfloat16, 22 for binary16) plus a range
 //           factor per row (binary16).  v stays fp32 in the workspace until then.
-//   expand_matrix_kernel   workgroup = (strip of columns, block of rows, add-on).
+//   expand_matrix_kernel   workgroup = (strip of columns, block of rows or short segment, add-on).
 //
-// All add-ons of a call go into one launch of each kernel.  4814 rows of eight segments, bfloat16: 8192 ->
+// Up to three add-ons of a call go into one launch of each kernel.  4814 rows of eight segments, bfloat16: 8192 ->
 // 8192 at rank 16 61.4 -> 53.3 us, 8192 -> 28672 at rank 64 167 -> 144; three projections of 4096 -> 4096, 41 decode
 // rows beside three prompts of 1152 rows, rank 16: 69.5 -> 33.1; of 3272 -> 4096, 3254 rows, rank 64: 119 -> 62.8.
 #include <type_traits>
@@ -39,8 +39,8 @@
 
 namespace sgmv {
 
-constexpr int kExpandCols = 256;   // columns per expand workgroup (64 per wave)
-constexpr int kExpandRows = 64;    // rows per expand workgroup and step (sixteen per wave in the row-wise kernel)
+constexpr int kExpandCols = 256;   // columns of a block item of the expand
+constexpr int kExpandRows = 64;    // its rows
 
 // ---------------------------------------------------------------- row blocks
 //
@@ -249,8 +249,9 @@ struct ShrinkShape {
   static constexpr int kTiles = (R + 15) / 16;              // 16-column tiles of one add-on
   static constexpr int kColumns = P * R;
   static constexpr int kWaves = kColumns > 32 ? 8 : 4;      // more waves to share a larger chunk of A_i
-  // k per LDS buffer: 128, so that four workgroups of the widest shape fit a compute unit (rank 64,
-  // 4814 rows of 8192: 44 us with 256, two workgroups per unit, against 26; with 64: 28)
+  // k per LDS buffer: 128.  Two chunks' operands of x and one chunk of A_i are in registers at a time, 88 registers at
+  // rank 64; with 256 they pass the 128 of four waves per SIMD and 29 go to scratch memory (4814 rows of 8192: 44 us
+  // against 26; with 64: 28)
   static constexpr int kChunk = 128;
   static constexpr int kBlk = kTiles * 16 + 1;              // 16-byte slots {8 k of one column} per 8 k; the odd pitch spreads the banks
   static constexpr int kRows = 16 * kWaves;
