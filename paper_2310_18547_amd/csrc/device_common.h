@@ -216,8 +216,8 @@ __device__ __forceinline__ void buffer_store128(__amdgpu_buffer_rsrc_t rsrc, uin
 // What the items of a single-row kernel's grid are (template argument MODE): the segments, or the
 // rows of the batch, each looking its segment up (kPerRow); and whether the weights are read past the
 // caches (non-temporal, kStreamed), which pays where a launch reads many of them once (launch.h,
-// stream_weights).
-constexpr int kPerSegment = 0, kPerRow = 1, kStreamed = 2;
+// stream_weights); and whether more than one workgroup per compute unit has to be resident (kCrowded).
+constexpr int kPerSegment = 0, kPerRow = 1, kStreamed = 2, kCrowded = 4;
 constexpr bool by_row(int mode) { return (mode & kPerRow) != 0; }
 constexpr int weights_aux(int mode) { return (mode & kStreamed) != 0 ? kNonTemporal : 0; }
 

@@ -384,16 +384,17 @@ __device__ __forceinline__ void add_lora_fused_body(
   SGMV_TRACE_FLUSH(tid == 0, 8, 8);
 }
 
-// Waves per SIMD that the registers must leave room for.  The per-row kernels of rank 32 with two lane groups serve up
-// to 480 workgroups of five waves; in bfloat16 the compiler takes 162 registers, three waves per SIMD, where 128 do
-// without spilling: 40 / 60 segments of 120 rows, 4096 -> 4096, 12.3 / 12.9 us against 10.5 / 11.0, one segment of 60
-// rows, 11008 -> 11008, 14.4 against 11.9.
-template <int R, int G, int MODE>
-constexpr int fused_waves = by_row(MODE) && R == 32 && G == 2 ? 4 : 1;
+// Waves per SIMD that the registers must leave room for (MODE with kCrowded).  The per-row kernels of rank 32 with
+// two lane groups serve up to 480 workgroups of five waves; in bfloat16 the compiler takes 162 registers, three waves per
+// SIMD, where 128 do without spilling: 40 / 60 segments of 120 rows, 4096 -> 4096, 12.3 / 12.9 us against 10.5 / 11.0, one
+// segment of 60 rows, 11008 -> 11008, 14.4 against 11.9.  Up to a workgroup per unit the 162 are ahead (8 segments of 64
+// rows, 5120 -> 5120, 9.1 against 9.35).
+constexpr int kUncrowded = 256;
+constexpr int fused_waves(int mode) { return (mode & kCrowded) != 0 ? 4 : 1; }
 
 // One add-on per launch.
 template <class DT, int R, int G, int RB, int MODE>
-__global__ __launch_bounds__(320, (fused_waves<R, G, MODE>)) void add_lora_fused_kernel(
+__global__ __launch_bounds__(320, fused_waves(MODE)) void add_lora_fused_kernel(
     // the first sixteen dwords are preloaded into SGPRs at wave launch: keep what the
     // first dependent loads need at the front
     const int32_t* __restrict__ seg_starts, const uint16_t* const* __restrict__ A_ptrs,
@@ -422,7 +423,7 @@ __global__ __launch_bounds__(320, (fused_waves<R, G, MODE>)) void add_lora_fused
 // stretch of the workspace.  Used while all workgroups of the launch are resident together
 // (small batches); larger launches take the pipelined kernel in fused_multi_kernel.hip.
 template <class DT, int R, int G, int MODE>
-__global__ __launch_bounds__(320, (fused_waves<R, G, MODE>)) void add_lora_fused_side_kernel(
+__global__ __launch_bounds__(320, fused_waves(MODE)) void add_lora_fused_side_kernel(
     const int32_t* __restrict__ seg_starts, int kslice, int cslice, int h_in, int h_out, int n_tokens,
     int S, long long offA, long long offB, unsigned long long* exch, unsigned long long* header,
     float scale, int spin_limit, int n_segs, int n_proj, FusedTable tab) {
@@ -489,17 +490,23 @@ static hipError_t launch_fused_side_t(const FusedArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <class DT, int R, int G, int MODE>
+static hipError_t launch_fused_rows(const FusedArgs& a, hipStream_t st) {
+  if constexpr (R == 32 && G == 2 && (MODE & kCrowded) == 0) {
+    if ((long long)a.S * a.n_tokens * (a.n_proj > 0 ? a.n_proj : 1) > kUncrowded)
+      return launch_fused_rows<DT, R, G, MODE | kCrowded>(a, st);
+  }
+  return a.n_proj > 0 ? launch_fused_side_t<DT, R, G, MODE>(a, st) : launch_fused_t<DT, R, G, 1, MODE>(a, st);
+}
+
 template <class DT, int R, int G>
 static hipError_t launch_fused_rb(const FusedArgs& a, hipStream_t st) {
   const bool streamed = stream_weights(a.by_rows, a.n_tokens, a.n_segs, a.r, (long long)a.h_in + a.h_out);
-  if (a.n_proj > 0) {
-    // streamed at every size (seven segments: 8.4 -> 7.9 us); only segments that carry the same pointers lose by it (128
-    // of eight adapters, rank 64, three add-ons 34.2 -> 39.9), and such rows belong in one segment
-    if (!a.by_rows) return launch_fused_side_t<DT, R, G, kPerSegment | kStreamed>(a, st);
-    return streamed ? launch_fused_side_t<DT, R, G, kPerRow | kStreamed>(a, st) : launch_fused_side_t<DT, R, G, kPerRow>(a, st);
-  }
   if (a.by_rows)
-    return streamed ? launch_fused_t<DT, R, G, 1, kPerRow | kStreamed>(a, st) : launch_fused_t<DT, R, G, 1, kPerRow>(a, st);
+    return streamed ? launch_fused_rows<DT, R, G, kPerRow | kStreamed>(a, st) : launch_fused_rows<DT, R, G, kPerRow>(a, st);
+  // streamed at every size (seven segments: 8.4 -> 7.9 us); only segments that carry the same pointers lose by it (128
+  // of eight adapters, rank 64, three add-ons 34.2 -> 39.9), and such rows belong in one segment
+  if (a.n_proj > 0) return launch_fused_side_t<DT, R, G, kPerSegment | kStreamed>(a, st);
   return streamed ? launch_fused_t<DT, R, G, 1, kPerSegment | kStreamed>(a, st) : launch_fused_t<DT, R, G, 1, kPerSegment>(a, st);
 }
 
