@@ -84,12 +84,14 @@ int spin_limit_of(const sgmv_problem* p) { return p->spin_limit > 0 ? p->spin_li
 // AUTO uses the MFMA kernels from this segment length on.  Their work goes with the number of
 // segments (every segment occupies at least one block of 64 rows), that of the vector kernels
 // with the rows: measured at h = 4096, 128 segments of 4 rows, ranks 8 / 16 / 32 / 64: vector
-// kernels 14.4 / 18.2 / 28.9 / 45.1 us against 23.9 / 26.3 / 31.3 / 47.7; 64 segments of 8 rows,
-// ranks 16 / 64: MFMA 19.1 / 37.6 against 25.1 / 60.6.
+// kernels 13.9 / 18.8 / 26.6 / 42.3 us against 18.7 / 22.0 / 27.1 / 40.6; 64 segments of 8 rows,
+// ranks 16 / 64: MFMA 16.7 / 25.2 against 24.4 / 42.3.  (At rank 64 the line lies a little high: 64
+// segments of 4 / 5 rows, MFMA 23.6 / 23.8 against 24.8 / 36.6.)
 constexpr int kMatrixMinSegLen = 6;
 // At rank 64 the vector kernels are slow enough that the MFMA kernels win from two rows per
-// segment on while the segments are few (32 segments of 2 / 4 rows: 21.7 / 21.9 us against 23.1 /
-// 31.4; the Uniform mix of 39 segments: 26.3 against 34.6; 64 segments of 4 rows: 36.9 against 34.0).
+// segment on while the segments are few (32 segments of 2 / 4 rows: 16.2 / 16.7 us against 15.8 /
+// 18.8; the Uniform mix of 64 rows, 42 segments: 20.7 against 20.9, of 256 rows, 63 segments of up to 8:
+// 23.8 against 39.5).
 constexpr int kMatrixFewSegments = 48;
 constexpr int kMatrixWaves = 4096;     // waves the MFMA shrink aims for (four per SIMD)
 
@@ -172,9 +174,9 @@ bool use_matrix(const sgmv_problem* p, int n_segs) {
 }
 
 // The stand-alone expand at rank 64 is ahead on the MFMA kernels for more short segments than the
-// shrink and the add-on are (h = 4096, 64 segments of 2 / 4 rows: 12.4 / 12.7 us against 16.1 / 20.4
-// on the vector kernel; Uniform mix of 128 rows, 56 segments: 11.8 against 27.3; 128 segments of 2
-// rows: 20.3 against 20.6).
+// shrink and the add-on are (h = 4096, 64 segments of 2 / 4 rows: 11.5 / 12.0 us against 10.2 / 12.3
+// on the vector kernel; Uniform mix of 128 rows, 57 segments: 11.2 against 15.0; 128 segments of 2
+// rows: 16.2 against 16.9).
 bool expand_use_matrix(const sgmv_problem* p, int n_segs) {
   if (use_matrix(p, n_segs)) return true;
   if (p->path != SGMV_PATH_AUTO || p->r < 64 || n_segs > 128) return false;
@@ -430,13 +432,12 @@ bool choose_tile(const sgmv_problem* p, int n_segs_one, TileArgs* t, int n_proj 
   if (n_segs > kFusedMaxWorkgroups) return false;
   // At rank 64 a full block of sixteen rows hands 8 KB of tagged words per slice from workgroup
   // to workgroup, and the launch-per-step MFMA kernels are ahead from about ten rows per segment
-  // on (h = 4096, one segment of 16 / 64 / 256 rows: 14.8 / 16.0 / 17.8 us against 20.2 / 20.2 /
-  // 20.7 here; Skewed mix of 32 rows, longest segment 12: 15.4 against 17.0; segments of up to 8
-  // rows: 13.0-15.5 here against 14.8-17.2)
-  // (a joint launch of several add-ons hands them over side by side in the same 20 us, which beats
-  // the launch-per-step kernels one add-on after the other from about 64 rows on: two segments
-  // of 32 rows, three add-ons 21.4 against 25.1 us; of 64 rows 22.4 against 48.7; one of 32 rows
-  // 20.9 against 18.4)
+  // on (h = 4096, one segment of 16 / 64 / 256 rows: 13.1 / 15.5 / 15.7 us against 21.2 / 20.8 /
+  // 21.3 here; four segments of 12 rows: 13.5 against 18.0; sixteen of 8 rows: 14.5 against 15.6)
+  // (a joint launch of several add-ons hands them over side by side in the same 20 us, where the
+  // launch-per-step kernels ran one add-on after the other: 47.7 us for three of two segments of 64
+  // rows.  Side by side these are ahead too, 20.5 against 23.3 here, of 32 rows 18.4 against 22.5, so
+  // from 64 rows on a joint launch is no longer the better one, by 10-20 %)
   if (p->path == SGMV_PATH_AUTO && p->r >= 64 && p->max_seg_len > 8 && (n_proj < 2 || p->n_tokens < 64)) return false;
   const int cap = split_cap(p->n_tokens);
   const int narrow = p->h_in < p->h_out ? p->h_in : p->h_out;
@@ -875,6 +876,9 @@ int plan_multi(const sgmv_problem* p, int n_segs, int n_proj, FusedArgs* f, Tile
   // against add-ons per row one after the other it is ahead also in groups and with fewer slices
   // (four add-ons, rank 8: 32 x 2 rows in two launches 17.5 against 19.4, Skewed of 64 rows at
   // three slices 11.8 against 18.4; rank 32: 32 x 4 rows 30.4 against 40.6)
+  // (The launch-per-step kernels, which take the add-ons side by side too, are not asked here: at rank 64
+  // they are ahead, 16 x 8 rows two / three add-ons 20.4 / 22.5 against 31.4 / 47.3, 64 x 4 rows 38.5 / 53.9
+  // against 49 / 74, and from 64 x 4 rows on at ranks 16 / 32, three add-ons 24.4 / 33.7 against 31.3 / 42.3.)
   if (tile && (!per_row || (t->n_proj == n_proj && t->S >= kTileMultiSlices))) return SGMV_KERNEL_TILE;
   if (per_row && !rows_first) {
     const int kernel = joint_rows();

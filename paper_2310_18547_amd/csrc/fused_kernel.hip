@@ -386,7 +386,7 @@ __device__ __forceinline__ void add_lora_fused_body(
 
 // Waves per SIMD that the registers must leave room for (MODE with kCrowded).  The per-row kernels of rank 32 with
 // two lane groups serve up to 480 workgroups of five waves; in bfloat16 the compiler takes 162 registers, three waves per
-// SIMD, where 128 do without spilling: 40 / 60 segments of 120 rows, 4096 -> 4096, 12.3 / 12.9 us against 10.5 / 11.0, one
+// SIMD, where 128 do without spilling: 120 rows of 40 / 60 segments, 4096 -> 4096, 12.3 / 12.9 us against 10.5 / 11.0, one
 // segment of 60 rows, 11008 -> 11008, 14.4 against 11.9.  Up to a workgroup per unit the 162 are ahead (8 segments of 64
 // rows, 5120 -> 5120, 9.1 against 9.35).
 constexpr int kUncrowded = 256;
