@@ -354,9 +354,9 @@ def run_timeline(args):
         names[3], names[5] = "shrink done (all of A_i consumed)", "v summed over the waves"
     if op != "add_lora":
         order = [0, 8, 1, 2, 6]
-        names[1] = "first tiles and weight loads issued"
-        names[2] = "weight slice transposed into LDS"
-        names[6] = "last tile done (results stored)"
+        names[1] = "first chunk's loads issued" if op == "shrink" else "strip of the weights arrived and placed in LDS"
+        names[2] = "last chunk consumed" if op == "shrink" else "strip placed by all waves"
+        names[6] = "results stored"
     points = []
     live_counts = []
     for p_ in order:
