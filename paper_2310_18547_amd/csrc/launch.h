@@ -167,7 +167,9 @@ inline long long fused_grid_items(long long items) {
 // rank 32 10.6 -> 10.3; but three segments of 4096 -> 12424, rank 32 (3 MB) 6.51 -> 6.73, 13 segments of a
 // 4096-wide rank-64 shrink (7 MB) 5.37 -> 5.45, and 90 rows of one adapter 11.2 -> 14.2, which the hint
 // takes out of the caches before the next row wants it.  A stand-alone shrink without Split-K of one segment (128 KB) whose
-// layers stay in the cache behind the L2s: 3.45 -> 4.28.
+// layers stay in the cache behind the L2s: 3.45 -> 4.28.  (Larger launches lose too while that cache
+// holds all their layers, 64 segments of a 5120-wide shrink, rank 16, 168 MB in rotation 5.37 -> 5.67; a program that uses its other
+// weights between two calls of a layer does not find them there.)
 inline bool stream_weights(bool by_rows, int n_tokens, int n_segs, int r, long long width) {
   return n_segs * width * r >= (4LL << 20) && (!by_rows || n_tokens <= 3LL * n_segs);
 }
