@@ -366,9 +366,16 @@ bool choose_fused(const sgmv_problem* p, int n_segs, FusedArgs* f, bool single_a
   // (not so eight slices, whose shares are small: 11008 -> 4096, 51 segments, the launch that took over
   // against eight slices: rank 32 17.5 / 12.5 us, rank 64 26.6 / 23.2; 45 rows of 18 adapters, bfloat16:
   // 13.7 / 10.7 and 37.3 / 16.9; but at rank 64 up to 40 segments, 320 workgroups, keep what they had: 13824 ->
-  // 5120, 35 segments 24.8 / 26.3)
+  // 5120, 33 / 36 / 40 segments, binary16 24.5 / 25.0, 22.9 / 25.7 and 24.8 / 26.1, bfloat16 24.3 / 27.4, 22.8 / 28.2 and
+  // 24.8 / 28.6; and so do up to 48 segments in bfloat16, which spends more on a value, where a workgroup passes over its
+  // columns of B_i more than once: 13824 -> 5120, 41 / 44 / 48 segments 26.6 / 28.7, 26.1 / 29.2, 27.0 / 29.8, 12544 -> 8192
+  // 27.4 / 29.6, 27.3 / 29.9, 29.0 / 30.3; not 13440 -> 4096, one pass, 26.4 / 25.8, 25.9 / 26.3, 25.9 / 26.2, nor 13824 -> 5120 in
+  // binary16 26.7 / 26.3, 26.2 / 26.9, 27.3 / 27.5)
+  const int cslice = ceil_div(ceil_div(p->h_out, s), 8) * 8;
+  const bool one_pass = cslice == 0 || cslice <= 256 / fused_lane_groups(p->r, cslice, single_add_on) * 8;
+  const long long few = p->dtype == SGMV_BF16 && !one_pass ? 48 : 40;
   if (p->path == SGMV_PATH_AUTO && p->ksplit == 0 && p->r >= 32 &&
-      !(eight && (by_rows || p->r < 64 || padded > 40)) && (long long)s * n_segs > lim.fused_workgroups) {
+      !(eight && (by_rows || p->r < 64 || padded > few)) && (long long)s * n_segs > lim.fused_workgroups) {
     const long long wg = (long long)s * n_segs;
     const long long rounds = ceil_div((int)wg, lim.fused_workgroups);
     if (rounds * lim.fused_workgroups * 5 > wg * 6) return false;  // more than 20 % of the slots idle

@@ -659,6 +659,22 @@ def test_slices_of_the_stand_alone_shrink_count_its_own_loads_only():
         assert rc == 0 and (plan.kernel, plan.slices) == (sg.KERNEL_FUSED, slices)
 
 
+def test_eight_slices_on_more_workgroups_than_units_only_where_they_are_ahead():
+    # a wide input that forces seven slices or six: 48 segments make 384 workgroups for 256 units.  At rank 64 a workgroup
+    # passes over 512 columns of B_i at a time, an eighth of 4096
+    for dtype, n, h_in, h_out, kernel in (
+            (sg.BF16, 48, 13824, 5120, sg.KERNEL_VECTOR), (sg.BF16, 41, 12288, 8192, sg.KERNEL_VECTOR),
+            (sg.BF16, 49, 13824, 5120, sg.KERNEL_FUSED), (sg.F16, 41, 13824, 5120, sg.KERNEL_FUSED),
+            (sg.BF16, 41, 13440, 4096, sg.KERNEL_FUSED), (sg.BF16, 41, 13440, 4104, sg.KERNEL_VECTOR),
+            (sg.F16, 40, 13824, 5120, sg.KERNEL_VECTOR), (sg.BF16, 40, 13824, 4096, sg.KERNEL_VECTOR)):
+        p = sg.make_problem(dtype, h_in, h_out, 64, 1, n, workspace=256, workspace_bytes=sg.sgmv_workspace_bytes(n, 64),
+                            max_seg_len=1, workspace_ready=1)
+        rc, plan = sg.sgmv_plan_add_lora(p, n, 1, check=False)
+        assert rc == 0 and plan.kernel == kernel, (dtype, n, h_in, h_out)
+        rc, plan = sg.sgmv_plan_shrink(p, n, check=False)  # the shrink alone has no columns to pass over
+        assert rc == 0 and plan.kernel == (sg.KERNEL_FUSED if n > 40 else sg.KERNEL_VECTOR), (dtype, n, h_in, h_out)
+
+
 def test_slices_of_long_segments_are_a_power_of_two():
     # beside what the workspace holds (16384 / rows, 16 at least) and what leaves a slice 128 wide
     for r, h_in, rows, slices in ((32, 11008, 1000, 16), (16, 5120, 700, 16), (16, 5120, 300, 32), (64, 13824, 700, 16), (8, 520, 130, 4)):
