@@ -370,12 +370,16 @@ bool choose_fused(const sgmv_problem* p, int n_segs, FusedArgs* f, bool single_a
   // 24.8 / 28.6; and so do up to 48 segments in bfloat16, which spends more on a value, where a workgroup passes over its
   // columns of B_i more than once: 13824 -> 5120, 41 / 44 / 48 segments 26.6 / 28.7, 26.1 / 29.2, 27.0 / 29.8, 12544 -> 8192
   // 27.4 / 29.6, 27.3 / 29.9, 29.0 / 30.3; not 13440 -> 4096, one pass, 26.4 / 25.8, 25.9 / 26.3, 25.9 / 26.2, nor 13824 -> 5120 in
-  // binary16 26.7 / 26.3, 26.2 / 26.9, 27.3 / 27.5)
+  // binary16 26.7 / 26.3, 26.2 / 26.9, 27.3 / 27.5.  At rank 32, where two passes are needed from 8192 columns on, the
+  // launch-per-step kernels are ahead as long as their expand, a workgroup per segment and 512 columns, is resident at once, four per
+  // unit: 12544 -> 9216, 36 / 40 / 48 segments 16.3 / 19.4, 17.2 / 19.9, 19.2 / 20.3, -> 11008, 46 / 48 segments 20.8 / 21.3, 21.9 /
+  // 21.5, -> 13824, 36 / 39 segments 18.1 / 21.0, 22.6 / 21.3; beyond 48 segments, 53 of 11008 -> 9216 20.6 / 19.7)
   const int cslice = ceil_div(ceil_div(p->h_out, s), 8) * 8;
   const bool one_pass = cslice == 0 || cslice <= 256 / fused_lane_groups(p->r, cslice, single_add_on) * 8;
-  const long long few = p->dtype == SGMV_BF16 && !one_pass ? 48 : 40;
+  const bool many = padded > 48 || (p->r >= 64 ? padded > 40 && (p->dtype == SGMV_F16 || one_pass)
+                                               : one_pass || (long long)n_segs * ceil_div(p->h_out, 512) > 4 * lim.fused_workgroups);
   if (p->path == SGMV_PATH_AUTO && p->ksplit == 0 && p->r >= 32 &&
-      !(eight && (by_rows || p->r < 64 || padded > few)) && (long long)s * n_segs > lim.fused_workgroups) {
+      !(eight && (by_rows || many)) && (long long)s * n_segs > lim.fused_workgroups) {
     const long long wg = (long long)s * n_segs;
     const long long rounds = ceil_div((int)wg, lim.fused_workgroups);
     if (rounds * lim.fused_workgroups * 5 > wg * 6) return false;  // more than 20 % of the slots idle

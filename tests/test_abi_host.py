@@ -673,6 +673,19 @@ def test_eight_slices_on_more_workgroups_than_units_only_where_they_are_ahead():
         assert rc == 0 and plan.kernel == kernel, (dtype, n, h_in, h_out)
         rc, plan = sg.sgmv_plan_shrink(p, n, check=False)  # the shrink alone has no columns to pass over
         assert rc == 0 and plan.kernel == (sg.KERNEL_FUSED if n > 40 else sg.KERNEL_VECTOR), (dtype, n, h_in, h_out)
+    # rank 32: two passes beyond 8192 columns; four workgroups of the expand, a segment and 512 columns each, per unit: 1024
+    for dtype in (sg.F16, sg.BF16):
+        for n, h_in, h_out, kernel in ((37, 13824, 13824, sg.KERNEL_VECTOR), (38, 13824, 13824, sg.KERNEL_FUSED),
+                                       (46, 13440, 11008, sg.KERNEL_VECTOR), (47, 13440, 11008, sg.KERNEL_FUSED),
+                                       (33, 13440, 16384, sg.KERNEL_FUSED), (48, 12544, 8256, sg.KERNEL_VECTOR),
+                                       (49, 12544, 8256, sg.KERNEL_FUSED),
+                                       (33, 13824, 5120, sg.KERNEL_FUSED), (33, 13824, 8192, sg.KERNEL_FUSED)):
+            p = sg.make_problem(dtype, h_in, h_out, 32, 1, n, workspace=256, workspace_bytes=sg.sgmv_workspace_bytes(n, 32),
+                                max_seg_len=1, workspace_ready=1)
+            rc, plan = sg.sgmv_plan_add_lora(p, n, 1, check=False)
+            assert rc == 0 and plan.kernel == kernel, (dtype, n, h_in, h_out)
+            rc, plan = sg.sgmv_plan_shrink(p, n, check=False)
+            assert rc == 0 and plan.kernel == sg.KERNEL_FUSED, (dtype, n, h_in, h_out)
 
 
 def test_slices_of_long_segments_are_a_power_of_two():
