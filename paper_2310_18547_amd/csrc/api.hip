@@ -2,6 +2,7 @@
 // Everything that computes runs in the kernels; this file only validates and
 // enqueues.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <atomic>
@@ -93,6 +94,7 @@ constexpr int kMatrixMinSegLen = 6;
 // 18.8; the Uniform mix of 64 rows, 42 segments: 20.7 against 20.9, of 256 rows, 63 segments of up to 8:
 // 23.8 against 39.5).
 constexpr int kMatrixFewSegments = 48;
+
 constexpr int kMatrixWaves = 4096;     // waves the MFMA shrink aims for (four per SIMD)
 
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -184,6 +186,30 @@ bool expand_use_matrix(const sgmv_problem* p, int n_segs) {
   return len >= 2;
 }
 
+// Split-K shape of the MFMA shrink of n_proj add-ons and whether the expand behind it adds the partial sums up itself
+// (`direct`, a launch less).
+struct MatrixSplit {
+  int ksplit, kslice;
+  bool direct;
+};
+
+// Direct: every workgroup of the expand reads the partial sums of its 64 rows, r * slices * 256 bytes beside 64 KB of y, and
+// each of the eight L2s fetches most of them once more, which takes back the 2 us of a launch at about 2 MB of partial sums.
+// Three launches / two, us (binary16): 700 rows, rank 16, sixteen slices, 4096 -> 4096 11.8 / 9.8 and -> 11008 14.9 / 13.6; 60
+// segments of 8 rows, eight slices, 14.3 / 12.7; 1152 rows beside 41 of one row, eight slices, 15.9 / 14.1, three projections of
+// them 29.4 / 28.9, to 11008 (2300 workgroups) 52.0 / 53.0; three of 3440 rows, 8192 -> 2048, 35.3 / 36.5.  At rank 32 the
+// partial sums are too many (1152 rows beside 41, eight slices, 19.1 / 20.4), at rank 64 also the operands in LDS.
+// Three launches from 2000 rows on, as sgmv_plan_add_lora has told the callers of such batches (two would be 16.7 against 17.7
+// us at 2000 rows, rank 16, 4096 wide, and 46.6 against 47.6 at 4814, 8192 wide).
+constexpr int kDirectMostRows = 1920;
+bool matrix_direct(const sgmv_problem* p, int n_segs, int n_proj, int slices) {
+  if (p->path == SGMV_PATH_MATRIX || p->r > 16 || p->n_tokens > kDirectMostRows) return false;
+  if (n_segs > 104) return false;  // every short segment is a block of its own (300 of 5 rows, 2048 -> 8192, rank 16: 39.6 / 52.0)
+  const long long sums = (long long)p->n_tokens * n_proj * p->r * slices;
+  const long long workgroups = (long long)ceil_div(p->n_tokens, 64) * ceil_div(p->h_out, 256) * n_proj;
+  return p->r * slices <= 256 && sums * (workgroups > 1024 ? workgroups : 1024) <= (512LL << 10) * 1024;
+}
+
 // Split-K shape of the MFMA shrink of n_proj add-ons: about kMatrixWaves waves in flight, a power of two
 // slices, so that a slice's workgroups (consecutive ids) meet on the same XCDs and its part of A_i in
 // their L2s (8192 wide, rank 16, 4814 rows, 8 / 11 / 16 slices: 18.6 / 19.9 / 17.4 us; the whole add-on to 4096, rank 16, 5120
@@ -191,8 +217,25 @@ bool expand_use_matrix(const sgmv_problem* p, int n_segs) {
 // wide, 700 rows, 23 / 16: 21.1 / 22.0), and from four slices on only as many as leave the partial sums of all add-ons,
 // written and read again, about half the bytes of one x, two thirds at most (11432 wide, rank 64, three add-ons of 724
 // rows, the whole call at 4 / 8 / 15 slices: 45.0 / 32.3 / 33.1 us; 3272 wide, 3254 rows, 2 / 4 / 13: 61.3 / 62.4 / 67.1).
-void choose_split_matrix(const sgmv_problem* p, int n_segs, int n_proj, bool same_x, int* ksplit, int* kslice) {
+//
+// Add-ons of long segments under SGMV_PATH_AUTO: instead as many slices as give every compute unit one workgroup and not
+// more, because the units that get a second one decide when the launch ends: 2000 rows of six segments, rank 16, 8192 wide (35
+// row blocks), whole add-on at 5 / 6 / 8 / 16 slices 25.7 / 25.1 / 27.3 / 27.5 us; 4814 rows at rank 64 (41 blocks of 128) 57.5 /
+// 56.5 / 60.0 / 59.6; three add-ons of 2600 rows at rank 32 (22 blocks) at 4 / 8 / 16 45.5 / 40.7 / 44.3.  From seven on only
+// eight or sixteen (1400 rows, rank 16, 8192 wide, 8 / 10 / 12 / 16 slices 19.0 / 20.0 / 21.4 / 20.5; three add-ons of 3440 rows,
+// rank 32, 8192 wide, 7 / 8 slices 46.1 / 40.9).  Fewer than four leave too few loads in flight (4814 rows, rank 16, 8192 wide,
+// 4 / 6 / 8 / 16 slices 52.6 / 50.4 / 48.9 / 47.6), and the rule above stays, as for five or six up to rank 16 (2625 rows, 11008 ->
+// 1024, rank 16, 5 / 16 slices 23.4 / 22.0).  Short segments whose partial sums the expand adds
+// up itself: eight, in small batches on wide inputs sixteen (60 of 8 rows, rank 16, 4096 wide, 8 / 16 slices 12.7 / 14.2; 20 of 20
+// rows, 8192 wide, 14.6 / 13.9).
+MatrixSplit choose_split_matrix(const sgmv_problem* p, int n_segs, int n_proj, bool same_x) {
   const int cap = split_cap(p->n_tokens);
+  const int most = p->h_in / 128 > 0 ? p->h_in / 128 : 1;  // keep slices of at least one chunk
+  const int limit = most < cap ? most : cap;
+  const auto within = [&](int s) {
+    while (s > limit) s = p->ksplit > 0 ? limit : s / 2;
+    return s < 1 ? 1 : s;
+  };
   int s = p->ksplit;
   if (s == 0) {
     const bool shared = same_x && shrink_shared_fits(p->r, n_proj);
@@ -202,14 +245,24 @@ void choose_split_matrix(const sgmv_problem* p, int n_segs, int n_proj, bool sam
     const long long by_partials = p->h_in / (8LL * p->r * n_proj);
     s = 1;
     while (s * 3 * waves <= 2LL * kMatrixWaves && (s < 4 || s * 3 <= 2 * by_partials)) s *= 2;
+    if (p->path != SGMV_PATH_MATRIX && p->h_out > 0) {
+      // A segment's last block is half full on average, in a sum over n segments with a deviation of 0.3 sqrt(n) blocks,
+      // twice which keeps the launch from passing the units by a few workgroups (4814 rows at rank 64, 8192 -> 28672, 43
+      // blocks: 5 / 6 slices 138 / 149 us); of a short segment's block one wave of four works
+      const bool is_long = p->n_tokens >= (long long)n_segs * rows;
+      const float last = is_long ? 0.5f * n_segs + 0.6f * sqrtf((float)n_segs) : 0.25f * n_segs;
+      const int fill = (int)(compute_units() / (((float)p->n_tokens / rows + last) * (shared ? 1 : n_proj)));
+      if (is_long && (fill >= 7 || fill == 4 || (fill > 4 && p->r >= 32)))
+        s = fill >= 14 ? 16 : fill >= 7 ? 8 : fill;
+      else if (!is_long && matrix_direct(p, n_segs, n_proj, within(8)))
+        s = fill >= 14 && p->h_in > 4096 && matrix_direct(p, n_segs, n_proj, within(16)) ? 16 : 8;
+    }
   }
-  const int most = p->h_in / 128 > 0 ? p->h_in / 128 : 1;  // keep slices of at least one chunk
-  const int limit = most < cap ? most : cap;
-  while (s > limit) s = p->ksplit > 0 ? limit : s / 2;
-  if (s < 1) s = 1;
-  const int len = ceil_div(ceil_div(p->h_in, s), 32) * 32;
-  *kslice = len;
-  *ksplit = ceil_div(p->h_in, len);
+  MatrixSplit m;
+  m.kslice = ceil_div(ceil_div(p->h_in, within(s)), 32) * 32;
+  m.ksplit = ceil_div(p->h_in, m.kslice);
+  m.direct = matrix_direct(p, n_segs, n_proj, m.ksplit);
+  return m;
 }
 
 size_t partial_bytes(int n_tokens, int r) {
@@ -658,6 +711,7 @@ struct SinglePlan {
   TileArgs tile;     // SGMV_KERNEL_TILE
   FusedArgs fused;   // SGMV_KERNEL_FUSED
   int ksplit, kslice;  // SGMV_KERNEL_MATRIX / SGMV_KERNEL_VECTOR
+  bool direct;         // SGMV_KERNEL_MATRIX: the expand adds the partial sums up itself
 };
 
 int plan_single(const sgmv_problem* p, int n_segs, SinglePlan* pl) {
@@ -724,7 +778,10 @@ int plan_single(const sgmv_problem* p, int n_segs, SinglePlan* pl) {
     if (p->path == SGMV_PATH_FUSED) return SGMV_ERR_UNSUPPORTED;
   }
   if (use_matrix(p, n_segs)) {
-    choose_split_matrix(p, n_segs, 1, false, &pl->ksplit, &pl->kslice);
+    const MatrixSplit m = choose_split_matrix(p, n_segs, 1, false);
+    pl->ksplit = m.ksplit;
+    pl->kslice = m.kslice;
+    pl->direct = m.direct;
     pl->kernel = SGMV_KERNEL_MATRIX;
     return SGMV_OK;
   }
@@ -809,7 +866,9 @@ int plan_shrink(const sgmv_problem* p, int n_segs, ShrinkPlan* pl) {
     return SGMV_OK;
   }
   if (use_matrix(p, n_segs)) {
-    choose_split_matrix(p, n_segs, 1, false, &pl->ksplit, &pl->kslice);
+    const MatrixSplit m = choose_split_matrix(&shrink_only, n_segs, 1, false);
+    pl->ksplit = m.ksplit;
+    pl->kslice = m.kslice;
     pl->kernel = SGMV_KERNEL_MATRIX;
     return SGMV_OK;
   }
@@ -1032,7 +1091,7 @@ int sgmv_expand(const sgmv_problem* p, void* y, const float* v, const void* cons
     if (launch_expand_vector(a, st) != hipSuccess) return SGMV_ERR_LAUNCH;
   } else if (have_ws && expand_use_matrix(p, n_segs)) {
     set_operands(&a, caller_scratch(p), p->n_tokens, p->r);
-    if (launch_expand_matrix(&a, 1, st) != hipSuccess) return SGMV_ERR_LAUNCH;
+    if (launch_expand_matrix(&a, 1, false, st) != hipSuccess) return SGMV_ERR_LAUNCH;
   } else {
     if (launch_expand_vector(a, st) != hipSuccess) return SGMV_ERR_LAUNCH;
   }
@@ -1113,7 +1172,7 @@ int add_lora_launch(const sgmv_problem* p, const Scratch& sc, void* y, const voi
       ExpandArgs e = make_expand(p, y, sa.partials, sa.ksplit, A_ptrs, B_ptrs, seg_starts, n_segs,
                                  layer_idx, scale);
       set_operands(&e, sc, p->n_tokens, p->r);
-      return launch_expand_matrix(&e, 1, st) == hipSuccess ? SGMV_OK : SGMV_ERR_LAUNCH;
+      return launch_expand_matrix(&e, 1, pl.direct, st) == hipSuccess ? SGMV_OK : SGMV_ERR_LAUNCH;
     }
     default: {
       ShrinkArgs sa = make_shrink(p, sc, x, A_ptrs, seg_starts, n_segs, layer_idx);
@@ -1292,7 +1351,9 @@ int sgmv_add_lora_multi(const sgmv_problem* p, int32_t n_proj, void* const* ys,
         sa.As[i] = A_ptrs[first + i];
         if (i > 0) sa.partials_of[i] = reinterpret_cast<float*>(extra + (size_t)(i - 1) * (parts + ops));
       }
-      choose_split_matrix(p, n_segs, count, sa.same_x, &sa.ksplit, &sa.kslice);
+      const MatrixSplit m = choose_split_matrix(p, n_segs, count, sa.same_x);
+      sa.ksplit = m.ksplit;
+      sa.kslice = m.kslice;
       if (launch_shrink_matrix(sa, st) != hipSuccess) return SGMV_ERR_LAUNCH;
       ExpandArgs es[kSharedShrinkMost];
       for (int i = 0; i < count; ++i) {
@@ -1302,7 +1363,7 @@ int sgmv_add_lora_multi(const sgmv_problem* p, int32_t n_proj, void* const* ys,
         if (i > 0) own.operands = extra + (size_t)(i - 1) * (parts + ops) + parts;
         set_operands(&es[i], own, p->n_tokens, p->r);
       }
-      if (launch_expand_matrix(es, count, st) != hipSuccess) return SGMV_ERR_LAUNCH;
+      if (launch_expand_matrix(es, count, m.direct, st) != hipSuccess) return SGMV_ERR_LAUNCH;
     }
     return SGMV_OK;
   }
@@ -1426,7 +1487,7 @@ int sgmv_plan_add_lora(const sgmv_problem* p, int32_t n_segs, int32_t n_proj, sg
       plan->workgroups = pl.fused.S * (int)fused_grid_items(pl.fused.by_rows ? p->n_tokens : n_segs);
       break;
     case SGMV_KERNEL_MATRIX:
-      plan->launches = 3;  // shrink, operand preparation, expand
+      plan->launches = pl.direct ? 2 : 3;  // shrink, operand preparation, expand
       plan->slices = pl.ksplit;
       break;
     default:
@@ -1437,10 +1498,13 @@ int sgmv_plan_add_lora(const sgmv_problem* p, int32_t n_segs, int32_t n_proj, sg
   }
   if (pl.kernel == SGMV_KERNEL_MATRIX && n_proj > 1 &&
       p->workspace_bytes >= sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj)) {
-    plan->launches *= ceil_div(n_proj, kSharedShrinkMost);
     // as for add-ons on one x, which a caller of several projections usually has
-    choose_split_matrix(p, n_segs, n_proj < kSharedShrinkMost ? n_proj : kSharedShrinkMost, true, &pl.ksplit, &pl.kslice);
-    plan->slices = pl.ksplit;
+    plan->launches = 0;
+    for (int first = 0; first < n_proj; first += kSharedShrinkMost) {
+      const MatrixSplit m = choose_split_matrix(p, n_segs, n_proj - first < kSharedShrinkMost ? n_proj - first : kSharedShrinkMost, true);
+      plan->launches += m.direct ? 2 : 3;
+      if (first == 0) plan->slices = m.ksplit;
+    }
   } else
     plan->launches *= n_proj;  // a multi-projection call that is not batched runs them in turn
   return SGMV_OK;

@@ -193,7 +193,8 @@ hipError_t launch_shrink_matrix(const ShrinkArgs& a, hipStream_t st);
 // Whether one pass over a common x serves n_shared add-ons, and the rows a workgroup then takes.
 bool shrink_shared_fits(int r, int n_shared);
 int shrink_stream_rows(int r, int n_shared);
-// v -> operand pairs, then y += v B_i, for n add-ons of one shape (each es[i] with its own operands).
-hipError_t launch_expand_matrix(const ExpandArgs* es, int n, hipStream_t st);
+// y += v B_i for n add-ons of one shape (each es[i] with its own operands), v's partial sums added up in the same launch
+// (direct, ranks up to 16) or made operand pairs by one in front of it.
+hipError_t launch_expand_matrix(const ExpandArgs* es, int n, bool direct, hipStream_t st);
 
 }  // namespace sgmv

@@ -174,63 +174,58 @@ static long long most_blocks(int n_tokens, int n_segs, int rows) {
 }
 static float segments_per_block(int n_segs, long long blocks) { return (float)n_segs / (float)blocks; }
 
-// Sum of the split-K parts of four consecutive k of one row (ascending order), then the two
-// 16-bit operand parts of the MFMA expand and the row's range factor: binary16 has a narrow
-// range, so for F16 a row whose largest |v| reaches 2^14 is scaled down by an exact power of
-// two and `undo` restores the fp32 result (1 otherwise).  The R / 4 lanes that hold a row are
-// consecutive lanes of a wave, and every lane of the wave calls this (live or not).
+// Binary16 has a narrow range, so a row of v whose largest |v|, amax, reaches 2^14 is scaled down by an exact power of
+// two, the result, and `undo` restores the fp32 result (both 1 otherwise).
+__device__ __forceinline__ float range_factor(float amax, float& undo) {
+  const bool large = amax >= 16384.f && amax < 3.0e38f;
+  const int e = large ? (int)((__float_as_uint(amax) >> 23) & 0xFF) - 127 - 13 : 0;  // amax * 2^-e < 2^14
+  undo = __uint_as_float((uint32_t)(127 + e) << 23);
+  return __uint_as_float((uint32_t)(127 - e) << 23);
+}
+
+// v of a row at four consecutive k as the MFMA expand's two 16-bit operand parts and, for binary16, the row's range
+// factor.  The R / 4 lanes that hold a row are consecutive lanes of a wave, and every lane of the wave calls this (live or
+// not; what a lane that is not live holds is of no consequence).
 template <class DT, int R>
-__device__ __forceinline__ void finalize_quad(const float* __restrict__ first_part, int nparts,
-                                              long long pstride, bool live, uint16_t* vh_at,
-                                              uint16_t* vl_at, float* undo_at, bool row_leader) {
+__device__ __forceinline__ void split_quad(const float4& sum, uint2& high, uint2& low, float& undo) {
   constexpr int GPR = R / 4;  // lanes per row
-  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-  auto add_parts = [&](auto pb_tag) {
-    constexpr int PB = decltype(pb_tag)::value;  // parts with their loads in flight together
-    for (int pb = 0; pb < nparts; pb += PB) {
-      float4 q[PB];
-#pragma unroll
-      for (int i = 0; i < PB; ++i)
-        q[i] = *reinterpret_cast<const float4*>(first_part + min(pb + i, nparts - 1) * pstride);
-#pragma unroll
-      for (int i = 0; i < PB; ++i) {
-        if (pb + i < nparts) {
-          sum.x += q[i].x; sum.y += q[i].y; sum.z += q[i].z; sum.w += q[i].w;
-        }
-      }
-    }
-  };
-  if (nparts <= 4)
-    add_parts(std::integral_constant<int, 4>{});
-  else if (nparts <= 8)
-    add_parts(std::integral_constant<int, 8>{});
-  else
-    add_parts(std::integral_constant<int, 16>{});
   float f[4] = {sum.x, sum.y, sum.z, sum.w};
-  float un = 1.f;
+  undo = 1.f;
   if (std::is_same<DT, F16>::value) {
     float amax = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) amax = fmaxf(amax, fabsf(f[i]));
 #pragma unroll
     for (int msk = 1; msk < GPR; msk <<= 1) amax = fmaxf(amax, __shfl_xor(amax, msk, 64));
-    if (amax >= 16384.f && amax < 3.0e38f) {
-      const int e = ((__float_as_uint(amax) >> 23) & 0xFF) - 127 - 13;  // amax * 2^-e < 2^14
-      const float down = __uint_as_float((uint32_t)(127 - e) << 23);
-      un = __uint_as_float((uint32_t)(127 + e) << 23);
+    const float down = range_factor(amax, undo);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) f[i] *= down;
-    }
+    for (int i = 0; i < 4; ++i) f[i] *= down;
   }
   uint32_t h[4], l[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) split16<DT>(f[i], h[i], l[i]);
-  if (live) {
-    *reinterpret_cast<uint2*>(vh_at) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-    *reinterpret_cast<uint2*>(vl_at) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
-    if (row_leader) *undo_at = un;
-  }
+  high = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+  low = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
 }
+
+// A lane's part of the split-K partial sums, four consecutive k, of up to N slices in flight together (load(i) gives those
+// of slice i), added up in ascending order.
+template <int N>
+struct PartialSums {
+  float4 q[N];
+  template <class Load>
+  __device__ __forceinline__ void load(int from, int slices, Load slice) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) q[i] = slice(min(from + i, slices - 1));
+  }
+  __device__ __forceinline__ void add_to(float4& sum, int from, int slices) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (from + i < slices) {
+        sum.x += q[i].x; sum.y += q[i].y; sum.z += q[i].z; sum.w += q[i].w;
+      }
+  }
+};
 
 // ---------------------------------------------------------------- shrink
 //
@@ -442,7 +437,7 @@ __global__ __launch_bounds__((64 * ShrinkShape<R, P>::kWaves), 4) void shrink_st
 
 // v[row][k] = sum over the split-K parts (ascending), written out as the two 16-bit
 // operands the expand kernel feeds to the matrix cores: vh, vl [n_tokens][R] 16-bit,
-// undo [n_tokens] fp32 (finalize_quad).  One thread handles four consecutive k of a row;
+// undo [n_tokens] fp32 (split_quad).  One thread handles four consecutive k of a row;
 // the kernel is one memory latency long.
 // blockIdx.y is the add-on.
 struct FinalizeTable {
@@ -460,9 +455,41 @@ __global__ __launch_bounds__(256) void finalize_v_kernel(int nparts, int n_token
   const bool live = item < total;
   const long long it = live ? item : total - 1;
   const long long e0 = it * 4;  // first element (row * R + k)
-  finalize_quad<DT, R>(tab.v_parts[z] + e0, nparts, (long long)n_tokens * R, live, tab.vh[z] + e0, tab.vl[z] + e0,
-                       tab.undo[z] + it / GPR, it % GPR == 0);
+  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto add_parts = [&](auto n_tag) {
+    PartialSums<decltype(n_tag)::value> parts;
+    for (int from = 0; from < nparts; from += decltype(n_tag)::value) {
+      parts.load(from, nparts, [&](int i) {
+        return *reinterpret_cast<const float4*>(tab.v_parts[z] + e0 + i * ((long long)n_tokens * R));
+      });
+      parts.add_to(sum, from, nparts);
+    }
+  };
+  if (nparts <= 4)
+    add_parts(std::integral_constant<int, 4>{});
+  else if (nparts <= 8)
+    add_parts(std::integral_constant<int, 8>{});
+  else
+    add_parts(std::integral_constant<int, 16>{});
+  uint2 high, low;
+  float undo;
+  split_quad<DT, R>(sum, high, low, undo);
+  if (live) {
+    *reinterpret_cast<uint2*>(tab.vh[z] + e0) = high;
+    *reinterpret_cast<uint2*>(tab.vl[z] + e0) = low;
+    if (it % GPR == 0) tab.undo[z][it / GPR] = undo;
+  }
 }
+
+// How the expand adds the partial sums of a block's v up itself (DIRECT, ranks up to 16): a thread has four consecutive k
+// of a row, kParts slices of them in flight together.
+template <int R>
+struct DirectShape {
+  static constexpr int kPerRow = R / 4;
+  static constexpr int kQuads = kExpandRows * kPerRow;
+  static constexpr int kParts = 8;
+  static constexpr int kPitch = R + 8;  // 16-bit elements of a row in LDS
+};
 
 // What the expand of one add-on reads and writes.
 struct ExpandTable {
@@ -472,6 +499,7 @@ struct ExpandTable {
   const float* undo[kSharedShrinkMost];
   const uint16_t* const* A_ptrs[kSharedShrinkMost];  // may be nullptr
   const uint16_t* const* B_ptrs[kSharedShrinkMost];
+  const float* v_parts[kSharedShrinkMost];  // DIRECT; else vh, vl and undo, which finalize_v_kernel made of them
 };
 
 // grid = (items, add-ons, further items); vh / vl / undo come from finalize_v_kernel.  The list of items: for a segment
@@ -519,10 +547,10 @@ __device__ __forceinline__ uint2 add4(const uint2& y, float scale, const f32x4 (
   return make_uint2(pack2<DT>(f[0], f[1]), pack2<DT>(f[2], f[3]));
 }
 
-template <class DT, int R>
+template <class DT, int R, bool DIRECT>
 __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
     const int32_t* __restrict__ seg_starts, int n_segs, float guess, int strips, int few_rows, int few_strips, int h_out,
-    long long layer_off, float scale, unsigned long long* header, ExpandTable tab) {
+    long long layer_off, float scale, unsigned long long* header, ExpandTable tab, int nparts, int n_tokens) {
   constexpr int NC = kExpandCols;        // columns of a strip
   constexpr int CT = 4;                  // 16-column tiles (and columns per lane) of a group
   constexpr int NG = NC / (16 * CT);     // column groups of the strip
@@ -530,6 +558,7 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
   constexpr bool PAIRED = R <= 16;       // the high and the low part of v side by side in one 32-deep step
   constexpr int KB = R / 8;              // blocks of eight weight rows
   constexpr int KR = R >= 64 ? 8 : R >= 32 ? 4 : 2;  // weight rows a thread transposes
+  static_assert(!DIRECT || (PAIRED && DirectShape<R>::kQuads <= 256), "a thread has at most one quad of v");
   constexpr int ITEMS = (R / KR) * (NC / 8);
   static_assert(ITEMS <= 256, "one item per thread");
   // B_i strip, transposed, as 16-byte slots {8 consecutive k of one column}, k block by k block; column c of
@@ -538,11 +567,17 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
   // of eight slots that lie in different halves of the banks
   constexpr int PITCH = 34, BLK = 8 * PITCH;
   __shared__ __align__(16) uint32_t bt[KB * BLK * 4];
+  using Direct = DirectShape<R>;
+  // the operands of the block's v, high and low part, and its rows' range factors
+  __shared__ __align__(16) uint16_t vs[2][DIRECT ? kExpandRows * Direct::kPitch : 8];
+  __shared__ float undo_s[DIRECT ? kExpandRows : 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int z = blockIdx.y;
   uint16_t* const y = tab.y[z];
+  const float* const v_parts = tab.v_parts[z];
+  const long long v_stride = (long long)n_tokens * R;  // from one part to the next
   const uint16_t *const vh = tab.vh[z], *const vl = tab.vl[z];
   const float* const undo = tab.undo[z];
   SGMV_TRACE_DECL
@@ -566,19 +601,52 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
       const __amdgpu_buffer_rsrc_t rB = make_uniform_buffer(B + layer_off, (uint32_t)((long long)R * h_out * 2));
       for (int row = it.lo; row < it.hi; row += 2) {
         const bool two = row + 1 < it.hi;
+        // lane j: v[row][j], v[row + 1][j]
+        const int vj = min(lane, R - 1), second = two ? R : 0;
+        constexpr int PB = 8;  // partial sums of a row in flight together
+        float p0[PB], p1[PB], sum0 = 0.f, sum1 = 0.f;
+        int part = 0;
+        auto load_parts = [&]() {
+#pragma unroll
+          for (int i = 0; i < PB; ++i) {
+            const float* const at = v_parts + min(part + i, nparts - 1) * v_stride + (long long)row * R + vj;
+            p0[i] = at[0];
+            p1[i] = at[second];
+          }
+        };
+        auto add_parts = [&]() {
+#pragma unroll
+          for (int i = 0; i < PB; ++i)
+            if (part + i < nparts) {
+              sum0 += p0[i];
+              sum1 += p1[i];
+            }
+        };
+        if constexpr (DIRECT) {
+          for (; part + PB < nparts; part += PB) {
+            load_parts();
+            add_parts();
+          }
+          load_parts();
+        }
         uint4 b[JC];
 #pragma unroll
         for (int j = 0; j < JC; ++j) b[j] = buffer_load128<kNonTemporal>(rB, off + (uint32_t)(j * h_out) * 2u);
         const __amdgpu_buffer_rsrc_t rY = make_uniform_buffer(y + (long long)row * h_out, (uint32_t)(two ? 2 : 1) * h_out * 2u);
         const uint4 y0 = buffer_load128<kNonTemporal>(rY, off);
         const uint4 y1 = buffer_load128<kNonTemporal>(rY, off + (uint32_t)h_out * 2u);
-        // lane j: v[row][j], v[row + 1][j]
-        const int vj = min(lane, R - 1), second = two ? R : 0;
-        const uint16_t *const h = vh + (long long)row * R + vj, *const l = vl + (long long)row * R + vj;
-        const float u0 = std::is_same<DT, F16>::value ? undo[row] : 1.f;
-        const float u1 = std::is_same<DT, F16>::value ? undo[two ? row + 1 : row] : 1.f;
-        const int v0 = __float_as_int((decode1<DT>(h[0]) + decode1<DT>(l[0])) * (scale * u0));
-        const int v1 = __float_as_int((decode1<DT>(h[second]) + decode1<DT>(l[second])) * (scale * u1));
+        int v0, v1;
+        if constexpr (DIRECT) {
+          add_parts();
+          v0 = __float_as_int(sum0 * scale);
+          v1 = __float_as_int(sum1 * scale);
+        } else {
+          const uint16_t *const h = vh + (long long)row * R + vj, *const l = vl + (long long)row * R + vj;
+          const float u0 = std::is_same<DT, F16>::value ? undo[row] : 1.f;
+          const float u1 = std::is_same<DT, F16>::value ? undo[two ? row + 1 : row] : 1.f;
+          v0 = __float_as_int((decode1<DT>(h[0]) + decode1<DT>(l[0])) * (scale * u0));
+          v1 = __float_as_int((decode1<DT>(h[second]) + decode1<DT>(l[second])) * (scale * u1));
+        }
         float s0[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, s1[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
         for (int jc = 0; jc < R; jc += JC) {
@@ -630,7 +698,28 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
 
       // ---- v: row n of the tile; rows past the segment read as zeros
       uint4 v_hi[KSTEPS], v_lo[KSTEPS];
-      {
+      float un[4];
+      // DIRECT: thread `tid` has quad `tid` of the block, whose partial sums are requested here, in front of y (the loads of
+      // a wave return in order), and added up behind y's requests
+      PartialSums<Direct::kParts> parts;
+      float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+      int part = 0;
+      const int quad_row = tid / Direct::kPerRow;
+      if constexpr (DIRECT) {
+        // rows past the segment read as zeros
+        const __amdgpu_buffer_rsrc_t rV = make_uniform_buffer(v_parts + (long long)row0 * R, (uint32_t)((nparts - 1) * v_stride + left * R) * 4u);
+        const uint32_t quad_at = tid < Direct::kQuads && quad_row < left ? (uint32_t)tid * 16u : kOutOfRange;
+        auto load_parts = [&]() {
+          parts.load(part, nparts, [&](int p) {
+            return __builtin_bit_cast(float4, buffer_load128_at(rV, quad_at, (uint32_t)(p * v_stride * 4)));
+          });
+        };
+        for (; part + Direct::kParts < nparts; part += Direct::kParts) {
+          load_parts();
+          parts.add_to(sum, part, nparts);
+        }
+        load_parts();
+      } else {
         const __amdgpu_buffer_rsrc_t rH = make_uniform_buffer(vh + (long long)r0 * R, (uint32_t)(rows * R) * 2u);
         const __amdgpu_buffer_rsrc_t rL = make_uniform_buffer(vl + (long long)r0 * R, (uint32_t)(rows * R) * 2u);
         if constexpr (PAIRED) {  // k blocks 0 .. KB - 1 the high part, KB .. 2 KB - 1 the low one
@@ -643,11 +732,30 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
             v_lo[ks] = buffer_load128(rL, (uint32_t)(n * R + ks * 32 + g * 8) * 2u);
           }
         }
-      }
-      float un[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        un[i] = std::is_same<DT, F16>::value && rows > 0 ? undo[r0 + min(4 * g + i, rows - 1)] : 1.f;
+        for (int i = 0; i < 4; ++i)
+          un[i] = std::is_same<DT, F16>::value && rows > 0 ? undo[r0 + min(4 * g + i, rows - 1)] : 1.f;
+      }
+      auto place_v = [&]() {
+        parts.add_to(sum, part, nparts);
+        uint2 high, low;
+        float factor;
+        split_quad<DT, R>(sum, high, low, factor);
+        if (tid < Direct::kQuads) {
+          const int k = tid % Direct::kPerRow * 4;
+          *reinterpret_cast<uint2*>(&vs[0][quad_row * Direct::kPitch + k]) = high;
+          *reinterpret_cast<uint2*>(&vs[1][quad_row * Direct::kPitch + k]) = low;
+          if (std::is_same<DT, F16>::value && k == 0) undo_s[quad_row] = factor;
+        }
+      };
+      auto fetch_v = [&]() {
+        const int row = (tile * 16 + n) * Direct::kPitch;
+        const uint4 none = make_uint4(0, 0, 0, 0);
+        v_hi[0] = g < 2 * KB ? *reinterpret_cast<const uint4*>(&vs[g < KB ? 0 : 1][row + g % KB * 8]) : none;
+        v_lo[0] = none;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) un[i] = std::is_same<DT, F16>::value ? undo_s[tile * 16 + 4 * g + i] : 1.f;
+      };
 
       // FULL: every column of the strip is inside h_out.  GROUPS: the most column groups this wave takes, so that
       // only their part of y is loaded and held.  (Loads from an empty buffer for the groups that other waves take cost
@@ -694,8 +802,13 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
               *at = d[0];
           }
         }
+        if constexpr (DIRECT) {
+          __builtin_amdgcn_sched_barrier(0);  // the strip's registers are free by now
+          place_v();
+        }
         SGMV_TRACE_POINT(1);
         lds_barrier();  // LDS only: the loads of y stay in flight
+        if constexpr (DIRECT) fetch_v();
         SGMV_TRACE_POINT(2);
 
         // second operands: column 64 (group0 + j) + 4 n + t of the strip
@@ -819,15 +932,15 @@ hipError_t launch_shrink_matrix(const ShrinkArgs& a, hipStream_t st) {
   return a.bf16 ? launch_shrink_matrix_r<BF16>(a, st) : launch_shrink_matrix_r<F16>(a, st);
 }
 
-// v -> operand pairs of n add-ons, then their expands, each in one launch.
+// The expands of n add-ons in one launch, in front of it the one that makes operand pairs of their v.
 template <class DT, int R>
-static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, hipStream_t st) {
+static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, bool direct, hipStream_t st) {
   const ExpandArgs& a = es[0];
   FinalizeTable fin;
   ExpandTable tab;
   for (int i = 0; i < kSharedShrinkMost; ++i) {
     const ExpandArgs& e = es[i < n ? i : 0];
-    fin.v_parts[i] = e.v_parts;
+    tab.v_parts[i] = fin.v_parts[i] = e.v_parts;
     tab.vh[i] = fin.vh[i] = e.vh;
     tab.vl[i] = fin.vl[i] = e.vl;
     tab.undo[i] = fin.undo[i] = e.undo;
@@ -835,11 +948,13 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, hipStream_
     tab.A_ptrs[i] = (const uint16_t* const*)e.A_ptrs;
     tab.B_ptrs[i] = (const uint16_t* const*)e.B_ptrs;
   }
-  const long long quads = (long long)a.n_tokens * (R / 4);
-  hipLaunchKernelGGL((finalize_v_kernel<DT, R>), dim3((unsigned)((quads + 255) / 256), (unsigned)n), dim3(256), 0, st, a.nparts,
-                     a.n_tokens, fin);
-  const hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
+  if (!direct) {
+    const long long quads = (long long)a.n_tokens * (R / 4);
+    hipLaunchKernelGGL((finalize_v_kernel<DT, R>), dim3((unsigned)((quads + 255) / 256), (unsigned)n), dim3(256), 0, st, a.nparts,
+                       a.n_tokens, fin);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
   const int strips = (a.h_out + kExpandCols - 1) / kExpandCols;
   // Strip items only where there can be enough of them: each walks its R weight rows in R / 8 batches of loads, one
   // after the other, so the higher the rank, the more of the chip they have to fill to be ahead of the blocks, which
@@ -854,25 +969,35 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, hipStream_
   const long long wgs = strips * blocks;
   const dim3 grid((unsigned)(wgs < kMostWorkgroups ? wgs : kMostWorkgroups), (unsigned)n,
                   (unsigned)((wgs + kMostWorkgroups - 1) / kMostWorkgroups));
-  hipLaunchKernelGGL((expand_matrix_kernel<DT, R>), grid, dim3(256), 0, st, a.seg_starts, a.n_segs,
-                     segments_per_block(a.n_segs, blocks), strips, few_rows, few, a.h_out, a.layer_off, a.scale, a.header, tab);
+  const auto launch = [&](auto direct_tag) {
+    hipLaunchKernelGGL((expand_matrix_kernel<DT, R, decltype(direct_tag)::value>), grid, dim3(256), 0, st, a.seg_starts, a.n_segs,
+                       segments_per_block(a.n_segs, blocks), strips, few_rows, few, a.h_out, a.layer_off, a.scale, a.header,
+                       tab, a.nparts, a.n_tokens);
+  };
+  if constexpr (R <= 16) {
+    if (direct) {
+      launch(std::true_type{});
+      return hipGetLastError();
+    }
+  }
+  launch(std::false_type{});
   return hipGetLastError();
 }
 
 template <class DT>
-static hipError_t launch_expand_matrix_r(const ExpandArgs* es, int n, hipStream_t st) {
+static hipError_t launch_expand_matrix_r(const ExpandArgs* es, int n, bool direct, hipStream_t st) {
   switch (es[0].r) {
-    case 8: return launch_expand_matrix_t<DT, 8>(es, n, st);
-    case 16: return launch_expand_matrix_t<DT, 16>(es, n, st);
-    case 32: return launch_expand_matrix_t<DT, 32>(es, n, st);
-    case 64: return launch_expand_matrix_t<DT, 64>(es, n, st);
+    case 8: return launch_expand_matrix_t<DT, 8>(es, n, direct, st);
+    case 16: return launch_expand_matrix_t<DT, 16>(es, n, direct, st);
+    case 32: return launch_expand_matrix_t<DT, 32>(es, n, direct, st);
+    case 64: return launch_expand_matrix_t<DT, 64>(es, n, direct, st);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_expand_matrix(const ExpandArgs* es, int n, hipStream_t st) {
-  if (n < 1 || n > kSharedShrinkMost) return hipErrorInvalidValue;
-  return es[0].bf16 ? launch_expand_matrix_r<BF16>(es, n, st) : launch_expand_matrix_r<F16>(es, n, st);
+hipError_t launch_expand_matrix(const ExpandArgs* es, int n, bool direct, hipStream_t st) {
+  if (n < 1 || n > kSharedShrinkMost || (direct && es[0].r > 16)) return hipErrorInvalidValue;
+  return es[0].bf16 ? launch_expand_matrix_r<BF16>(es, n, direct, st) : launch_expand_matrix_r<F16>(es, n, direct, st);
 }
 
 }  // namespace sgmv

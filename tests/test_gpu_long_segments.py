@@ -39,6 +39,34 @@ def test_every_edge_of_the_work_lists(dtype, r, P, same_x, h_in, h_out):
         assert_parity(got[k], oracle.run_workload(w, layer_idx=1, n_threads=8), dtype, f"add-on {k} of {P}")
 
 
+# The same where the expand adds the partial sums up itself: one slice, as many as it requests at a time (eight), one more,
+# twice as many; binary16 with rows of v on both sides of the range factor.
+@pytest.mark.parametrize("dtype,r,P,h_in,h_out,slices,large", [
+    ("bf16", 8, 1, 136, 264, 1, False), ("f16", 16, 1, 1152, 2056, 8, True), ("bf16", 16, 3, 1152, 264, 9, False),
+    ("f16", 8, 2, 2048, 520, 16, True), ("bf16", 16, 1, 2048, 256, 16, False)])
+def test_expand_that_adds_the_partial_sums_up(dtype, r, P, h_in, h_out, slices, large):
+    from paper_2310_18547_amd import binding as B
+    n = len(LENS)
+    scale = 2.0 ** -13 if large else 0.5
+    ws = [wl.custom(LENS, h_in, h_out, r, dtype, seed=950 + r + k, num_layers=2, scale=scale,
+                    seg_adapter=[-1 if k == P - 1 and i in (6, 11, n - 1) else i for i in range(n)]) for k in range(P)]
+    if large:  # |v| about 2^13 in every other row, the largest of a row on both sides of 2^14
+        x = decode64(ws[0].x, dtype) * np.where(np.arange(ws[0].n_tokens) % 2, 2.0 ** 13, 1.0)[:, None]
+        ws[0].x[...] = wl.encode(x.astype(np.float32), dtype)
+    for w in ws[1:]:
+        w.x[...] = ws[0].x
+    ds = [_dev(w, n_proj=P, ksplit=slices) for w in ws]
+    plan = B.sgmv_plan_add_lora(ds[0].problem, n, P)
+    assert (plan.kernel, plan.launches) == (B.KERNEL_MATRIX, 2)
+    if P == 1:
+        ds[0].add_lora(1)
+    else:
+        B.sgmv_add_lora_multi(ds[0].problem, [d.y[0] for d in ds], [ds[0].x[0]] * P, [d.A_ptrs for d in ds],
+                              [d.B_ptrs for d in ds], ds[0].seg_starts, n, 1, scale)
+    for k, w in enumerate(ws):
+        assert_parity(ds[k].y_bits(), oracle.run_workload(w, layer_idx=1, n_threads=8), dtype, f"add-on {k} of {P}")
+
+
 # Every kernel that stores y, by path and segment lengths: with one term per sum the fp32 result is exact, so that y is
 # its rounding to nearest even, bit for bit (the operands lie within a factor of four: many ties).
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
