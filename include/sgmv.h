@@ -152,7 +152,8 @@ typedef struct sgmv_problem {
 typedef enum {
   SGMV_KERNEL_NONE = 0,             /* nothing to launch (no segments or no rows)          */
   SGMV_KERNEL_FUSED = 1,            /* single launch, vector ALUs: a set of workgroups per */
-                                    /* one-row segment, or per row of a small batch        */
+                                    /* one-row segment, or per row (wide inputs: per two   */
+                                    /* rows of a segment) of a small batch                 */
   SGMV_KERNEL_TILE = 2,             /* single launch, sixteen-row MFMA tiles               */
   SGMV_KERNEL_MULTI_SIDE = 3,       /* several projections side by side in one launch      */
   SGMV_KERNEL_MULTI_PIPELINED = 4,  /* several projections walked by every workgroup       */

@@ -94,7 +94,6 @@ constexpr int kMatrixMinSegLen = 6;
 // 18.8; the Uniform mix of 64 rows, 42 segments: 20.7 against 20.9, of 256 rows, 63 segments of up to 8:
 // 23.8 against 39.5).
 constexpr int kMatrixFewSegments = 48;
-
 constexpr int kMatrixWaves = 4096;     // waves the MFMA shrink aims for (four per SIMD)
 
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -331,7 +330,9 @@ int fused_round_trips(const sgmv_problem* p, int s, bool single_add_on) {
 bool choose_fused(const sgmv_problem* p, int n_segs, FusedArgs* f, bool single_add_on = true, bool by_rows = false) {
   if (!p->workspace_ready) return false;
   const Limits lim = limits();
+  f->items = n_segs;
   f->by_rows = by_rows;
+  f->paired = false;
   if (p->max_seg_len != 1 && !by_rows) return false;  // one row per segment; longer ones go to the tile kernel
   if (n_segs > kFusedMaxWorkgroups) return false;
   const int cap = split_cap(p->n_tokens);
@@ -655,6 +656,46 @@ ExpandArgs make_expand(const sgmv_problem* p, void* y, const float* v_parts, int
   return a;
 }
 
+// A per-row launch whose items are pairs of rows of one segment, which then read the segment's weights once.  Only where
+// a launch of an item per row is out, being too many workgroups (wide inputs, whose slices are many): where it applies it
+// is ahead although it reads more, the second row's arithmetic and the empty places costing 0.3 to 1 us (45 rows of 18
+// segments, 5120 wide, rank 32, bfloat16 8.1 / 8.5 us per row / per pair; 64 rows of 42, 4096 wide, rank 16 5.5 / 6.4).
+// Fewer than four slices leave a workgroup too much (120 rows of 15 segments, 5120 wide, rank 32, three slices 11.0 with the
+// tile kernel / 12.7).
+bool choose_fused_pairs(const sgmv_problem* p, int n_segs, FusedArgs* f) {
+  if (p->path != SGMV_PATH_AUTO || p->n_tokens <= 64 || p->r > 32 || n_segs > p->n_tokens) return false;
+  if (!choose_fused(p, pair_places(p->n_tokens, n_segs), f, true, true) || f->S < 4) return false;
+  f->paired = true;
+  return true;
+}
+
+// The add-on in such a launch (`tile_slices`: of the tile kernel, 0 where it does not apply).  Measured, us, what was taken
+// before / pairs: 11008 -> 4096, rank 8, 128 rows: Uniform 15.5 / 10.0, Skewed 11.3 / 9.0, 64 x 2 rows 12.0 / 9.0; 13824 -> 5120, rank
+// 8, 16 x 8 rows 9.6 / 7.1; rank 16, Skewed of 120 rows 14.0 / 12.8, 9992 -> 3000, 64 x 2 rows 14.4 / 11.9; 8192 -> 8192, rank 8, Skewed of
+// 256 rows 13.0 / 11.5; rank 32: 5120 -> 5120, Skewed of 96 rows 14.2 / 12.0, 6144 -> 4096 15.4 / 10.1, 8192 -> 8192 16.5 / 14.0.
+// Left to the others:
+//  * from rank 16 on where the tile kernel has six slices or more (12000 -> 1024, rank 16, 33 x 3 rows 10.0 / 13.0; 9992 ->
+//    3000, 6 x 20 rows 8.9 / 11.4), at rank 8 six or seven (128 rows of 42 segments 8.9 / 9.7; eight 9.6 / 7.1, above);
+//  * from rank 16 on more than 128 rows (8192 -> 8192, rank 16, Skewed of 256 rows 14.5 / 18.4);
+//  * a column slice a workgroup takes several passes or single lanes for (11008 -> 11008, rank 16, Skewed of 128 rows 13.9 / 18.7;
+//    8192 -> 28672, rank 8, 12 x 20 rows 16.0 / 21.9, rank 32, Skewed of 66 rows 19.9 / 25.7);
+//  * at rank 32 more than a workgroup per unit (11008 -> 4096, Skewed of 128 rows 16.8 / 17.3).
+bool choose_add_on_pairs(const sgmv_problem* p, int n_segs, int tile_slices, FusedArgs* f) {
+  if (p->r == 8 ? tile_slices == 6 || tile_slices == 7 : tile_slices >= 6 || p->n_tokens > 128) return false;
+  return choose_fused_pairs(p, n_segs, f) && f->cslice <= (p->r == 16 ? 1024 : 2048) &&
+         (p->r < 32 || (long long)f->S * f->items <= limits().fused_workgroups);
+}
+
+// The stand-alone shrink: rank 8, 13824 wide, Uniform of 128 rows 15.4 / 7.2, 11008 wide, 16 x 8 rows 10.5 / 5.3; rank 16, 13824 wide,
+// 64 x 2 rows 12.3 / 9.9, 9992 wide, Skewed of 256 rows, five slices, 12.5 / 10.1.  With four slices the workgroup per row without
+// Split-K is ahead on most batches (7168 wide, rank 16, Uniform of 256 rows 8.4 / 10.1), and at rank 32 pairs gain for sure only
+// on many short segments (11008 wide, Uniform of 120 rows 21.2 / 13.2, 9992 wide, 64 x 2 rows 14.9 / 12.0; 33 x 3 rows 11.4 /
+// 11.9; against the MFMA kernels 128 rows of 6 segments, 12000 wide, 7.9 / 9.1).
+bool choose_shrink_pairs(const sgmv_problem* p, int n_segs, FusedArgs* f) {
+  if (!choose_fused_pairs(p, n_segs, f) || f->S < 5) return false;
+  return p->r < 32 || (f->S >= kFusedSlices && !use_matrix(p, n_segs) && 2LL * p->n_tokens <= 5LL * n_segs);
+}
+
 // Small batches of segments longer than a row (or of unknown length): whether AUTO runs the
 // one-row kernel with the hand-off per ROW of the batch (SGMV_PATH_ROWS), every row's workgroups
 // reading the row's adapter through the caches, rather than the tile kernel (`tile`: it applies, with
@@ -714,7 +755,8 @@ struct SinglePlan {
   bool direct;         // SGMV_KERNEL_MATRIX: the expand adds the partial sums up itself
 };
 
-int plan_single(const sgmv_problem* p, int n_segs, SinglePlan* pl) {
+// pairs: whether rows may be taken two to an item (choose_add_on_pairs).
+int plan_single(const sgmv_problem* p, int n_segs, SinglePlan* pl, bool pairs = true) {
   if (p->path == SGMV_PATH_WHOLE) {
     if (!choose_whole(p, n_segs, &pl->whole)) return SGMV_ERR_UNSUPPORTED;
     pl->kernel = SGMV_KERNEL_WHOLE;
@@ -733,7 +775,8 @@ int plan_single(const sgmv_problem* p, int n_segs, SinglePlan* pl) {
       pl->kernel = SGMV_KERNEL_WHOLE;
       return SGMV_OK;
     }
-    if (choose_fused(p, p->n_tokens, &pl->fused, true, true)) {
+    if (choose_fused(p, p->n_tokens, &pl->fused, true, true) ||
+        (pairs && choose_add_on_pairs(p, n_segs, tile ? pl->tile.S : 0, &pl->fused))) {
       pl->kernel = SGMV_KERNEL_FUSED;
       return SGMV_OK;
     }
@@ -845,7 +888,8 @@ int plan_shrink(const sgmv_problem* p, int n_segs, ShrinkPlan* pl) {
   // 1024 rows 8.2 against 7.8; rank 8, Uniform of 64 rows 2.9 against 4.0; rank 32, where A_i is
   // 256 KB: 64 rows 6.6 against 5.5, 256 rows 7.2 against 9.3)
   const bool fused_rows = p->path == SGMV_PATH_AUTO && rows_apply(p, n_segs, false, 0) &&
-                          choose_fused(&shrink_only, p->n_tokens, &pl->fused, true, true);
+                          (choose_fused(&shrink_only, p->n_tokens, &pl->fused, true, true) ||
+                           choose_shrink_pairs(&shrink_only, n_segs, &pl->fused));
   {
     const bool small = a_elems <= 32768 || (a_elems <= 65536 && a_elems % (16 * 256 * 8) == 0 &&
                                             (p->dtype == SGMV_F16 || p->n_tokens >= 96));
@@ -1331,8 +1375,10 @@ int sgmv_add_lora_multi(const sgmv_problem* p, int32_t n_proj, void* const* ys,
   // Long segments on the MFMA kernels: up to three add-ons per launch of each kernel (one pass over x
   // where they read the same one).  Needs the larger workspace of sgmv_workspace_bytes_multi for the
   // partial sums and operands of the second and third add-on.
+  // (Where a single add-on would take two rows to an item of the hand-off kernel, these launches together are ahead: two of
+  // 250 rows of 37 adapters, 8192 wide, rank 16, 20.2 us against 35.9; three of 120 rows of 22, 13824 wide, rank 32, 37.7 / 66.1.)
   SinglePlan pl;
-  if (n_proj >= 2 && plan_single(p, n_segs, &pl) == SGMV_OK && pl.kernel == SGMV_KERNEL_MATRIX &&
+  if (n_proj >= 2 && plan_single(p, n_segs, &pl, false) == SGMV_OK && pl.kernel == SGMV_KERNEL_MATRIX &&
       p->workspace_bytes >= sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj)) {
     const Scratch sc = caller_scratch(p);
     // the first add-on's partial sums and operands where a single call keeps them, the others' behind the
@@ -1397,7 +1443,7 @@ int sgmv_plan_shrink(const sgmv_problem* p, int32_t n_segs, sgmv_plan* plan) {
   } else if (pl.kernel == SGMV_KERNEL_FUSED) {
     plan->launches = 1;
     plan->slices = pl.fused.S;
-    plan->workgroups = pl.fused.S * (int)fused_grid_items(pl.fused.by_rows ? p->n_tokens : n_segs);
+    plan->workgroups = pl.fused.S * (int)fused_grid_items(pl.fused.items);
   } else {
     plan->launches = 2;
     plan->slices = pl.ksplit;
@@ -1460,12 +1506,15 @@ int sgmv_plan_add_lora(const sgmv_problem* p, int32_t n_segs, int32_t n_proj, sg
       plan->kernel = kernel;
       plan->launches = 1;
       plan->slices = f.S;
-      plan->workgroups = f.S * (int)fused_grid_items(f.by_rows ? p->n_tokens : n_segs) * (kernel == SGMV_KERNEL_MULTI_SIDE ? n_proj : 1);
+      plan->workgroups = f.S * (int)fused_grid_items(f.items) * (kernel == SGMV_KERNEL_MULTI_SIDE ? n_proj : 1);
       return SGMV_OK;
     }
   }
   SinglePlan pl;
-  rc = plan_single(p, n_segs, &pl);
+  rc = plan_single(p, n_segs, &pl, n_proj < 2);
+  if (rc == SGMV_OK && n_proj >= 2 &&
+      (pl.kernel != SGMV_KERNEL_MATRIX || p->workspace_bytes < sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj)))
+    rc = plan_single(p, n_segs, &pl);  // one after the other
   if (rc != SGMV_OK) return rc;
   plan->kernel = pl.kernel;
   switch (pl.kernel) {
@@ -1484,7 +1533,7 @@ int sgmv_plan_add_lora(const sgmv_problem* p, int32_t n_segs, int32_t n_proj, sg
     case SGMV_KERNEL_FUSED:
       plan->launches = 1;
       plan->slices = pl.fused.S;
-      plan->workgroups = pl.fused.S * (int)fused_grid_items(pl.fused.by_rows ? p->n_tokens : n_segs);
+      plan->workgroups = pl.fused.S * (int)fused_grid_items(pl.fused.items);
       break;
     case SGMV_KERNEL_MATRIX:
       plan->launches = pl.direct ? 2 : 3;  // shrink, operand preparation, expand

@@ -5,6 +5,8 @@
 
 #include <type_traits>
 
+#include "launch.h"
+
 namespace sgmv {
 
 struct F16 {};
@@ -217,8 +219,14 @@ __device__ __forceinline__ void buffer_store128(__amdgpu_buffer_rsrc_t rsrc, uin
 // rows of the batch, each looking its segment up (kPerRow); and whether the weights are read past the
 // caches (non-temporal, kStreamed), which pays where a launch reads many of them once (launch.h,
 // stream_weights); and whether more than one workgroup per compute unit has to be resident (kCrowded).
-constexpr int kPerSegment = 0, kPerRow = 1, kStreamed = 2, kCrowded = 4;
+// kPaired, with kPerRow: two rows of one segment to an item (launch.h, pair_rows).
+constexpr int kPerSegment = 0, kPerRow = 1, kStreamed = 2, kCrowded = 4, kPaired = 8;
 constexpr bool by_row(int mode) { return (mode & kPerRow) != 0; }
+constexpr bool paired(int mode) { return (mode & kPaired) != 0; }
+constexpr int rows_of_item(int mode) { return paired(mode) ? 2 : 1; }
+__device__ __forceinline__ int items_of_grid(int mode, int n_tokens, int n_segs) {
+  return paired(mode) ? pair_places(n_tokens, n_segs) : by_row(mode) ? n_tokens : n_segs;
+}
 constexpr int weights_aux(int mode) { return (mode & kStreamed) != 0 ? kNonTemporal : 0; }
 
 // Per-row launches: the segment that holds row `row`, i.e. the number of segment ends at or
@@ -233,6 +241,38 @@ __device__ __forceinline__ int segment_of_row(const int32_t* __restrict__ seg_st
     found += __popcll(__ballot(end <= row));
   }
   return __builtin_amdgcn_readfirstlane(found);
+}
+
+// The segment and the rows [lo, hi) of an item of a per-row launch (kPerRow); lo = hi where there are none: behind the last
+// segment end, or a place of a paired launch that stays empty.  With kPaired segment i's pairs have the places from
+// (seg_starts[i] + i) / 2 on: at least as many as it has pairs up to the next segment's first, with no sum over the segments
+// before it.
+struct RowItem {
+  int seg, lo, hi;
+};
+template <int MODE>
+__device__ __forceinline__ RowItem find_rows(const int32_t* __restrict__ seg_starts, int n_segs, int n_tokens, int item, int lane) {
+  if constexpr (!paired(MODE)) {
+    const int seg = segment_of_row(seg_starts, n_segs, item, lane);
+    return RowItem{seg, item, seg < n_segs ? item + 1 : item};
+  } else {
+    // the segment's ends come out of the lanes that looked at them: no load waits for the look-up but those of its pointers
+    int found = 0, start = 0, end = 0;
+    for (int base = 0; base < n_segs; base += 64) {
+      const int i = base + lane;
+      const int mine = seg_starts[min(i, n_segs - 1) + 1];
+      const int next = i < n_segs ? (mine + i + 1) >> 1 : 0x7fffffff;  // the first place behind segment i's
+      const int passed = __popcll(__ballot(next <= item));
+      if (passed > 0) start = __builtin_amdgcn_readlane(mine, passed - 1);
+      found += passed;
+      if (passed < 64) {
+        end = __builtin_amdgcn_readlane(mine, passed);
+        break;
+      }
+    }
+    const int lo = start + 2 * (item - ((start + found) >> 1));
+    return RowItem{found, lo, found < n_segs ? min(lo + 2, min(end, n_tokens)) : lo};
+  }
 }
 
 // Workgroup barrier that orders LDS traffic only: outstanding global loads stay

@@ -54,9 +54,10 @@ namespace sgmv {
 //   header the workspace's generation copies, then the error flag
 // G  = lane groups of the expand phase: group g multiplies weight rows
 //      g*R/G .. (g+1)*R/G-1; the groups are summed through LDS.
-// RB = rows handled per pass over the weights (1 when every segment is one row).
-// MODE with kPerRow: `seg` is a row of the batch, not a segment: the workgroup serves that one row and
-//      looks its segment up in seg_starts (n_segs of them).
+// RB = rows handled per pass over the weights: 1, or 2 with kPaired.  What a pair's missing second row gives is computed
+//      and not stored, so that the inner loops have no branch.
+// MODE with kPerRow: `seg` is a row of the batch (kPaired: the place of a pair of rows), not a segment: the workgroup
+//      serves that one row (pair) and looks its segment up in seg_starts (n_segs of them).
 template <class DT, int R, int G, int RB, int MODE = kPerSegment>
 __device__ __forceinline__ void add_lora_fused_body(
     const int32_t* __restrict__ seg_starts, const uint16_t* const* __restrict__ A_ptrs,
@@ -90,11 +91,11 @@ __device__ __forceinline__ void add_lora_fused_body(
   int lo, hi;
   const uint16_t *A, *B;
   if constexpr (by_row(MODE)) {
-    const int found = segment_of_row(seg_starts, n_segs, seg, lane);
-    lo = seg;
-    hi = found < n_segs ? seg + 1 : seg;  // a row behind the last segment end: nothing to do
-    A = found < n_segs ? A_ptrs[found] : nullptr;
-    B = found < n_segs ? B_ptrs[found] : nullptr;
+    const RowItem it = find_rows<MODE>(seg_starts, n_segs, n_tokens, seg, lane);
+    lo = it.lo;
+    hi = it.hi;
+    A = it.seg < n_segs ? A_ptrs[it.seg] : nullptr;
+    B = it.seg < n_segs ? B_ptrs[it.seg] : nullptr;
   } else {
     lo = seg_starts[seg];
     hi = seg_starts[seg + 1];
@@ -248,11 +249,12 @@ __device__ __forceinline__ void add_lora_fused_body(
       for (int u = 0; u < U; ++u) {
         const int q = base + u * NT + tid;
         const int kk = (q / LPR) & (kMaxKSlice - 1);
+        if constexpr (RB > 1) asm volatile("" : "+v"(a[u].x), "+v"(a[u].y), "+v"(a[u].z), "+v"(a[u].w), "+v"(acc[RB - 1][7]));
         float af[8];
         unpack8<DT>(a[u], af);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-          if (RB == 1 || rb < nrows) {
+          if (RB <= 2 || rb < nrows) {
             const float xraw = decode1<DT>(xs[rb][kk]);
             const float xv = (q < nchunks) ? xraw : 0.f;
 #pragma unroll
@@ -266,7 +268,7 @@ __device__ __forceinline__ void add_lora_fused_body(
     // in LDS, and the exchange wave adds the sixteen rows of the workgroup in a fixed order.
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      if (RB == 1 || rb < nrows) {
+      if (RB <= 2 || rb < nrows) {
         float d[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) d[e] = row_sum_same_group<LPR>(acc[rb][e]);
@@ -314,11 +316,13 @@ __device__ __forceinline__ void add_lora_fused_body(
         for (int e = 0; e < 8; ++e) acc[rb][e] = 0.f;
 #pragma unroll
       for (int j = 0; j < JL; ++j) {
+        // weight row after weight row: the compiler would widen all of them to fp32 first (252 registers at rank 32)
+        if constexpr (RB > 1) asm volatile("" : "+v"(b[j].x), "+v"(b[j].y), "+v"(b[j].z), "+v"(b[j].w), "+v"(acc[RB - 1][7]));
         float bf[8];
         unpack8<DT>(b[j], bf);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-          if (RB == 1 || rb < nrows) {
+          if (RB <= 2 || rb < nrows) {
             const float vj = vs[rb][cg * JL + j];
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[rb][e] = fmaf(vj, bf[e], acc[rb][e]);
@@ -336,7 +340,7 @@ __device__ __forceinline__ void add_lora_fused_body(
         if (cg > 0) {
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb) {
-            if (RB == 1 || rb < nrows) {
+            if (RB <= 2 || rb < nrows) {
               float* dst = &ex[(((cg - 1) * RB + rb) * CPW + cc) * 8];
               *reinterpret_cast<float4*>(dst) = make_float4(acc[rb][0], acc[rb][1], acc[rb][2], acc[rb][3]);
               *reinterpret_cast<float4*>(dst + 4) = make_float4(acc[rb][4], acc[rb][5], acc[rb][6], acc[rb][7]);
@@ -349,7 +353,7 @@ __device__ __forceinline__ void add_lora_fused_body(
           for (int g = 1; g < G; ++g) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-              if (RB == 1 || rb < nrows) {
+              if (RB <= 2 || rb < nrows) {
                 const float* srcp = &ex[(((g - 1) * RB + rb) * CPW + cc) * 8];
                 const float4 p0 = *reinterpret_cast<const float4*>(srcp);
                 const float4 p1 = *reinterpret_cast<const float4*>(srcp + 4);
@@ -393,7 +397,7 @@ constexpr int kUncrowded = 256;
 constexpr int fused_waves(int mode) { return (mode & kCrowded) != 0 ? 4 : 1; }
 
 // One add-on per launch.
-template <class DT, int R, int G, int RB, int MODE>
+template <class DT, int R, int G, int MODE>
 __global__ __launch_bounds__(320, fused_waves(MODE)) void add_lora_fused_kernel(
     // the first sixteen dwords are preloaded into SGPRs at wave launch: keep what the
     // first dependent loads need at the front
@@ -409,13 +413,13 @@ __global__ __launch_bounds__(320, fused_waves(MODE)) void add_lora_fused_kernel(
   // in their XCD's L2 (dealt round the XCDs, eight-row segments were read by all eight of them:
   // 16 segments of 8 rows 8.8 us)
   const int seg = by_row(MODE) ? blockIdx.x * gridDim.z + blockIdx.z : blockIdx.z * gridDim.x + blockIdx.x;
-  if (seg >= (by_row(MODE) ? n_tokens : n_segs)) {  // the grid is padded to whole rows of segments
+  if (seg >= items_of_grid(MODE, n_tokens, n_segs)) {  // the grid is padded to whole rows of segments
     if (threadIdx.x < 64) leave_launch_idle(header, (int)(gridDim.x * gridDim.y * gridDim.z), (int)threadIdx.x);
     return;
   }
-  add_lora_fused_body<DT, R, G, RB, MODE>(seg_starts, A_ptrs, B_ptrs, x, y, kslice, cslice, h_in, h_out,
-                                            n_tokens, S, offA, offB, exch, header, scale, spin_limit, seg,
-                                            (int)blockIdx.y, n_segs);
+  add_lora_fused_body<DT, R, G, rows_of_item(MODE), MODE>(seg_starts, A_ptrs, B_ptrs, x, y, kslice, cslice, h_in, h_out,
+                                                          n_tokens, S, offA, offB, exch, header, scale, spin_limit, seg,
+                                                          (int)blockIdx.y, n_segs);
 }
 
 // Several independent add-ons of one shape per launch, side by side: blockIdx.z selects
@@ -432,7 +436,7 @@ __global__ __launch_bounds__(320, fused_waves(MODE)) void add_lora_fused_side_ke
   const int z = (int)blockIdx.z - row * n_proj;
   // MODE with kPerRow: items are rows of the batch, an XCD (blockIdx.x) taking a run of consecutive rows
   const int seg = by_row(MODE) ? blockIdx.x * ((int)gridDim.z / n_proj) + row : row * gridDim.x + blockIdx.x;
-  if (seg >= (by_row(MODE) ? n_tokens : n_segs)) {  // the grid is padded to whole rows of segments
+  if (seg >= items_of_grid(MODE, n_tokens, n_segs)) {  // the grid is padded to whole rows of segments
     if (threadIdx.x < 64) leave_launch_idle(header, (int)(gridDim.x * gridDim.y * gridDim.z), (int)threadIdx.x);
     return;
   }
@@ -466,12 +470,11 @@ hipError_t launch_workspace_init(void* p, size_t bytes, size_t header_offset, hi
   return hipGetLastError();
 }
 
-template <class DT, int R, int G, int RB, int MODE>
+template <class DT, int R, int G, int MODE>
 static hipError_t launch_fused_t(const FusedArgs& a, hipStream_t st) {
-  const int items = by_row(MODE) ? a.n_tokens : a.n_segs;
-  hipLaunchKernelGGL((add_lora_fused_kernel<DT, R, G, RB, MODE>),
-                     dim3((unsigned)fused_grid_x(items), (unsigned)a.S,
-                          (unsigned)((items + fused_grid_x(items) - 1) / fused_grid_x(items))),
+  hipLaunchKernelGGL((add_lora_fused_kernel<DT, R, G, MODE>),
+                     dim3((unsigned)fused_grid_x(a.items), (unsigned)a.S,
+                          (unsigned)((a.items + fused_grid_x(a.items) - 1) / fused_grid_x(a.items))),
                      dim3(320), 0, st, a.seg_starts, (const uint16_t* const*)a.A_ptrs,
                      (const uint16_t* const*)a.B_ptrs, (const uint16_t*)a.x, (uint16_t*)a.y,
                      a.kslice, a.cslice, a.h_in, a.h_out, a.n_tokens, a.S, a.offA, a.offB, a.exch,
@@ -481,10 +484,9 @@ static hipError_t launch_fused_t(const FusedArgs& a, hipStream_t st) {
 
 template <class DT, int R, int G, int MODE>
 static hipError_t launch_fused_side_t(const FusedArgs& a, hipStream_t st) {
-  const int items = by_row(MODE) ? a.n_tokens : a.n_segs;
   hipLaunchKernelGGL((add_lora_fused_side_kernel<DT, R, G, MODE>),
-                     dim3((unsigned)fused_grid_x(items), (unsigned)a.S,
-                          (unsigned)(fused_grid_items(items) / fused_grid_x(items) * a.n_proj)),
+                     dim3((unsigned)fused_grid_x(a.items), (unsigned)a.S,
+                          (unsigned)(fused_grid_items(a.items) / fused_grid_x(a.items) * a.n_proj)),
                      dim3(320), 0, st, a.seg_starts, a.kslice, a.cslice, a.h_in, a.h_out, a.n_tokens, a.S,
                      a.offA, a.offB, a.exch, a.header, a.scale, a.spin_limit, a.n_segs, a.n_proj, a.table);
   return hipGetLastError();
@@ -493,21 +495,27 @@ static hipError_t launch_fused_side_t(const FusedArgs& a, hipStream_t st) {
 template <class DT, int R, int G, int MODE>
 static hipError_t launch_fused_rows(const FusedArgs& a, hipStream_t st) {
   if constexpr (R == 32 && G == 2 && (MODE & kCrowded) == 0) {
-    if ((long long)a.S * a.n_tokens * (a.n_proj > 0 ? a.n_proj : 1) > kUncrowded)
+    if ((long long)a.S * a.items * (a.n_proj > 0 ? a.n_proj : 1) > kUncrowded)
       return launch_fused_rows<DT, R, G, MODE | kCrowded>(a, st);
   }
-  return a.n_proj > 0 ? launch_fused_side_t<DT, R, G, MODE>(a, st) : launch_fused_t<DT, R, G, 1, MODE>(a, st);
+  return a.n_proj > 0 ? launch_fused_side_t<DT, R, G, MODE>(a, st) : launch_fused_t<DT, R, G, MODE>(a, st);
 }
 
 template <class DT, int R, int G>
 static hipError_t launch_fused_rb(const FusedArgs& a, hipStream_t st) {
   const bool streamed = stream_weights(a.by_rows, a.n_tokens, a.n_segs, a.r, (long long)a.h_in + a.h_out);
+  if (a.paired) {
+    if constexpr (R <= 32)
+      return streamed ? launch_fused_t<DT, R, G, kPerRow | kPaired | kStreamed>(a, st) : launch_fused_t<DT, R, G, kPerRow | kPaired>(a, st);
+    else
+      return hipErrorInvalidValue;
+  }
   if (a.by_rows)
     return streamed ? launch_fused_rows<DT, R, G, kPerRow | kStreamed>(a, st) : launch_fused_rows<DT, R, G, kPerRow>(a, st);
   // streamed at every size (seven segments: 8.4 -> 7.9 us); only segments that carry the same pointers lose by it (128
   // of eight adapters, rank 64, three add-ons 34.2 -> 39.9), and such rows belong in one segment
   if (a.n_proj > 0) return launch_fused_side_t<DT, R, G, kPerSegment | kStreamed>(a, st);
-  return streamed ? launch_fused_t<DT, R, G, 1, kPerSegment | kStreamed>(a, st) : launch_fused_t<DT, R, G, 1, kPerSegment>(a, st);
+  return streamed ? launch_fused_t<DT, R, G, kPerSegment | kStreamed>(a, st) : launch_fused_t<DT, R, G, kPerSegment>(a, st);
 }
 
 template <class DT, int R>

@@ -87,7 +87,9 @@ struct FusedArgs {
   int S;                     // workgroups per segment = k-slices = column slices
   int kslice, cslice;        // elements per k-slice / columns per column slice
   int G;                     // lane groups of the expand phase (1, 2, 4 or 8)
-  bool by_rows;              // the grid's items are the n_tokens rows, each looking its segment up, not the segments
+  int items;                 // of the grid: the segments ...
+  bool by_rows;              // ... or the n_tokens rows, each looking its segment up ...
+  bool paired;               // ... or pairs of rows of one segment (pair_places)
   int spin_limit;            // polls before a waiting workgroup gives up
   long long offA, offB;      // layer offsets in elements
   float scale;
@@ -173,6 +175,9 @@ inline long long fused_grid_items(long long items) {
 inline bool stream_weights(bool by_rows, int n_tokens, int n_segs, int r, long long width) {
   return n_segs * width * r >= (4LL << 20) && (!by_rows || n_tokens <= 3LL * n_segs);
 }
+
+// Items of a per-row launch that takes two rows of a segment to an item (device_common.h, find_rows); some stay empty.
+__host__ __device__ inline int pair_places(int n_tokens, int n_segs) { return (n_tokens + n_segs) / 2; }
 
 size_t tile_lds_bytes(int r, int kslice, int cslice);
 hipError_t launch_add_lora_whole(const WholeArgs& a, hipStream_t st);
