@@ -1002,6 +1002,17 @@ int plan_multi(const sgmv_problem* p, int n_segs, int n_proj, FusedArgs* f, Tile
   return SGMV_KERNEL_SEQUENCE;
 }
 
+// Add-ons that plan_multi gives several launches (`kernel`, `t`), at rank 64: the MFMA kernels, three launches for three of
+// them, from four rows per segment on.  Measured, us, one after the other or in groups / on these: two or three add-ons of 24 to 400 rows,
+// seven shapes, 1.4 times as fast on average (three of 4096 -> 4096, 16 x 8 rows 47.3 / 22.5, 32 x 4 rows 51.8 / 35.3), the least
+// 0.99 (two of 100 x 4 rows, 8192 wide, 109.3 / 110.3), which is where the line lies; with fewer rows per segment 0.82 to 1.7.
+bool multi_takes_matrix(const sgmv_problem* p, int n_segs, int n_proj, int kernel, const TileArgs& t) {
+  const bool several = kernel == SGMV_KERNEL_SEQUENCE || (kernel == SGMV_KERNEL_TILE && t.n_proj < n_proj);
+  return several && n_proj >= 2 && p->path == SGMV_PATH_AUTO && p->ksplit == 0 && p->r == 64 && p->max_seg_len != 1 &&
+         p->n_tokens >= 24 && p->n_tokens <= 400 && p->n_tokens >= 4LL * n_segs && p->workspace != nullptr &&
+         p->workspace_bytes >= sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj);
+}
+
 }  // namespace
 
 extern "C" {
@@ -1330,7 +1341,9 @@ int sgmv_add_lora_multi(const sgmv_problem* p, int32_t n_proj, void* const* ys,
   hipStream_t st = static_cast<hipStream_t>(stream);
   FusedArgs f;
   TileArgs tile;
-  const int kernel = plan_multi(p, n_segs, n_proj, &f, &tile);
+  int kernel = plan_multi(p, n_segs, n_proj, &f, &tile);
+  const bool joint_matrix = multi_takes_matrix(p, n_segs, n_proj, kernel, tile);
+  if (joint_matrix) kernel = SGMV_KERNEL_SEQUENCE;
   if (kernel == SGMV_KERNEL_TILE) {
     const Scratch sc = caller_scratch(p);
     const int group = tile.n_proj;
@@ -1378,7 +1391,7 @@ int sgmv_add_lora_multi(const sgmv_problem* p, int32_t n_proj, void* const* ys,
   // (Where a single add-on would take two rows to an item of the hand-off kernel, these launches together are ahead: two of
   // 250 rows of 37 adapters, 8192 wide, rank 16, 20.2 us against 35.9; three of 120 rows of 22, 13824 wide, rank 32, 37.7 / 66.1.)
   SinglePlan pl;
-  if (n_proj >= 2 && plan_single(p, n_segs, &pl, false) == SGMV_OK && pl.kernel == SGMV_KERNEL_MATRIX &&
+  if (n_proj >= 2 && (joint_matrix || (plan_single(p, n_segs, &pl, false) == SGMV_OK && pl.kernel == SGMV_KERNEL_MATRIX)) &&
       p->workspace_bytes >= sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj)) {
     const Scratch sc = caller_scratch(p);
     // the first add-on's partial sums and operands where a single call keeps them, the others' behind the
@@ -1490,10 +1503,13 @@ int sgmv_plan_add_lora(const sgmv_problem* p, int32_t n_segs, int32_t n_proj, sg
     rc = check_workspace(p);
     if (rc != SGMV_OK) return rc;
   }
+  bool joint_matrix = false;
   if (n_proj > 1) {
     FusedArgs f;
     TileArgs tile;
-    const int kernel = plan_multi(p, n_segs, n_proj, &f, &tile);
+    int kernel = plan_multi(p, n_segs, n_proj, &f, &tile);
+    joint_matrix = multi_takes_matrix(p, n_segs, n_proj, kernel, tile);
+    if (joint_matrix) kernel = SGMV_KERNEL_SEQUENCE;
     if (kernel == SGMV_KERNEL_TILE) {  // groups of tile.n_proj add-ons; slices and workgroups of the first launch
       plan->kernel = kernel;
       plan->launches = (n_proj + tile.n_proj - 1) / tile.n_proj;
@@ -1515,6 +1531,11 @@ int sgmv_plan_add_lora(const sgmv_problem* p, int32_t n_segs, int32_t n_proj, sg
   if (rc == SGMV_OK && n_proj >= 2 &&
       (pl.kernel != SGMV_KERNEL_MATRIX || p->workspace_bytes < sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj)))
     rc = plan_single(p, n_segs, &pl);  // one after the other
+  if (joint_matrix) {
+    rc = SGMV_OK;
+    pl.kernel = SGMV_KERNEL_MATRIX;
+    pl.direct = false;
+  }
   if (rc != SGMV_OK) return rc;
   plan->kernel = pl.kernel;
   switch (pl.kernel) {
