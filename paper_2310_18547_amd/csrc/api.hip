@@ -990,9 +990,8 @@ int plan_multi(const sgmv_problem* p, int n_segs, int n_proj, FusedArgs* f, Tile
   // against add-ons per row one after the other it is ahead also in groups and with fewer slices
   // (four add-ons, rank 8: 32 x 2 rows in two launches 17.5 against 19.4, Skewed of 64 rows at
   // three slices 11.8 against 18.4; rank 32: 32 x 4 rows 30.4 against 40.6)
-  // (The launch-per-step kernels, which take the add-ons side by side too, are not asked here: at rank 64
-  // they are ahead, 16 x 8 rows two / three add-ons 20.4 / 22.5 against 31.4 / 47.3, 64 x 4 rows 38.5 / 53.9
-  // against 49 / 74, and from 64 x 4 rows on at ranks 16 / 32, three add-ons 24.4 / 33.7 against 31.3 / 42.3.)
+  // (The launch-per-step kernels, which take the add-ons side by side too, are asked at rank 64 in place of several tile launches,
+  // multi_takes_matrix.  From 64 x 4 rows on they are ahead at ranks 16 / 32 too, three add-ons 24.4 / 33.7 against 31.3 / 42.3.)
   if (tile && (!per_row || (t->n_proj == n_proj && t->S >= kTileMultiSlices))) return SGMV_KERNEL_TILE;
   if (per_row && !rows_first) {
     const int kernel = joint_rows();
@@ -1002,15 +1001,28 @@ int plan_multi(const sgmv_problem* p, int n_segs, int n_proj, FusedArgs* f, Tile
   return SGMV_KERNEL_SEQUENCE;
 }
 
-// Add-ons that plan_multi gives several launches (`kernel`, `t`), at rank 64: the MFMA kernels, three launches for three of
-// them, from four rows per segment on.  Measured, us, one after the other or in groups / on these: two or three add-ons of 24 to 400 rows,
-// seven shapes, 1.4 times as fast on average (three of 4096 -> 4096, 16 x 8 rows 47.3 / 22.5, 32 x 4 rows 51.8 / 35.3), the least
-// 0.99 (two of 100 x 4 rows, 8192 wide, 109.3 / 110.3), which is where the line lies; with fewer rows per segment 0.82 to 1.7.
+// Add-ons of rank 64 that plan_multi gives several launches of the tile kernel (`kernel`, `t`: in groups, or one by one): the
+// MFMA kernels, three launches for three of them, from four rows per segment on.  Only in place of the tile kernel, which
+// feeds v to the second product as a high and a low 16-bit part too; the hand-off and vector kernels keep it in fp32, and their calls
+// stay with them.  Measured, us, tile launches / MFMA kernels, 24 to 400 rows, two to eight add-ons, 256 to 13824 wide: where the tile
+// launches are at least twice the groups of three, 551 points, 1.43 times as fast on average (three of 16 x 8 rows, 4096 wide,
+// 47.3 / 22.5), the least 0.97 (three of 48 segments of 200 rows, 2048 -> 2184).  With fewer they lose: four add-ons in two launches 0.83 on
+// average, five 0.84 (9088 -> 264, four of 7 segments of 32 rows, 25 / 41), in three 1.11 but down to 0.90; eight in two, three and four 0.56,
+// 0.83 and 1.04 (4160 -> 2048, 5 segments of 30 rows, 21.5 / 51.5).
 bool multi_takes_matrix(const sgmv_problem* p, int n_segs, int n_proj, int kernel, const TileArgs& t) {
-  const bool several = kernel == SGMV_KERNEL_SEQUENCE || (kernel == SGMV_KERNEL_TILE && t.n_proj < n_proj);
-  return several && n_proj >= 2 && p->path == SGMV_PATH_AUTO && p->ksplit == 0 && p->r == 64 && p->max_seg_len != 1 &&
-         p->n_tokens >= 24 && p->n_tokens <= 400 && p->n_tokens >= 4LL * n_segs && p->workspace != nullptr &&
-         p->workspace_bytes >= sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj);
+  if (n_proj < 2 || p->path != SGMV_PATH_AUTO || p->ksplit != 0 || p->r != 64 || p->max_seg_len == 1) return false;
+  if (p->n_tokens < 24 || p->n_tokens > 400 || p->n_tokens < 4LL * n_segs || p->workspace == nullptr ||
+      p->workspace_bytes < sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj))
+    return false;
+  int group = t.n_proj;
+  if (kernel == SGMV_KERNEL_SEQUENCE) {
+    SinglePlan one;
+    if (plan_single(p, n_segs, &one) != SGMV_OK || one.kernel != SGMV_KERNEL_TILE) return false;
+    group = 1;
+  } else if (kernel != SGMV_KERNEL_TILE) {
+    return false;
+  }
+  return ceil_div(n_proj, group) >= 2 * ceil_div(n_proj, kSharedShrinkMost);
 }
 
 }  // namespace
