@@ -677,13 +677,23 @@ bool choose_fused_pairs(const sgmv_problem* p, int n_segs, FusedArgs* f) {
 //  * from rank 16 on where the tile kernel has six slices or more (12000 -> 1024, rank 16, 33 x 3 rows 10.0 / 13.0; 9992 ->
 //    3000, 6 x 20 rows 8.9 / 11.4), at rank 8 six or seven (128 rows of 42 segments 8.9 / 9.7; eight 9.6 / 7.1, above);
 //  * from rank 16 on more than 128 rows (8192 -> 8192, rank 16, Skewed of 256 rows 14.5 / 18.4);
-//  * a column slice a workgroup takes several passes or single lanes for (11008 -> 11008, rank 16, Skewed of 128 rows 13.9 / 18.7;
+//  * column slices beyond 1024 columns at rank 16, a pass with two lane groups, and beyond 2048 at the others, a pass of rank 8 with one
+//    and two passes of rank 32 with two (11008 -> 11008, rank 16, Skewed of 128 rows 13.9 / 18.7;
 //    8192 -> 28672, rank 8, 12 x 20 rows 16.0 / 21.9, rank 32, Skewed of 66 rows 19.9 / 25.7);
-//  * at rank 32 more than a workgroup per unit (11008 -> 4096, Skewed of 128 rows 16.8 / 17.3).
+//  * at rank 32 more than a workgroup per unit (11008 -> 4096, Skewed of 128 rows 16.8 / 17.3);
+//  * to the tile kernel up to rank 16, where pairs are more than two workgroups per unit and no segment is long (three rows take two
+//    pairs' places but one block of the tile kernel, which takes several for more than sixteen): at rank 16 segments of 3 to 48 rows (9992 ->
+//    1024, 101 rows of 51 10.4 / 13.8, 110 rows of 23 10.4 / 12.2; 253 such points 1.08 times as fast on the tile kernel, 147 others
+//    1.24 times on pairs, 0.99 at least: 13824 -> 2048, 51 x 2 rows 12.5 / 11.1), at rank 8, where the tile kernel has five slices and more,
+//    of 5 to 32 rows (9992 -> 1024, 116 rows of 20 8.1 / 9.7; 83 points 1.02 times on the tile kernel, 317 others 1.28 times on pairs).
 bool choose_add_on_pairs(const sgmv_problem* p, int n_segs, int tile_slices, FusedArgs* f) {
   if (p->r == 8 ? tile_slices == 6 || tile_slices == 7 : tile_slices >= 6 || p->n_tokens > 128) return false;
-  return choose_fused_pairs(p, n_segs, f) && f->cslice <= (p->r == 16 ? 1024 : 2048) &&
-         (p->r < 32 || (long long)f->S * f->items <= limits().fused_workgroups);
+  if (!choose_fused_pairs(p, n_segs, f) || f->cslice > (p->r == 16 ? 1024 : 2048)) return false;
+  const int units = limits().fused_workgroups;
+  if (p->r == 32) return (long long)f->S * f->items <= units;
+  if (tile_slices == 0 || f->S * fused_grid_items(f->items) <= 2 * units) return true;
+  if (p->r == 8) return tile_slices < 5 || p->max_seg_len <= 4 || p->max_seg_len > 32;
+  return p->max_seg_len > 48 || (p->max_seg_len == 2 && 4LL * p->n_tokens > 7LL * n_segs);
 }
 
 // The stand-alone shrink: rank 8, 13824 wide, Uniform of 128 rows 15.4 / 7.2, 11008 wide, 16 x 8 rows 10.5 / 5.3; rank 16, 13824 wide,

@@ -710,3 +710,19 @@ def test_joint_launches_of_rank_64_leave_v_in_the_precision_it_had():
                             max_seg_len=hint, workspace_ready=1)
         kernels = [sg.sgmv_plan_add_lora(p, len(lens), count, check=False)[1].kernel for count in (1, n_proj)]
         assert kernels == [one, joint], (lens, n_proj)
+
+
+def test_pairs_of_rows_leave_the_tile_kernel_what_it_is_ahead_on():
+    # (segment lengths, h_in, h_out, rank) on both sides of the lines: two workgroups per unit (512), segments of 3 and 49 rows at rank
+    # 16, of 5 and 33 at rank 8
+    tile, pairs = sg.KERNEL_TILE, sg.KERNEL_FUSED
+    for lens, h_in, h_out, r, kernel in (
+            ([3, 2, 1] * 17, 9992, 1024, 16, tile), ([2] * 51, 13824, 2048, 16, pairs), ([2] * 40 + [1] * 18, 13824, 1024, 16, tile),
+            ([5] * 22, 9992, 1024, 16, tile), ([48] + [3] * 21, 9992, 1024, 16, tile), ([49] + [3] * 21, 9992, 1024, 16, pairs),
+            ([6] * 19, 9992, 1024, 8, tile), ([4] * 29, 9992, 1024, 8, pairs),
+            ([32] + [8] * 12, 9992, 1024, 8, tile), ([33] + [8] * 11 + [7], 9992, 1024, 8, pairs)):
+        n = sum(lens)
+        p = sg.make_problem(sg.F16, h_in, h_out, r, 1, n, workspace=256, workspace_bytes=sg.sgmv_workspace_bytes(n, r),
+                            max_seg_len=max(lens), workspace_ready=1)
+        rc, plan = sg.sgmv_plan_add_lora(p, len(lens), 1, check=False)
+        assert rc == 0 and plan.kernel == kernel, (lens, h_in, h_out, r)
