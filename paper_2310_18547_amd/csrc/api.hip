@@ -220,13 +220,26 @@ bool matrix_direct(const sgmv_problem* p, int n_segs, int n_proj, int slices) {
 // Add-ons of long segments under SGMV_PATH_AUTO: instead as many slices as give every compute unit one workgroup and not
 // more, because the units that get a second one decide when the launch ends: 2000 rows of six segments, rank 16, 8192 wide (35
 // row blocks), whole add-on at 5 / 6 / 8 / 16 slices 25.7 / 25.1 / 27.3 / 27.5 us; 4814 rows at rank 64 (41 blocks of 128) 57.5 /
-// 56.5 / 60.0 / 59.6; three add-ons of 2600 rows at rank 32 (22 blocks) at 4 / 8 / 16 45.5 / 40.7 / 44.3.  From seven on only
-// eight or sixteen (1400 rows, rank 16, 8192 wide, 8 / 10 / 12 / 16 slices 19.0 / 20.0 / 21.4 / 20.5; three add-ons of 3440 rows,
-// rank 32, 8192 wide, 7 / 8 slices 46.1 / 40.9).  Fewer than four leave too few loads in flight (4814 rows, rank 16, 8192 wide,
-// 4 / 6 / 8 / 16 slices 52.6 / 50.4 / 48.9 / 47.6), and the rule above stays, as for five or six up to rank 16 (2625 rows, 11008 ->
-// 1024, rank 16, 5 / 16 slices 23.4 / 22.0).  Short segments whose partial sums the expand adds
-// up itself: eight, in small batches on wide inputs sixteen (60 of 8 rows, rank 16, 4096 wide, 8 / 16 slices 12.7 / 14.2; 20 of 20
-// rows, 8192 wide, 14.6 / 13.9).
+// 56.5 / 60.0 / 59.6; three add-ons of 2600 rows at rank 32 (22 blocks) at 4 / 8 / 16 45.5 / 40.7 / 44.3.  From eight on only
+// eight or sixteen (1400 rows, rank 16, 8192 wide, 8 / 10 / 12 / 16 slices 19.0 / 20.0 / 21.4 / 20.5).  Fewer than four leave too few
+// loads in flight (4814 rows, rank 16, 8192 wide, 4 / 6 / 8 / 16 slices 52.6 / 50.4 / 48.9 / 47.6), and the count above stays, as it does
+//  * for five or six up to rank 16 (2625 rows, 11008 -> 1024, rank 16, 5 / 16 slices 23.4 / 22.0), and five at rank 32 on inputs wider than
+//    8192 (2335 rows, 11008 -> 13824, 5 / 16 slices 47.8 / 46.0), whose last chunks are the longer the fewer they are;
+//  * for four at rank 8 from 8192 on (3535 rows, 8192 -> 5120, 4 / 16 slices 34.4 / 32.8), and for four and five beyond eight segments,
+//    which are often many short ones beside a few long ones and then more blocks than this reckons (1686 rows of twelve, 11008 -> 4096,
+//    rank 64, three add-ons, 4 / 8 slices 71.3 / 56.4);
+//  * for seven, which eight overfills: 1921 rows, 11008 -> 2048, rank 16, 8 / 16 slices 27.2 / 24.6; 1124 rows, 1024 -> 824, rank 64, three
+//    add-ons, 8 / 4 slices 20.1 / 17.9; but where the count above is four or less on inputs wider than 4096, eight it is (1.11 times as fast
+//    on average);
+//  * where a slice would have less than 256 of the input, two chunks (1312 rows, 1024 wide, rank 64, 6 / 4 slices 19.2 / 18.0);
+//  * at rank 64 for more than sixteen (454 rows, 13824 -> 5120, 31 / 16 slices 20.3 / 23.0).
+// Sixteen from fourteen on, on inputs wider than 8192 from twelve on, where half as many chunks one after the other outweigh a
+// second round (1755 rows, 11008 -> 2424, rank 32, three add-ons 13.6: 8 / 16 slices 47.9 / 42.8).  1712 points whose count or launches
+// follow from these rules, against the count above and three launches: 1.08 times as fast on average, four below 0.97, 0.93 at worst.
+// Short segments whose partial sums the expand adds up itself: eight, in small batches on wide inputs sixteen (60 of 8 rows, rank 16, 4096 wide,
+// 8 / 16 slices 12.7 / 14.2; 20 of 20 rows, 8192 wide, 14.6 / 13.9), or the count above and three launches where sixteen are too many to be
+// added up there (three add-ons of 788 rows, 11352 -> 1320, rank 16, 8 / 16 slices 31.0 / 25.9), and where that count is more than sixteen for
+// three add-ons of rank 16 (462 rows of six, 11008 -> 11008, 32 / 16 slices 27.6 / 30.2).
 MatrixSplit choose_split_matrix(const sgmv_problem* p, int n_segs, int n_proj, bool same_x) {
   const int cap = split_cap(p->n_tokens);
   const int most = p->h_in / 128 > 0 ? p->h_in / 128 : 1;  // keep slices of at least one chunk
@@ -251,10 +264,26 @@ MatrixSplit choose_split_matrix(const sgmv_problem* p, int n_segs, int n_proj, b
       const bool is_long = p->n_tokens >= (long long)n_segs * rows;
       const float last = is_long ? 0.5f * n_segs + 0.6f * sqrtf((float)n_segs) : 0.25f * n_segs;
       const int fill = (int)(compute_units() / (((float)p->n_tokens / rows + last) * (shared ? 1 : n_proj)));
-      if (is_long && (fill >= 7 || fill == 4 || (fill > 4 && p->r >= 32)))
-        s = fill >= 14 ? 16 : fill >= 7 ? 8 : fill;
-      else if (!is_long && matrix_direct(p, n_segs, n_proj, within(8)))
-        s = fill >= 14 && p->h_in > 4096 && matrix_direct(p, n_segs, n_proj, within(16)) ? 16 : 8;
+      if (is_long) {
+        int n = s;
+        if (fill >= (p->h_in > 8192 ? 12 : 14))
+          n = p->r == 64 && s > 16 ? s : 16;
+        else if (fill >= 8 || (fill == 7 && s < 8 && p->h_in > 4096))
+          n = 8;
+        else if (p->r >= 32 && fill == 6)
+          n = 6;
+        else if (n_segs <= 8 && (fill == 4 ? p->r > 8 || p->h_in < 8192 : fill == 5 && (p->r == 64 || (p->r == 32 && p->h_in <= 8192))))
+          n = fill;
+        while (n > s && n * 256 > p->h_in) n = n >= 8 ? n / 2 : s;
+        s = n;
+      } else if ((s <= 16 || p->r * n_proj <= 32 || p->h_in <= 8192) && matrix_direct(p, n_segs, n_proj, within(8))) {
+        if (fill < 14 || p->h_in <= 4096)
+          s = 8;
+        else if (matrix_direct(p, n_segs, n_proj, within(16)))
+          s = 16;
+        else if (p->h_in <= 8192)
+          s = 8;
+      }
     }
   }
   MatrixSplit m;
