@@ -678,7 +678,7 @@ ExpandArgs make_expand(const sgmv_problem* p, void* y, const float* v_parts, int
   a.B_ptrs = B_ptrs;
   a.seg_starts = seg_starts;
   a.scale = scale;
-  a.vh = a.vl = nullptr;
+  a.vh = a.vl = a.vr = nullptr;
   a.undo = nullptr;
   a.header = nullptr;
   a.by_rows = false;
@@ -1040,28 +1040,37 @@ int plan_multi(const sgmv_problem* p, int n_segs, int n_proj, FusedArgs* f, Tile
   return SGMV_KERNEL_SEQUENCE;
 }
 
-// Add-ons of rank 64 that plan_multi gives several launches of the tile kernel (`kernel`, `t`: in groups, or one by one): the
-// MFMA kernels, three launches for three of them, from four rows per segment on.  Only in place of the tile kernel, which
-// feeds v to the second product as a high and a low 16-bit part too; the hand-off and vector kernels keep it in fp32, and their calls
-// stay with them.  Measured, us, tile launches / MFMA kernels, 24 to 400 rows, two to eight add-ons, 256 to 13824 wide: where the tile
-// launches are at least twice the groups of three, 551 points, 1.43 times as fast on average (three of 16 x 8 rows, 4096 wide,
-// 47.3 / 22.5), the least 0.97 (three of 48 segments of 200 rows, 2048 -> 2184).  With fewer they lose: four add-ons in two launches 0.83 on
-// average, five 0.84 (9088 -> 264, four of 7 segments of 32 rows, 25 / 41), in three 1.11 but down to 0.90; eight in two, three and four 0.56,
-// 0.83 and 1.04 (4160 -> 2048, 5 segments of 30 rows, 21.5 / 51.5).
+// Add-ons of rank 64 that plan_multi gives several launches (`kernel`, `t`): the MFMA kernels, three launches for three of them,
+// from four rows per segment on.  Their second product then takes v as three 16-bit parts, all 24 bits of it, as the hand-off and vector
+// kernels do, whose calls these mostly are (ExpandArgs::vr; two parts give y a relative error of 4.5e-3 in binary16 where v is about 2^-18).
+// Measured, us, what was taken before / these, 24 to 400 rows, two to eight add-ons, 256 to 13824 wide, by the launches that were taken
+// before (vector kernels two per add-on) to the groups of three:
+//  * at least twice as many, 1055 points: 1.47 times as fast on average, six below 0.97, 0.90 at worst; four add-ons of the hand-off
+//    kernel only from 50 rows on (45 rows of nine, 1736 -> 1024, 22.8 / 27.3);
+//  * fewer, in groups of the tile kernel, 152 points: 0.84 times (four in two launches 0.83, five in two and three 0.82 and 1.08, eight in two,
+//    three and four 0.60, 0.82 and 1.00: 4160 -> 2048, 30 rows of five, 21.5 / 52), so those stay.
 bool multi_takes_matrix(const sgmv_problem* p, int n_segs, int n_proj, int kernel, const TileArgs& t) {
   if (n_proj < 2 || p->path != SGMV_PATH_AUTO || p->ksplit != 0 || p->r != 64 || p->max_seg_len == 1) return false;
   if (p->n_tokens < 24 || p->n_tokens > 400 || p->n_tokens < 4LL * n_segs || p->workspace == nullptr ||
       p->workspace_bytes < sgmv_workspace_bytes_multi(p->n_tokens, p->r, n_proj))
     return false;
-  int group = t.n_proj;
-  if (kernel == SGMV_KERNEL_SEQUENCE) {
+  int launches;
+  if (kernel == SGMV_KERNEL_TILE) {
+    launches = ceil_div(n_proj, t.n_proj);
+  } else if (kernel == SGMV_KERNEL_SEQUENCE) {
     SinglePlan one;
-    if (plan_single(p, n_segs, &one) != SGMV_OK || one.kernel != SGMV_KERNEL_TILE) return false;
-    group = 1;
-  } else if (kernel != SGMV_KERNEL_TILE) {
+    if (plan_single(p, n_segs, &one) != SGMV_OK || one.kernel == SGMV_KERNEL_MATRIX) return false;  // these it takes anyway
+    if (one.kernel == SGMV_KERNEL_FUSED && n_proj == 4 && p->n_tokens < 50) return false;
+    launches = one.kernel == SGMV_KERNEL_VECTOR ? 2 * n_proj : n_proj;
+  } else {
     return false;
   }
-  return ceil_div(n_proj, group) >= 2 * ceil_div(n_proj, kSharedShrinkMost);
+  if (launches < 2 * ceil_div(n_proj, kSharedShrinkMost)) return false;
+  // the third part of v lies behind the partial sums, half a slice of them: room for it in every group of add-ons
+  const int cap = split_cap(p->n_tokens);
+  for (int count = n_proj < kSharedShrinkMost ? n_proj : kSharedShrinkMost; count > 0; --count)
+    if (choose_split_matrix(p, n_segs, count, true).ksplit >= cap || choose_split_matrix(p, n_segs, count, false).ksplit >= cap) return false;
+  return true;
 }
 
 }  // namespace
@@ -1472,6 +1481,8 @@ int sgmv_add_lora_multi(const sgmv_problem* p, int32_t n_proj, void* const* ys,
         Scratch own = sc;
         if (i > 0) own.operands = extra + (size_t)(i - 1) * (parts + ops) + parts;
         set_operands(&es[i], own, p->n_tokens, p->r);
+        if (joint_matrix)  // behind the last slice's partial sums (multi_takes_matrix: there is room)
+          es[i].vr = reinterpret_cast<uint16_t*>(sa.partials_of[i] + (size_t)m.ksplit * p->n_tokens * p->r);
       }
       if (launch_expand_matrix(es, count, m.direct, st) != hipSuccess) return SGMV_ERR_LAUNCH;
     }

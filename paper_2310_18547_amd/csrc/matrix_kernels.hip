@@ -175,37 +175,44 @@ static long long most_blocks(int n_tokens, int n_segs, int rows) {
 static float segments_per_block(int n_segs, long long blocks) { return (float)n_segs / (float)blocks; }
 
 // Binary16 has a narrow range, so a row of v whose largest |v|, amax, reaches 2^14 is scaled down by an exact power of
-// two, the result, and `undo` restores the fp32 result (both 1 otherwise).
+// two, the result, and `undo` restores the fp32 result (both 1 otherwise).  As three parts (BOTH) a smaller row is scaled up
+// likewise, so that its parts keep all bits.
+template <bool BOTH = false>
 __device__ __forceinline__ float range_factor(float amax, float& undo) {
-  const bool large = amax >= 16384.f && amax < 3.0e38f;
-  const int e = large ? (int)((__float_as_uint(amax) >> 23) & 0xFF) - 127 - 13 : 0;  // amax * 2^-e < 2^14
+  const int above = (int)((__float_as_uint(amax) >> 23) & 0xFF) - 127 - 13;  // amax * 2^-above is in 2^13 .. 2^14
+  const int e = amax >= 3.0e38f ? 0 : amax >= 16384.f ? above : BOTH ? max(above, -100) : 0;
   undo = __uint_as_float((uint32_t)(127 + e) << 23);
   return __uint_as_float((uint32_t)(127 - e) << 23);
 }
 
-// v of a row at four consecutive k as the MFMA expand's two 16-bit operand parts and, for binary16, the row's range
-// factor.  The R / 4 lanes that hold a row are consecutive lanes of a wave, and every lane of the wave calls this (live or
-// not; what a lane that is not live holds is of no consequence).
-template <class DT, int R>
-__device__ __forceinline__ void split_quad(const float4& sum, uint2& high, uint2& low, float& undo) {
+// v of a row at four consecutive k as the MFMA expand's PARTS 16-bit operand parts (two, or three: all 24 bits) and, for binary16,
+// the row's range factor.  The R / 4 lanes that hold a row are consecutive lanes of a wave, and every lane of the wave calls this
+// (live or not; what a lane that is not live holds is of no consequence).
+template <class DT, int R, int PARTS>
+__device__ __forceinline__ void split_quad(const float4& sum, uint2 (&part)[PARTS], float& undo) {
   constexpr int GPR = R / 4;  // lanes per row
   float f[4] = {sum.x, sum.y, sum.z, sum.w};
   undo = 1.f;
   if (std::is_same<DT, F16>::value) {
     float amax = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) amax = fmaxf(amax, fabsf(f[i]));
+    for (int i = 0; i < 4; ++i) amax = fmaxf(amax, PARTS == 3 && !(fabsf(f[i]) < 3.0e38f) ? 0.f : fabsf(f[i]));
 #pragma unroll
     for (int msk = 1; msk < GPR; msk <<= 1) amax = fmaxf(amax, __shfl_xor(amax, msk, 64));
-    const float down = range_factor(amax, undo);
+    const float down = range_factor<PARTS == 3>(amax, undo);
 #pragma unroll
     for (int i = 0; i < 4; ++i) f[i] *= down;
   }
-  uint32_t h[4], l[4];
+  uint32_t h[PARTS][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) split16<DT>(f[i], h[i], l[i]);
-  high = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-  low = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (PARTS == 3)
+      split16<DT>(f[i], h[0][i], h[1][i], h[2][i]);
+    else
+      split16<DT>(f[i], h[0][i], h[1][i]);
+  }
+#pragma unroll
+  for (int q = 0; q < PARTS; ++q) part[q] = make_uint2(h[q][0] | (h[q][1] << 16), h[q][2] | (h[q][3] << 16));
 }
 
 // A lane's part of the split-K partial sums, four consecutive k, of up to N slices in flight together (load(i) gives those
@@ -435,8 +442,8 @@ __global__ __launch_bounds__((64 * ShrinkShape<R, P>::kWaves), 4) void shrink_st
 
 // ---------------------------------------------------------------- expand
 
-// v[row][k] = sum over the split-K parts (ascending), written out as the two 16-bit
-// operands the expand kernel feeds to the matrix cores: vh, vl [n_tokens][R] 16-bit,
+// v[row][k] = sum over the split-K parts (ascending), written out as the two or three 16-bit
+// operands the expand kernel feeds to the matrix cores: vh, vl and vr [n_tokens][R] 16-bit,
 // undo [n_tokens] fp32 (split_quad).  One thread handles four consecutive k of a row;
 // the kernel is one memory latency long.
 // blockIdx.y is the add-on.
@@ -444,9 +451,10 @@ struct FinalizeTable {
   const float* v_parts[kSharedShrinkMost];
   uint16_t* vh[kSharedShrinkMost];
   uint16_t* vl[kSharedShrinkMost];
+  uint16_t* vr[kSharedShrinkMost];
   float* undo[kSharedShrinkMost];
 };
-template <class DT, int R>
+template <class DT, int R, int PARTS>
 __global__ __launch_bounds__(256) void finalize_v_kernel(int nparts, int n_tokens, FinalizeTable tab) {
   constexpr int GPR = R / 4;  // threads per row
   const int z = blockIdx.y;
@@ -471,12 +479,13 @@ __global__ __launch_bounds__(256) void finalize_v_kernel(int nparts, int n_token
     add_parts(std::integral_constant<int, 8>{});
   else
     add_parts(std::integral_constant<int, 16>{});
-  uint2 high, low;
+  uint2 part[PARTS];
   float undo;
-  split_quad<DT, R>(sum, high, low, undo);
+  split_quad<DT, R>(sum, part, undo);
   if (live) {
-    *reinterpret_cast<uint2*>(tab.vh[z] + e0) = high;
-    *reinterpret_cast<uint2*>(tab.vl[z] + e0) = low;
+    *reinterpret_cast<uint2*>(tab.vh[z] + e0) = part[0];
+    *reinterpret_cast<uint2*>(tab.vl[z] + e0) = part[1];
+    if constexpr (PARTS == 3) *reinterpret_cast<uint2*>(tab.vr[z] + e0) = part[2];
     if (it % GPR == 0) tab.undo[z][it / GPR] = undo;
   }
 }
@@ -496,13 +505,14 @@ struct ExpandTable {
   uint16_t* y[kSharedShrinkMost];
   const uint16_t* vh[kSharedShrinkMost];
   const uint16_t* vl[kSharedShrinkMost];
+  const uint16_t* vr[kSharedShrinkMost];  // PARTS = 3
   const float* undo[kSharedShrinkMost];
   const uint16_t* const* A_ptrs[kSharedShrinkMost];  // may be nullptr
   const uint16_t* const* B_ptrs[kSharedShrinkMost];
-  const float* v_parts[kSharedShrinkMost];  // DIRECT; else vh, vl and undo, which finalize_v_kernel made of them
+  const float* v_parts[kSharedShrinkMost];  // DIRECT; else vh, vl, vr and undo, which finalize_v_kernel made of them
 };
 
-// grid = (items, add-ons, further items); vh / vl / undo come from finalize_v_kernel.  The list of items: for a segment
+// grid = (items, add-ons, further items); v comes as the partial sums (DIRECT) or as finalize_v_kernel's operands.  The list of items: for a segment
 // of more than few_rows rows its 64-row blocks x strips of 256 columns, for a shorter one its strips of 2048
 // columns.
 //
@@ -547,8 +557,9 @@ __device__ __forceinline__ uint2 add4(const uint2& y, float scale, const f32x4 (
   return make_uint2(pack2<DT>(f[0], f[1]), pack2<DT>(f[2], f[3]));
 }
 
-template <class DT, int R, bool DIRECT>
-__global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
+// (three parts of v at rank 64: 137 registers)
+template <class DT, int R, bool DIRECT, int PARTS>
+__global__ __launch_bounds__(256, PARTS == 3 ? 3 : 4) void expand_matrix_kernel(
     const int32_t* __restrict__ seg_starts, int n_segs, float guess, int strips, int few_rows, int few_strips, int h_out,
     long long layer_off, float scale, unsigned long long* header, ExpandTable tab, int nparts, int n_tokens) {
   constexpr int NC = kExpandCols;        // columns of a strip
@@ -561,6 +572,7 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
   static_assert(!DIRECT || (PAIRED && DirectShape<R>::kQuads <= 256), "a thread has at most one quad of v");
   constexpr int ITEMS = (R / KR) * (NC / 8);
   static_assert(ITEMS <= 256, "one item per thread");
+  static_assert(PARTS == 2 || (PARTS == 3 && !PAIRED), "v as two parts or three");
   // B_i strip, transposed, as 16-byte slots {8 consecutive k of one column}, k block by k block; column c of
   // the strip sits in slot (c % 8) * PITCH + c / 8: consecutive lanes of the staging write
   // consecutive slots, and the sixteen lanes of an operand read (columns 4 n + t) read two runs
@@ -578,7 +590,7 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
   uint16_t* const y = tab.y[z];
   const float* const v_parts = tab.v_parts[z];
   const long long v_stride = (long long)n_tokens * R;  // from one part to the next
-  const uint16_t *const vh = tab.vh[z], *const vl = tab.vl[z];
+  const uint16_t *const vh = tab.vh[z], *const vl = tab.vl[z], *const vr = tab.vr[z];
   const float* const undo = tab.undo[z];
   SGMV_TRACE_DECL
   SGMV_TRACE_POINT(0);
@@ -641,11 +653,16 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
           v0 = __float_as_int(sum0 * scale);
           v1 = __float_as_int(sum1 * scale);
         } else {
-          const uint16_t *const h = vh + (long long)row * R + vj, *const l = vl + (long long)row * R + vj;
+          const long long at = (long long)row * R + vj;
+          const auto joined = [&](int more) {
+            float low = decode1<DT>(vl[at + more]);
+            if constexpr (PARTS == 3) low += decode1<DT>(vr[at + more]);
+            return decode1<DT>(vh[at + more]) + low;
+          };
           const float u0 = std::is_same<DT, F16>::value ? undo[row] : 1.f;
           const float u1 = std::is_same<DT, F16>::value ? undo[two ? row + 1 : row] : 1.f;
-          v0 = __float_as_int((decode1<DT>(h[0]) + decode1<DT>(l[0])) * (scale * u0));
-          v1 = __float_as_int((decode1<DT>(h[second]) + decode1<DT>(l[second])) * (scale * u1));
+          v0 = __float_as_int(joined(0) * (scale * u0));
+          v1 = __float_as_int(joined(second) * (scale * u1));
         }
         float s0[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, s1[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
@@ -697,7 +714,7 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
         w[i] = buffer_load128(rB, stages && cg * 8 < ncols ? (uint32_t)((kq * KR + i) * h_out + cg * 8) * 2u : kOutOfRange);
 
       // ---- v: row n of the tile; rows past the segment read as zeros
-      uint4 v_hi[KSTEPS], v_lo[KSTEPS];
+      uint4 v_hi[KSTEPS], v_lo[KSTEPS], v_rest[KSTEPS];
       float un[4];
       // DIRECT: thread `tid` has quad `tid` of the block, whose partial sums are requested here, in front of y (the loads of
       // a wave return in order), and added up behind y's requests
@@ -730,6 +747,10 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
           for (int ks = 0; ks < KSTEPS; ++ks) {
             v_hi[ks] = buffer_load128(rH, (uint32_t)(n * R + ks * 32 + g * 8) * 2u);
             v_lo[ks] = buffer_load128(rL, (uint32_t)(n * R + ks * 32 + g * 8) * 2u);
+            if constexpr (PARTS == 3) {
+              const __amdgpu_buffer_rsrc_t rR = make_uniform_buffer(vr + (long long)r0 * R, (uint32_t)(rows * R) * 2u);
+              v_rest[ks] = buffer_load128(rR, (uint32_t)(n * R + ks * 32 + g * 8) * 2u);
+            }
           }
         }
 #pragma unroll
@@ -738,13 +759,13 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
       }
       auto place_v = [&]() {
         parts.add_to(sum, part, nparts);
-        uint2 high, low;
+        uint2 operand[2];
         float factor;
-        split_quad<DT, R>(sum, high, low, factor);
+        split_quad<DT, R>(sum, operand, factor);
         if (tid < Direct::kQuads) {
           const int k = tid % Direct::kPerRow * 4;
-          *reinterpret_cast<uint2*>(&vs[0][quad_row * Direct::kPitch + k]) = high;
-          *reinterpret_cast<uint2*>(&vs[1][quad_row * Direct::kPitch + k]) = low;
+          *reinterpret_cast<uint2*>(&vs[0][quad_row * Direct::kPitch + k]) = operand[0];
+          *reinterpret_cast<uint2*>(&vs[1][quad_row * Direct::kPitch + k]) = operand[1];
           if (std::is_same<DT, F16>::value && k == 0) undo_s[quad_row] = factor;
         }
       };
@@ -837,6 +858,10 @@ __global__ __launch_bounds__(256, 4) void expand_matrix_kernel(
                 uint4 bop[CT];
 #pragma unroll
                 for (int t = 0; t < CT; ++t) bop[t] = operand(j, ks * 4 + g, t);
+                if constexpr (PARTS == 3) {
+#pragma unroll
+                  for (int t = 0; t < CT; ++t) acc[t] = mfma16x16x32<DT>(v_rest[ks], bop[t], acc[t]);
+                }
 #pragma unroll
                 for (int t = 0; t < CT; ++t) acc[t] = mfma16x16x32<DT>(v_lo[ks], bop[t], acc[t]);
 #pragma unroll
@@ -932,7 +957,7 @@ hipError_t launch_shrink_matrix(const ShrinkArgs& a, hipStream_t st) {
   return a.bf16 ? launch_shrink_matrix_r<BF16>(a, st) : launch_shrink_matrix_r<F16>(a, st);
 }
 
-// The expands of n add-ons in one launch, in front of it the one that makes operand pairs of their v.
+// The expands of n add-ons in one launch, in front of it the one that makes operands of their v.
 template <class DT, int R>
 static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, bool direct, hipStream_t st) {
   const ExpandArgs& a = es[0];
@@ -943,15 +968,24 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, bool direc
     tab.v_parts[i] = fin.v_parts[i] = e.v_parts;
     tab.vh[i] = fin.vh[i] = e.vh;
     tab.vl[i] = fin.vl[i] = e.vl;
+    tab.vr[i] = fin.vr[i] = e.vr;
     tab.undo[i] = fin.undo[i] = e.undo;
     tab.y[i] = (uint16_t*)e.y;
     tab.A_ptrs[i] = (const uint16_t* const*)e.A_ptrs;
     tab.B_ptrs[i] = (const uint16_t* const*)e.B_ptrs;
   }
+  const bool three_parts = a.vr != nullptr;
+  if (three_parts && R != 64) return hipErrorInvalidValue;
   if (!direct) {
     const long long quads = (long long)a.n_tokens * (R / 4);
-    hipLaunchKernelGGL((finalize_v_kernel<DT, R>), dim3((unsigned)((quads + 255) / 256), (unsigned)n), dim3(256), 0, st, a.nparts,
-                       a.n_tokens, fin);
+    const auto finalize = [&](auto parts_tag) {
+      hipLaunchKernelGGL((finalize_v_kernel<DT, R, decltype(parts_tag)::value>), dim3((unsigned)((quads + 255) / 256), (unsigned)n),
+                         dim3(256), 0, st, a.nparts, a.n_tokens, fin);
+    };
+    if constexpr (R == 64) {
+      if (three_parts) finalize(std::integral_constant<int, 3>{});
+    }
+    if (!three_parts) finalize(std::integral_constant<int, 2>{});
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
@@ -969,18 +1003,24 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, bool direc
   const long long wgs = strips * blocks;
   const dim3 grid((unsigned)(wgs < kMostWorkgroups ? wgs : kMostWorkgroups), (unsigned)n,
                   (unsigned)((wgs + kMostWorkgroups - 1) / kMostWorkgroups));
-  const auto launch = [&](auto direct_tag) {
-    hipLaunchKernelGGL((expand_matrix_kernel<DT, R, decltype(direct_tag)::value>), grid, dim3(256), 0, st, a.seg_starts, a.n_segs,
+  const auto launch = [&](auto direct_tag, auto parts_tag) {
+    hipLaunchKernelGGL((expand_matrix_kernel<DT, R, decltype(direct_tag)::value, decltype(parts_tag)::value>), grid, dim3(256), 0, st, a.seg_starts, a.n_segs,
                        segments_per_block(a.n_segs, blocks), strips, few_rows, few, a.h_out, a.layer_off, a.scale, a.header,
                        tab, a.nparts, a.n_tokens);
   };
   if constexpr (R <= 16) {
     if (direct) {
-      launch(std::true_type{});
+      launch(std::true_type{}, std::integral_constant<int, 2>{});
       return hipGetLastError();
     }
   }
-  launch(std::false_type{});
+  if constexpr (R == 64) {
+    if (three_parts) {
+      launch(std::false_type{}, std::integral_constant<int, 3>{});
+      return hipGetLastError();
+    }
+  }
+  launch(std::false_type{}, std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 

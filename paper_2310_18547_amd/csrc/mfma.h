@@ -32,4 +32,14 @@ __device__ __forceinline__ void split16(float v, uint32_t& hi, uint32_t& lo) {
   lo = encode1<DT>(v - decode1<DT>((uint16_t)hi));
 }
 
+// The same as three parts, which together hold all 24 bits of v.  What is not finite is one part.
+template <class DT>
+__device__ __forceinline__ void split16(float v, uint32_t& hi, uint32_t& lo, uint32_t& rest) {
+  hi = encode1<DT>(v);
+  const float behind = v - decode1<DT>((uint16_t)hi);
+  const bool finite = fabsf(behind) < 3.0e38f;
+  lo = finite ? encode1<DT>(behind) : 0;
+  rest = finite ? encode1<DT>(behind - decode1<DT>((uint16_t)lo)) : 0;
+}
+
 }  // namespace sgmv

@@ -697,14 +697,14 @@ def test_slices_of_long_segments_are_a_power_of_two():
         assert rc == 0 and (plan.kernel, plan.slices) == (sg.KERNEL_MATRIX, slices)
 
 
-def test_joint_launches_of_rank_64_leave_v_in_the_precision_it_had():
-    # the MFMA kernels hold v as two 16-bit parts: they may stand in for the tile kernel, which does too, where its launches are at
-    # least two for every three add-ons, and not for the kernels that keep v in fp32
+def test_joint_launches_of_rank_64():
+    # the MFMA kernels where what is taken instead is at least two launches for every three add-ons
+    T, F, V, W, M = sg.KERNEL_TILE, sg.KERNEL_FUSED, sg.KERNEL_VECTOR, sg.KERNEL_WHOLE, sg.KERNEL_MATRIX
     for lens, hint, n_proj, h_in, h_out, one, joint in (
-            ([8] * 16, 8, 3, 4096, 4104, sg.KERNEL_TILE, sg.KERNEL_MATRIX), ([8] * 16, 8, 4, 4096, 4104, sg.KERNEL_TILE, sg.KERNEL_MATRIX),
-            ([4] * 100, 4, 2, 4096, 4104, sg.KERNEL_VECTOR, sg.KERNEL_VECTOR), ([30], 30, 3, 4096, 1608, sg.KERNEL_FUSED, sg.KERNEL_FUSED),
-            ([4] * 25, 0, 3, 2048, 1024, sg.KERNEL_FUSED, sg.KERNEL_FUSED), ([4] * 25, 0, 3, 512, 512, sg.KERNEL_WHOLE, sg.KERNEL_WHOLE),
-            ([7, 7, 7, 7, 2], 7, 8, 4160, 2048, sg.KERNEL_FUSED, sg.KERNEL_TILE), ([8, 4] * 6, 8, 8, 5120, 1024, sg.KERNEL_TILE, sg.KERNEL_TILE)):
+            ([8] * 16, 8, 3, 4096, 4104, T, M), ([8] * 16, 8, 4, 4096, 4104, T, M), ([4] * 100, 4, 2, 4096, 4104, V, M),
+            ([4] * 99 + [3], 4, 2, 4096, 4104, V, V), ([30], 30, 3, 4096, 1608, F, M), ([4] * 25, 0, 3, 2048, 1024, F, M),
+            ([4] * 25, 0, 3, 512, 512, W, M), ([9] * 5, 0, 4, 1736, 1024, F, F), ([10] * 5, 0, 4, 1736, 1024, F, M),
+            ([7, 7, 7, 7, 2], 7, 8, 4160, 2048, F, T), ([8, 4] * 6, 8, 8, 5120, 1024, T, T)):
         n = sum(lens)
         p = sg.make_problem(sg.F16, h_in, h_out, 64, 1, n, workspace=256, workspace_bytes=sg.sgmv_workspace_bytes_multi(n, 64, n_proj),
                             max_seg_len=hint, workspace_ready=1)
