@@ -209,6 +209,49 @@ bool matrix_direct(const sgmv_problem* p, int n_segs, int n_proj, int slices) {
   return p->r * slices <= 256 && sums * (workgroups > 1024 ? workgroups : 1024) <= (512LL << 10) * 1024;
 }
 
+// Add-ons of long segments under SGMV_PATH_AUTO: instead of `power`, choose_split_matrix's power of two, as many slices as give every compute
+// unit one workgroup and not more (`fill` of them would), because the units that get a second one decide when the launch ends: 2000 rows of
+// six segments, rank 16, 8192 wide (35 row blocks), whole add-on at 5 / 6 / 8 / 16 slices 25.7 / 25.1 / 27.3 / 27.5 us; 4814 rows at rank 64 (41
+// blocks of 128) 57.5 / 56.5 / 60.0 / 59.6; three add-ons of 2600 rows at rank 32 (22 blocks) at 4 / 8 / 16 45.5 / 40.7 / 44.3.  From
+// seven on only eight or sixteen (1400 rows, rank 16, 8192 wide, 8 / 10 / 12 / 16 slices 19.0 / 20.0 / 21.4 / 20.5).  Fewer than four leave too
+// few loads in flight (4814 rows, rank 16, 8192 wide, 4 / 6 / 8 / 16 slices 52.6 / 50.4 / 48.9 / 47.6), and `power` stays, as it does
+//  * for five and six up to rank 16 (2625 rows, 11008 -> 1024, rank 16, 5 / 16 slices 23.4 / 22.0), five at rank 32 on inputs wider than
+//    8192 (2335 rows, 11008 -> 13824, 5 / 16 slices 47.8 / 46.0), four at rank 8 from 8192 on (3535 rows, 8192 -> 5120, 4 / 16 slices 34.4 /
+//    32.8), four of add-ons that do not share their pass over x (`unshared`) and, at rank 64 or on inputs wider than 8192, four to six of more than eight
+//    segments: these are often many short ones beside a few long ones, and then more blocks than `fill` reckons (1686 rows of twelve, 11008 ->
+//    4096, rank 64, three add-ons, 4 / 8 slices 71.3 / 56.4);
+//  * for seven, which eight overfills, on inputs wider than 8192 and, where `power` is less than eight, up to 3072 (11008 -> 2048, 1921 rows, rank
+//    16, 8 / 16 slices 27.2 / 24.6; 1024 -> 824, 1124 rows, rank 64, three add-ons, 8 / 4 slices 20.1 / 17.9), unless the expand then adds the
+//    partial sums up itself (1863 rows, 3560 -> 1144, rank 16, 8 / 16 slices 12.3 / 14.2);
+//  * where a slice would be thinner than 192, while the units are few enough 128 (1312 rows, 1024 wide, rank 64, 6 / 4 slices 19.2 / 18.0; 1076 rows
+//    of 2048, rank 32, 16 / 8 slices 12.3 / 11.9; at rank 64, where `power` is four, 16 / 4 of 2000 13.1 / 15.3);
+//  * at rank 64 for more than sixteen where the units take 28 (454 rows, 13824 -> 5120, 31 / 16 slices 20.3 / 23.0).
+// Sixteen from fourteen on, up to rank 32 on inputs wider than 8192 from thirteen on, where half as many chunks one after the other outweigh a
+// second round (1755 rows, 11008 -> 2424, rank 32, three add-ons, fill 13.6, 8 / 16 slices 47.9 / 42.8).
+// 1712 points that this rule and the launch less behind it change, against `power` and three launches: 1.09 times as fast on average, seven
+// below 0.97, 0.93 at worst.
+int filling_slices(const sgmv_problem* p, int n_segs, int power, float fill, bool unshared, bool direct_at_eight) {
+  const bool wide = p->h_in > 8192;
+  const bool steady = n_segs <= 8 || (p->r < 64 && !wide);
+  int n = power;
+  if (fill >= (p->r <= 32 && wide ? 13.f : 14.f)) {
+    n = p->r == 64 && power > 16 && fill >= 28.f ? power : 16;
+    if (n > power && p->h_in < 16 * (p->r == 64 ? 128 : 192)) n = 8;
+  } else if (fill >= 8.f) {
+    n = 8;
+  } else if (fill >= 7.f) {
+    if (direct_at_eight || (power >= 8 ? !wide : p->h_in > 3072)) n = 8;
+  } else if (fill >= 6.f) {
+    if (p->r >= 32 && steady) n = 6;
+  } else if (fill >= 5.f) {
+    if (steady && (p->r == 64 || (p->r == 32 && !wide))) n = 5;
+  } else if (fill >= 4.f) {
+    if (steady && !unshared && (p->r > 8 || p->h_in < 8192)) n = 4;
+  }
+  if (n > power && n <= 8 && p->h_in < n * (fill >= 15.f ? 128 : 192)) n = power;
+  return n;
+}
+
 // Split-K shape of the MFMA shrink of n_proj add-ons: about kMatrixWaves waves in flight, a power of two
 // slices, so that a slice's workgroups (consecutive ids) meet on the same XCDs and its part of A_i in
 // their L2s (8192 wide, rank 16, 4814 rows, 8 / 11 / 16 slices: 18.6 / 19.9 / 17.4 us; the whole add-on to 4096, rank 16, 5120
@@ -217,29 +260,10 @@ bool matrix_direct(const sgmv_problem* p, int n_segs, int n_proj, int slices) {
 // written and read again, about half the bytes of one x, two thirds at most (11432 wide, rank 64, three add-ons of 724
 // rows, the whole call at 4 / 8 / 15 slices: 45.0 / 32.3 / 33.1 us; 3272 wide, 3254 rows, 2 / 4 / 13: 61.3 / 62.4 / 67.1).
 //
-// Add-ons of long segments under SGMV_PATH_AUTO: instead as many slices as give every compute unit one workgroup and not
-// more, because the units that get a second one decide when the launch ends: 2000 rows of six segments, rank 16, 8192 wide (35
-// row blocks), whole add-on at 5 / 6 / 8 / 16 slices 25.7 / 25.1 / 27.3 / 27.5 us; 4814 rows at rank 64 (41 blocks of 128) 57.5 /
-// 56.5 / 60.0 / 59.6; three add-ons of 2600 rows at rank 32 (22 blocks) at 4 / 8 / 16 45.5 / 40.7 / 44.3.  From eight on only
-// eight or sixteen (1400 rows, rank 16, 8192 wide, 8 / 10 / 12 / 16 slices 19.0 / 20.0 / 21.4 / 20.5).  Fewer than four leave too few
-// loads in flight (4814 rows, rank 16, 8192 wide, 4 / 6 / 8 / 16 slices 52.6 / 50.4 / 48.9 / 47.6), and the count above stays, as it does
-//  * for five or six up to rank 16 (2625 rows, 11008 -> 1024, rank 16, 5 / 16 slices 23.4 / 22.0), and five at rank 32 on inputs wider than
-//    8192 (2335 rows, 11008 -> 13824, 5 / 16 slices 47.8 / 46.0), whose last chunks are the longer the fewer they are;
-//  * for four at rank 8 from 8192 on (3535 rows, 8192 -> 5120, 4 / 16 slices 34.4 / 32.8), and for four and five beyond eight segments,
-//    which are often many short ones beside a few long ones and then more blocks than this reckons (1686 rows of twelve, 11008 -> 4096,
-//    rank 64, three add-ons, 4 / 8 slices 71.3 / 56.4);
-//  * for seven, which eight overfills: 1921 rows, 11008 -> 2048, rank 16, 8 / 16 slices 27.2 / 24.6; 1124 rows, 1024 -> 824, rank 64, three
-//    add-ons, 8 / 4 slices 20.1 / 17.9; but where the count above is four or less on inputs wider than 4096, eight it is (1.11 times as fast
-//    on average);
-//  * where a slice would have less than 256 of the input, two chunks (1312 rows, 1024 wide, rank 64, 6 / 4 slices 19.2 / 18.0);
-//  * at rank 64 for more than sixteen (454 rows, 13824 -> 5120, 31 / 16 slices 20.3 / 23.0).
-// Sixteen from fourteen on, on inputs wider than 8192 from twelve on, where half as many chunks one after the other outweigh a
-// second round (1755 rows, 11008 -> 2424, rank 32, three add-ons 13.6: 8 / 16 slices 47.9 / 42.8).  1712 points whose count or launches
-// follow from these rules, against the count above and three launches: 1.08 times as fast on average, four below 0.97, 0.93 at worst.
-// Short segments whose partial sums the expand adds up itself: eight, in small batches on wide inputs sixteen (60 of 8 rows, rank 16, 4096 wide,
-// 8 / 16 slices 12.7 / 14.2; 20 of 20 rows, 8192 wide, 14.6 / 13.9), or the count above and three launches where sixteen are too many to be
-// added up there (three add-ons of 788 rows, 11352 -> 1320, rank 16, 8 / 16 slices 31.0 / 25.9), and where that count is more than sixteen for
-// three add-ons of rank 16 (462 rows of six, 11008 -> 11008, 32 / 16 slices 27.6 / 30.2).
+// Add-ons on long segments: filling_slices.  On short segments whose partial sums the expand adds up itself: eight, in small batches on wide inputs
+// sixteen (60 of 8 rows, rank 16, 4096 wide, 8 / 16 slices 12.7 / 14.2; 20 of 20 rows, 8192 wide, 14.6 / 13.9), or the power of two and three
+// launches where sixteen are too many to be added up there (three add-ons of 788 rows, 11352 -> 1320, rank 16, 8 / 16 slices 31.0 /
+// 25.9), and where it is more than sixteen for three add-ons of rank 16 (462 rows of six, 11008 -> 11008, 32 / 16 slices 27.6 / 30.2).
 MatrixSplit choose_split_matrix(const sgmv_problem* p, int n_segs, int n_proj, bool same_x) {
   const int cap = split_cap(p->n_tokens);
   const int most = p->h_in / 128 > 0 ? p->h_in / 128 : 1;  // keep slices of at least one chunk
@@ -263,21 +287,11 @@ MatrixSplit choose_split_matrix(const sgmv_problem* p, int n_segs, int n_proj, b
       // blocks: 5 / 6 slices 138 / 149 us); of a short segment's block one wave of four works
       const bool is_long = p->n_tokens >= (long long)n_segs * rows;
       const float last = is_long ? 0.5f * n_segs + 0.6f * sqrtf((float)n_segs) : 0.25f * n_segs;
-      const int fill = (int)(compute_units() / (((float)p->n_tokens / rows + last) * (shared ? 1 : n_proj)));
+      const float fill = compute_units() / (((float)p->n_tokens / rows + last) * (shared ? 1 : n_proj));
       if (is_long) {
-        int n = s;
-        if (fill >= (p->h_in > 8192 ? 12 : 14))
-          n = p->r == 64 && s > 16 ? s : 16;
-        else if (fill >= 8 || (fill == 7 && s < 8 && p->h_in > 4096))
-          n = 8;
-        else if (p->r >= 32 && fill == 6)
-          n = 6;
-        else if (n_segs <= 8 && (fill == 4 ? p->r > 8 || p->h_in < 8192 : fill == 5 && (p->r == 64 || (p->r == 32 && p->h_in <= 8192))))
-          n = fill;
-        while (n > s && n * 256 > p->h_in) n = n >= 8 ? n / 2 : s;
-        s = n;
+        s = filling_slices(p, n_segs, s, fill, !shared && n_proj > 1, matrix_direct(p, n_segs, n_proj, within(8)));
       } else if ((s <= 16 || p->r * n_proj <= 32 || p->h_in <= 8192) && matrix_direct(p, n_segs, n_proj, within(8))) {
-        if (fill < 14 || p->h_in <= 4096)
+        if (fill < 14.f || p->h_in <= 4096)
           s = 8;
         else if (matrix_direct(p, n_segs, n_proj, within(16)))
           s = 16;

@@ -732,15 +732,19 @@ def test_slices_and_launches_of_add_ons_on_long_segments():
     # (rank, add-ons, h_in, h_out, rows, segments, slices, launches) on both sides of the lines; 256 compute units over the row blocks,
     # of 64 rows (128 beyond 32 columns), half a block and 0.6 sqrt(segments) more per segment, give the slices
     for r, P, h_in, h_out, rows, n, slices, launches in (
-            (16, 1, 8192, 4096, 1960, 8, 16, 3), (16, 1, 8192, 4096, 1700, 7, 8, 2),        # 7.0: the power of two; 8.0
+            (16, 1, 8200, 4096, 1960, 8, 16, 3), (16, 1, 8192, 4096, 1960, 8, 8, 3),        # 7.0 on a wide input; on another
+            (16, 1, 8200, 4096, 1800, 8, 8, 2), (16, 1, 8192, 4096, 1700, 7, 8, 2),         # 7.6 and added up in the expand; 8.0
             (16, 1, 8192, 4096, 870, 7, 8, 2), (16, 1, 8192, 4096, 800, 7, 16, 2),          # 13.7; 14.5
             (32, 1, 11008, 2352, 830, 8, 16, 3), (32, 1, 11008, 2352, 1100, 8, 8, 3),       # 13.7 on a wide input; 11.2
-            (64, 1, 13824, 5120, 450, 2, 31, 3), (64, 1, 8192, 5120, 450, 2, 16, 3),        # more than sixteen where the rank has it
-            (64, 1, 1024, 4096, 3500, 6, 4, 3), (64, 1, 2048, 4096, 3500, 6, 8, 3),         # slices of 256 at least
+            (64, 1, 13824, 5120, 450, 2, 31, 3), (64, 1, 13824, 5120, 1650, 6, 16, 3),      # more than sixteen: 47; 14.7
+            (64, 1, 1528, 4096, 3500, 6, 4, 3), (64, 1, 1536, 4096, 3500, 6, 8, 3),         # 8.05: slices of 192 at least ...
+            (64, 1, 1024, 4096, 1400, 6, 8, 3), (64, 1, 2048, 4096, 1400, 6, 16, 3),        # 16.6: of 128
+            (32, 1, 2048, 4096, 700, 6, 8, 3), (32, 1, 3072, 4096, 700, 6, 16, 3),          # 16.6: sixteen of 192
             (64, 3, 1024, 824, 1124, 4, 4, 3), (64, 3, 8192, 824, 1124, 4, 8, 3),           # 7.1: where the power of two is four
             (64, 1, 8192, 8192, 4300, 8, 6, 3), (64, 1, 8192, 8192, 5000, 8, 5, 3),         # 6.4; 5.7
             (16, 1, 8192, 4096, 4000, 9, 16, 3), (16, 1, 4096, 4096, 3300, 8, 4, 3),        # 3.7; 4.4
-            (64, 1, 8192, 8192, 4700, 12, 16, 3), (8, 1, 8192, 4096, 3300, 8, 16, 3),        # 5.6 but twelve segments; 4.4 at rank 8
+            (64, 1, 8192, 8192, 4700, 12, 16, 3), (8, 1, 8192, 4096, 3300, 8, 16, 3),       # 5.6 but twelve segments; 4.4 at rank 8
+            (64, 3, 11008, 4096, 1900, 6, 8, 3),                                            # 4.4 without sharing the pass over x
             (16, 1, 4096, 4096, 480, 60, 8, 2), (16, 1, 8192, 4096, 400, 20, 16, 2),        # short segments
             (16, 1, 8192, 4096, 480, 105, 16, 3), (16, 3, 11008, 1320, 790, 9, 16, 3),      # beyond what the expand adds up
             (16, 3, 11008, 1320, 300, 6, 32, 3), (8, 3, 11008, 1320, 300, 6, 16, 2)):
