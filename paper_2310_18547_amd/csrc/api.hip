@@ -1484,7 +1484,10 @@ int sgmv_add_lora_multi(const sgmv_problem* p, int32_t n_proj, void* const* ys,
         sa.As[i] = A_ptrs[first + i];
         if (i > 0) sa.partials_of[i] = reinterpret_cast<float*>(extra + (size_t)(i - 1) * (parts + ops));
       }
-      const MatrixSplit m = choose_split_matrix(p, n_segs, count, sa.same_x);
+      MatrixSplit m = choose_split_matrix(p, n_segs, count, sa.same_x);
+      // two launches or three as sgmv_plan_add_lora tells, which does not see the inputs (slices of inputs of their own are fewer: what
+      // the expand adds up of one x it can add up of several)
+      if (!sa.same_x) m.direct = choose_split_matrix(p, n_segs, count, true).direct;
       sa.ksplit = m.ksplit;
       sa.kslice = m.kslice;
       if (launch_shrink_matrix(sa, st) != hipSuccess) return SGMV_ERR_LAUNCH;

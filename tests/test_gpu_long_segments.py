@@ -1,4 +1,6 @@
 """The MFMA kernels where their lists of work have edges, and the rounding of bfloat16 stores."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -65,6 +67,34 @@ def test_expand_that_adds_the_partial_sums_up(dtype, r, P, h_in, h_out, slices, 
                               [d.B_ptrs for d in ds], ds[0].seg_starts, n, 1, scale)
     for k, w in enumerate(ws):
         assert_parity(ds[k].y_bits(), oracle.run_workload(w, layer_idx=1, n_threads=8), dtype, f"add-on {k} of {P}")
+
+
+# The launches of a call are those of its plan, whichever of the add-ons read one x (900 rows of inputs of their own take fewer slices).
+@pytest.mark.parametrize("r,P,one_x", [(16, 3, True), (16, 3, False), (8, 2, False), (16, 4, False), (64, 3, False)])
+def test_launches_are_those_of_the_plan(r, P, one_x):
+    from paper_2310_18547_amd import binding as B
+    lens = [520, 180, 20, 180]
+    ws = [wl.custom(lens, 4096, 4096, r, "bf16", seed=70 + k, scale=0.5) for k in range(P)]
+    if one_x:
+        for w in ws[1:]:
+            w.x[...] = ws[0].x
+    ds = [_dev(w, n_proj=P) for w in ws]
+    plan = B.sgmv_plan_add_lora(ds[0].problem, len(lens), P)
+    assert plan.kernel == B.KERNEL_MATRIX
+    def call(stream=None):
+        B.sgmv_add_lora_multi(ds[0].problem, [d.y[0] for d in ds], [(ds[0] if one_x else d).x[0] for d in ds], [d.A_ptrs for d in ds],
+                              [d.B_ptrs for d in ds], ds[0].seg_starts, len(lens), 0, 0.5, stream)
+    call()                                              # kernels loaded
+    for k, w in enumerate(ws):
+        assert_parity(ds[k].y_bits(), oracle.run_workload(w, n_threads=8), "bf16", f"add-on {k} of {P}")
+    graph, nodes = ctypes.c_void_p(), ctypes.c_size_t()
+    stream = torch.cuda.Stream(device="cuda:0")
+    assert B.lib.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), 1) == 0
+    call(stream.cuda_stream)
+    assert B.lib.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)) == 0
+    assert B.lib.hipGraphGetNodes(graph, None, ctypes.byref(nodes)) == 0
+    assert B.lib.hipGraphDestroy(graph) == 0
+    assert nodes.value == plan.launches
 
 
 # Every kernel that stores y, by path and segment lengths: with one term per sum the fp32 result is exact, so that y is
