@@ -728,14 +728,15 @@ bool choose_fused_pairs(const sgmv_problem* p, int n_segs, FusedArgs* f) {
 //    pairs' places but one block of the tile kernel, which takes several for more than sixteen): at rank 16 segments of 3 to 48 rows (9992 ->
 //    1024, 101 rows of 51 10.4 / 13.8, 110 rows of 23 10.4 / 12.2; 253 such points 1.08 times as fast on the tile kernel, 147 others
 //    1.24 times on pairs, 0.99 at least: 13824 -> 2048, 51 x 2 rows 12.5 / 11.1), at rank 8, where the tile kernel has five slices and more,
-//    of 5 to 32 rows (9992 -> 1024, 116 rows of 20 8.1 / 9.7; 83 points 1.02 times on the tile kernel, 317 others 1.28 times on pairs).
+//    of 5 to 32 rows, more than three and a half on average (9992 -> 1024, 116 rows of 20 8.1 / 9.7; 74 points 1.02 times on the tile
+//    kernel, 326 others 1.27 times on pairs: 11008 -> 4096, 101 rows of 47, in a layer of seven projections 40.9 / 36.5).
 bool choose_add_on_pairs(const sgmv_problem* p, int n_segs, int tile_slices, FusedArgs* f) {
   if (p->r == 8 ? tile_slices == 6 || tile_slices == 7 : tile_slices >= 6 || p->n_tokens > 128) return false;
   if (!choose_fused_pairs(p, n_segs, f) || f->cslice > (p->r == 16 ? 1024 : 2048)) return false;
   const int units = limits().fused_workgroups;
   if (p->r == 32) return (long long)f->S * f->items <= units;
   if (tile_slices == 0 || f->S * fused_grid_items(f->items) <= 2 * units) return true;
-  if (p->r == 8) return tile_slices < 5 || p->max_seg_len <= 4 || p->max_seg_len > 32;
+  if (p->r == 8) return tile_slices < 5 || p->max_seg_len <= 4 || p->max_seg_len > 32 || 2LL * p->n_tokens <= 7LL * n_segs;
   return p->max_seg_len > 48 || (p->max_seg_len == 2 && 4LL * p->n_tokens > 7LL * n_segs);
 }
 
