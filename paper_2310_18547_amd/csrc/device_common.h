@@ -219,7 +219,7 @@ __device__ __forceinline__ void buffer_store128(__amdgpu_buffer_rsrc_t rsrc, uin
 // rows of the batch, each looking its segment up (kPerRow); and whether the weights are read past the
 // caches (non-temporal, kStreamed), which pays where a launch reads many of them once (launch.h,
 // stream_weights); and whether more than one workgroup per compute unit has to be resident (kCrowded).
-// kPaired, with kPerRow: two rows of one segment to an item (launch.h, pair_rows).
+// kPaired, with kPerRow: two rows of one segment to an item (launch.h, pair_places).
 constexpr int kPerSegment = 0, kPerRow = 1, kStreamed = 2, kCrowded = 4, kPaired = 8;
 constexpr bool by_row(int mode) { return (mode & kPerRow) != 0; }
 constexpr bool paired(int mode) { return (mode & kPaired) != 0; }

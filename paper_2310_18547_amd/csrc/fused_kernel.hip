@@ -71,6 +71,7 @@ __device__ __forceinline__ void add_lora_fused_body(
   constexpr int CPW = NT / G;  // 8-column chunks per pass
   constexpr int JL = R / G;    // weight rows per lane in the expand phase
   static_assert(JL >= 1 && JL <= 16, "bad lane-group count");
+  static_assert(RB == 1 || RB == 2, "a row or a pair");
   static_assert(kMaxKSlice / 8 == NT, "one 128-bit x chunk per lane and row");
   // Two lane groups sit in neighbouring lanes of a wave (lane group = lane % 2) and add their
   // sums with cross-lane moves: no LDS, no barrier, 0.2 us less behind the hand-off (B = 64:
@@ -254,12 +255,10 @@ __device__ __forceinline__ void add_lora_fused_body(
         unpack8<DT>(a[u], af);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-          if (RB <= 2 || rb < nrows) {
-            const float xraw = decode1<DT>(xs[rb][kk]);
-            const float xv = (q < nchunks) ? xraw : 0.f;
+          const float xraw = decode1<DT>(xs[rb][kk]);
+          const float xv = (q < nchunks) ? xraw : 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[rb][e] = fmaf(xv, af[e], acc[rb][e]);
-          }
+          for (int e = 0; e < 8; ++e) acc[rb][e] = fmaf(xv, af[e], acc[rb][e]);
         }
       }
     }
@@ -268,15 +267,13 @@ __device__ __forceinline__ void add_lora_fused_body(
     // in LDS, and the exchange wave adds the sixteen rows of the workgroup in a fixed order.
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      if (RB <= 2 || rb < nrows) {
-        float d[8];
+      float d[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) d[e] = row_sum_same_group<LPR>(acc[rb][e]);
-        if ((lane & 15) < LPR) {
-          float* dst = &red[wave * 4 + (lane >> 4)][rb][(lane & 15) * 8];
-          *reinterpret_cast<float4*>(dst) = make_float4(d[0], d[1], d[2], d[3]);
-          *reinterpret_cast<float4*>(dst + 4) = make_float4(d[4], d[5], d[6], d[7]);
-        }
+      for (int e = 0; e < 8; ++e) d[e] = row_sum_same_group<LPR>(acc[rb][e]);
+      if ((lane & 15) < LPR) {
+        float* dst = &red[wave * 4 + (lane >> 4)][rb][(lane & 15) * 8];
+        *reinterpret_cast<float4*>(dst) = make_float4(d[0], d[1], d[2], d[3]);
+        *reinterpret_cast<float4*>(dst + 4) = make_float4(d[4], d[5], d[6], d[7]);
       }
     }
     SGMV_TRACE_POINT(3);
@@ -322,11 +319,9 @@ __device__ __forceinline__ void add_lora_fused_body(
         unpack8<DT>(b[j], bf);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-          if (RB <= 2 || rb < nrows) {
-            const float vj = vs[rb][cg * JL + j];
+          const float vj = vs[rb][cg * JL + j];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[rb][e] = fmaf(vj, bf[e], acc[rb][e]);
-          }
+          for (int e = 0; e < 8; ++e) acc[rb][e] = fmaf(vj, bf[e], acc[rb][e]);
         }
       }
       if (INTRA) {
@@ -340,11 +335,9 @@ __device__ __forceinline__ void add_lora_fused_body(
         if (cg > 0) {
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb) {
-            if (RB <= 2 || rb < nrows) {
-              float* dst = &ex[(((cg - 1) * RB + rb) * CPW + cc) * 8];
-              *reinterpret_cast<float4*>(dst) = make_float4(acc[rb][0], acc[rb][1], acc[rb][2], acc[rb][3]);
-              *reinterpret_cast<float4*>(dst + 4) = make_float4(acc[rb][4], acc[rb][5], acc[rb][6], acc[rb][7]);
-            }
+            float* dst = &ex[(((cg - 1) * RB + rb) * CPW + cc) * 8];
+            *reinterpret_cast<float4*>(dst) = make_float4(acc[rb][0], acc[rb][1], acc[rb][2], acc[rb][3]);
+            *reinterpret_cast<float4*>(dst + 4) = make_float4(acc[rb][4], acc[rb][5], acc[rb][6], acc[rb][7]);
           }
         }
         lds_barrier();  // (g) ex filled
@@ -353,13 +346,11 @@ __device__ __forceinline__ void add_lora_fused_body(
           for (int g = 1; g < G; ++g) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-              if (RB <= 2 || rb < nrows) {
-                const float* srcp = &ex[(((g - 1) * RB + rb) * CPW + cc) * 8];
-                const float4 p0 = *reinterpret_cast<const float4*>(srcp);
-                const float4 p1 = *reinterpret_cast<const float4*>(srcp + 4);
-                acc[rb][0] += p0.x; acc[rb][1] += p0.y; acc[rb][2] += p0.z; acc[rb][3] += p0.w;
-                acc[rb][4] += p1.x; acc[rb][5] += p1.y; acc[rb][6] += p1.z; acc[rb][7] += p1.w;
-              }
+              const float* srcp = &ex[(((g - 1) * RB + rb) * CPW + cc) * 8];
+              const float4 p0 = *reinterpret_cast<const float4*>(srcp);
+              const float4 p1 = *reinterpret_cast<const float4*>(srcp + 4);
+              acc[rb][0] += p0.x; acc[rb][1] += p0.y; acc[rb][2] += p0.z; acc[rb][3] += p0.w;
+              acc[rb][4] += p1.x; acc[rb][5] += p1.y; acc[rb][6] += p1.z; acc[rb][7] += p1.w;
             }
           }
         }
@@ -505,7 +496,8 @@ template <class DT, int R, int G>
 static hipError_t launch_fused_rb(const FusedArgs& a, hipStream_t st) {
   const bool streamed = stream_weights(a.by_rows, a.n_tokens, a.n_segs, a.r, (long long)a.h_in + a.h_out);
   if (a.paired) {
-    if constexpr (R <= 32)
+    // single add-ons, whose lane groups are at most two up to rank 16, at rank 16 on column slices of a pass with two (choose_add_on_pairs)
+    if constexpr ((R == 8 && G <= 2) || (R == 16 && G == 2) || R == 32)
       return streamed ? launch_fused_t<DT, R, G, kPerRow | kPaired | kStreamed>(a, st) : launch_fused_t<DT, R, G, kPerRow | kPaired>(a, st);
     else
       return hipErrorInvalidValue;
