@@ -69,6 +69,20 @@ def test_expand_that_adds_the_partial_sums_up(dtype, r, P, h_in, h_out, slices, 
         assert_parity(ds[k].y_bits(), oracle.run_workload(w, layer_idx=1, n_threads=8), dtype, f"add-on {k} of {P}")
 
 
+# The same at rank 8 where segments of up to four rows are strips, three and four as two pairs (63 segments to 8200 columns, 315 strips),
+# the split-K factor the library's own.
+@pytest.mark.parametrize("dtype,h_in", [("f16", 4104), ("bf16", 8192)])
+def test_strips_of_three_and_four_rows_add_the_partial_sums_up(dtype, h_in):
+    from paper_2310_18547_amd import binding as B
+    lens = [3, 4, 1, 2, 4, 3, 0, 150] + [4, 3, 1, 2, 3] * 11
+    w = wl.custom(lens, h_in, 8200, 8, dtype, seed=31, num_layers=2, scale=0.5, seg_adapter=[-1 if i == 4 else i % 9 for i in range(len(lens))])
+    d = _dev(w)
+    plan = B.sgmv_plan_add_lora(d.problem, len(lens), 1)
+    assert len(lens) == 63 and (plan.kernel, plan.launches) == (B.KERNEL_MATRIX, 2)
+    d.add_lora(1)
+    assert_parity(d.y_bits(), oracle.run_workload(w, layer_idx=1, n_threads=8), dtype, "strips")
+
+
 # The launches of a call are those of its plan, whichever of the add-ons read one x (900 rows of inputs of their own take fewer slices).
 @pytest.mark.parametrize("r,P,one_x", [(16, 3, True), (16, 3, False), (8, 2, False), (16, 4, False), (64, 3, False)])
 def test_launches_are_those_of_the_plan(r, P, one_x):

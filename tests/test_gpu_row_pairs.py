@@ -28,7 +28,11 @@ def _is_paired(plan, w, slices):
 @pytest.mark.parametrize("dtype,lens,h_in,h_out,r,slices", [
     ("f16", MIXED, 11008, 520, 8, 8), ("bf16", MIXED, 9992, 2056, 8, 8), ("f16", [2] * 64, 11008, 4104, 16, 8),
     ("bf16", [2, 2, 1, 3] * 16, 11008, 8192, 16, 8), ("f16", MANY, 11000, 264, 8, 8), ("bf16", [50, 19] + [3, 0, 2, 1] * 4 + [3], 6152, 4096, 32, 4),
-    ("f16", [50, 19] + [3, 0, 2, 1] * 4 + [3], 5120, 1032, 32, 4), ("bf16", [200] + [0, 7, 1, 3, 1, 2] * 4, 8192, 1024, 8, 4)])
+    ("f16", [50, 19] + [3, 0, 2, 1] * 4 + [3], 5120, 1032, 32, 4), ("bf16", [200] + [0, 7, 1, 3, 1, 2] * 4, 8192, 1024, 8, 4),
+    # rank 8 with one lane group (slices of more than 1024 columns), rank 32 with eight and with two passes over B_i
+    ("f16", [200] + [0, 7, 1, 3, 1, 2] * 4, 8192, 8192, 8, 4), ("bf16", MIXED, 11008, 11000, 8, 8),
+    ("bf16", [50, 19] + [3, 0, 2, 1] * 4 + [3], 5120, 1024, 32, 4), ("f16", [50, 19] + [3, 0, 2, 1] * 4 + [3], 8192, 8192, 32, 4),
+    ("bf16", [50, 19] + [3, 0, 2, 1] * 4 + [3], 8192, 5000, 32, 4)])
 def test_add_on(dtype, lens, h_in, h_out, r, slices):
     from paper_2310_18547_amd import binding as B
     w = _workload(lens, h_in, h_out, r, dtype)
@@ -56,3 +60,33 @@ def test_shrink(dtype, lens, h_in, r, slices):
     ref = oracle.run_workload(w, op="shrink", layer_idx=1, v=np.ones((w.n_tokens, r), np.float32), n_threads=8)
     assert np.all(np.abs(v.cpu().numpy() - ref) <= 2e-3 + 2e-2 * np.abs(ref))
     assert d.check() == 0
+
+
+# The bounded wait, forced from the host: workgroup 0 tags its partial sums with a generation that its neighbours do not expect, so the
+# first pair is given up: both its rows stay as they were, all others are finished.
+@pytest.mark.parametrize("op", ["add_lora", "shrink"])
+def test_a_pair_that_is_given_up_stays_as_it_was(op):
+    from paper_2310_18547_amd import binding as B
+    lens = [3, 48] + [3, 0, 2, 1] * 7 + [3]                        # 96 rows
+    w = _workload(lens, 6152, 4096, 32, "f16") if op == "add_lora" else _workload([3, 56] + lens[2:], 11008, 64, 8, "f16")
+    d = _dev(w, spin_limit=5000)
+    plan = (B.sgmv_plan_add_lora(d.problem, w.n_segs, 1) if op == "add_lora" else B.sgmv_plan_shrink(d.problem, w.n_segs))
+    assert _is_paired(plan, w, 4 if op == "add_lora" else 8)
+    v0 = np.full((w.n_tokens, w.r), 3.0, np.float32)
+    ref = oracle.run_workload(w, layer_idx=1, n_threads=8) if op == "add_lora" else oracle.run_workload(w, op="shrink", layer_idx=1, v=v0.copy())
+    v = torch.from_numpy(v0.copy()).to("cuda:0")
+    d.workspace[0:4].view(torch.int32).fill_(77)
+    torch.cuda.synchronize()
+    if op == "add_lora":
+        d.add_lora(1)
+    else:
+        d.shrink(v, 1)
+    assert d.check() == 8                                          # SGMV_ERR_TIMEOUT
+    if op == "add_lora":
+        got = d.y_bits()
+        assert np.array_equal(got[:2], w.y0[:2])
+        assert_parity(got[2:], ref[2:], "f16", "the other rows")
+    else:
+        got = v.cpu().numpy()
+        assert np.all(got[:2] == 3.0)
+        assert np.all(np.abs(got[2:] - ref[2:]) <= 2e-3 + 2e-2 * np.abs(ref[2:]))
