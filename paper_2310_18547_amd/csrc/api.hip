@@ -692,7 +692,8 @@ ExpandArgs make_expand(const sgmv_problem* p, void* y, const float* v_parts, int
   a.B_ptrs = B_ptrs;
   a.seg_starts = seg_starts;
   a.scale = scale;
-  a.vh = a.vl = a.vr = nullptr;
+  a.three_parts = false;
+  a.vh = a.vl = nullptr;
   a.undo = nullptr;
   a.header = nullptr;
   a.by_rows = false;
@@ -1057,7 +1058,7 @@ int plan_multi(const sgmv_problem* p, int n_segs, int n_proj, FusedArgs* f, Tile
 
 // Add-ons of rank 64 that plan_multi gives several launches (`kernel`, `t`): the MFMA kernels, three launches for three of them,
 // from four rows per segment on.  Their second product then takes v as three 16-bit parts, all 24 bits of it, as the hand-off and vector
-// kernels do, whose calls these mostly are (ExpandArgs::vr; two parts give y a relative error of 4.5e-3 in binary16 where v is about 2^-18).
+// kernels do, whose calls these mostly are (ExpandArgs::three_parts; two parts give y a relative error of 4.5e-3 in binary16 where v is about 2^-18).
 // Measured, us, what was taken before / these, 24 to 400 rows, two to eight add-ons, 256 to 13824 wide, by the launches that were taken
 // before (vector kernels two per add-on) to the groups of three:
 //  * at least twice as many, 1055 points: 1.47 times as fast on average, six below 0.97, 0.90 at worst; four add-ons of the hand-off
@@ -1499,8 +1500,7 @@ int sgmv_add_lora_multi(const sgmv_problem* p, int32_t n_proj, void* const* ys,
         Scratch own = sc;
         if (i > 0) own.operands = extra + (size_t)(i - 1) * (parts + ops) + parts;
         set_operands(&es[i], own, p->n_tokens, p->r);
-        if (joint_matrix)  // behind the last slice's partial sums (multi_takes_matrix: there is room)
-          es[i].vr = reinterpret_cast<uint16_t*>(sa.partials_of[i] + (size_t)m.ksplit * p->n_tokens * p->r);
+        es[i].three_parts = joint_matrix;
       }
       if (launch_expand_matrix(es, count, m.direct, st) != hipSuccess) return SGMV_ERR_LAUNCH;
     }

@@ -64,10 +64,11 @@ struct ExpandArgs {
   const void* const* B_ptrs;
   const int32_t* seg_starts;
   float scale;
-  // MFMA path only: 16-bit operands of v, two parts or (vr not nullptr, rank 64) three, and the per-row range factor (workspace)
+  // MFMA path only: 16-bit operands of v, two parts or (rank 64) three, the third behind the partial sums, half a slice of them, and
+  // the per-row range factor (workspace)
+  bool three_parts;
   uint16_t* vh;
   uint16_t* vl;
-  uint16_t* vr;
   float* undo;
   unsigned long long* header;// workspace header or nullptr (only trace builds look at it)
 };

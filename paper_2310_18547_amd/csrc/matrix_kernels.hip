@@ -443,17 +443,22 @@ __global__ __launch_bounds__((64 * ShrinkShape<R, P>::kWaves), 4) void shrink_st
 // ---------------------------------------------------------------- expand
 
 // v[row][k] = sum over the split-K parts (ascending), written out as the two or three 16-bit
-// operands the expand kernel feeds to the matrix cores: vh, vl and vr [n_tokens][R] 16-bit,
-// undo [n_tokens] fp32 (split_quad).  One thread handles four consecutive k of a row;
+// operands the expand kernel feeds to the matrix cores: vh, vl [n_tokens][R] 16-bit, the third likewise behind
+// the partial sums (third_part), undo [n_tokens] fp32 (split_quad).  One thread handles four consecutive k of a row;
 // the kernel is one memory latency long.
 // blockIdx.y is the add-on.
 struct FinalizeTable {
   const float* v_parts[kSharedShrinkMost];
   uint16_t* vh[kSharedShrinkMost];
   uint16_t* vl[kSharedShrinkMost];
-  uint16_t* vr[kSharedShrinkMost];
   float* undo[kSharedShrinkMost];
 };
+// (A pointer of its own in the kernels' arguments moves others to another cache line, which every workgroup waits for: 4814
+// rows, rank 16, four calls of 8192 -> 8192 204.2 -> 205.4 us.)
+template <int R>
+__device__ __forceinline__ uint16_t* third_part(const float* v_parts, int nparts, int n_tokens) {
+  return reinterpret_cast<uint16_t*>(const_cast<float*>(v_parts + nparts * ((long long)n_tokens * R)));
+}
 template <class DT, int R, int PARTS>
 __global__ __launch_bounds__(256) void finalize_v_kernel(int nparts, int n_tokens, FinalizeTable tab) {
   constexpr int GPR = R / 4;  // threads per row
@@ -485,7 +490,7 @@ __global__ __launch_bounds__(256) void finalize_v_kernel(int nparts, int n_token
   if (live) {
     *reinterpret_cast<uint2*>(tab.vh[z] + e0) = part[0];
     *reinterpret_cast<uint2*>(tab.vl[z] + e0) = part[1];
-    if constexpr (PARTS == 3) *reinterpret_cast<uint2*>(tab.vr[z] + e0) = part[2];
+    if constexpr (PARTS == 3) *reinterpret_cast<uint2*>(third_part<R>(tab.v_parts[z], nparts, n_tokens) + e0) = part[2];
     if (it % GPR == 0) tab.undo[z][it / GPR] = undo;
   }
 }
@@ -505,11 +510,10 @@ struct ExpandTable {
   uint16_t* y[kSharedShrinkMost];
   const uint16_t* vh[kSharedShrinkMost];
   const uint16_t* vl[kSharedShrinkMost];
-  const uint16_t* vr[kSharedShrinkMost];  // PARTS = 3
   const float* undo[kSharedShrinkMost];
   const uint16_t* const* A_ptrs[kSharedShrinkMost];  // may be nullptr
   const uint16_t* const* B_ptrs[kSharedShrinkMost];
-  const float* v_parts[kSharedShrinkMost];  // DIRECT; else vh, vl, vr and undo, which finalize_v_kernel made of them
+  const float* v_parts[kSharedShrinkMost];  // DIRECT; else vh, vl and undo, which finalize_v_kernel made of them
 };
 
 // grid = (items, add-ons, further items); v comes as the partial sums (DIRECT) or as finalize_v_kernel's operands.  The list of items: for a segment
@@ -590,7 +594,8 @@ __global__ __launch_bounds__(256, PARTS == 3 ? 3 : 4) void expand_matrix_kernel(
   uint16_t* const y = tab.y[z];
   const float* const v_parts = tab.v_parts[z];
   const long long v_stride = (long long)n_tokens * R;  // from one part to the next
-  const uint16_t *const vh = tab.vh[z], *const vl = tab.vl[z], *const vr = tab.vr[z];
+  const uint16_t *const vh = tab.vh[z], *const vl = tab.vl[z];
+  const uint16_t* const vr = PARTS == 3 ? third_part<R>(v_parts, nparts, n_tokens) : nullptr;
   const float* const undo = tab.undo[z];
   SGMV_TRACE_DECL
   SGMV_TRACE_POINT(0);
@@ -653,16 +658,17 @@ __global__ __launch_bounds__(256, PARTS == 3 ? 3 : 4) void expand_matrix_kernel(
           v0 = __float_as_int(sum0 * scale);
           v1 = __float_as_int(sum1 * scale);
         } else {
-          const long long at = (long long)row * R + vj;
-          const auto joined = [&](int more) {
-            float low = decode1<DT>(vl[at + more]);
-            if constexpr (PARTS == 3) low += decode1<DT>(vr[at + more]);
-            return decode1<DT>(vh[at + more]) + low;
-          };
+          const uint16_t *const h = vh + (long long)row * R + vj, *const l = vl + (long long)row * R + vj;
           const float u0 = std::is_same<DT, F16>::value ? undo[row] : 1.f;
           const float u1 = std::is_same<DT, F16>::value ? undo[two ? row + 1 : row] : 1.f;
-          v0 = __float_as_int(joined(0) * (scale * u0));
-          v1 = __float_as_int(joined(second) * (scale * u1));
+          float l0 = decode1<DT>(l[0]), l1 = decode1<DT>(l[second]);
+          if constexpr (PARTS == 3) {
+            const uint16_t* const r = vr + (long long)row * R + vj;
+            l0 += decode1<DT>(r[0]);
+            l1 += decode1<DT>(r[second]);
+          }
+          v0 = __float_as_int((decode1<DT>(h[0]) + l0) * (scale * u0));
+          v1 = __float_as_int((decode1<DT>(h[second]) + l1) * (scale * u1));
         }
         float s0[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, s1[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
@@ -968,14 +974,12 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, bool direc
     tab.v_parts[i] = fin.v_parts[i] = e.v_parts;
     tab.vh[i] = fin.vh[i] = e.vh;
     tab.vl[i] = fin.vl[i] = e.vl;
-    tab.vr[i] = fin.vr[i] = e.vr;
     tab.undo[i] = fin.undo[i] = e.undo;
     tab.y[i] = (uint16_t*)e.y;
     tab.A_ptrs[i] = (const uint16_t* const*)e.A_ptrs;
     tab.B_ptrs[i] = (const uint16_t* const*)e.B_ptrs;
   }
-  const bool three_parts = a.vr != nullptr;
-  if (three_parts && R != 64) return hipErrorInvalidValue;
+  if (a.three_parts && R != 64) return hipErrorInvalidValue;
   if (!direct) {
     const long long quads = (long long)a.n_tokens * (R / 4);
     const auto finalize = [&](auto parts_tag) {
@@ -983,9 +987,9 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, bool direc
                          dim3(256), 0, st, a.nparts, a.n_tokens, fin);
     };
     if constexpr (R == 64) {
-      if (three_parts) finalize(std::integral_constant<int, 3>{});
+      if (a.three_parts) finalize(std::integral_constant<int, 3>{});
     }
-    if (!three_parts) finalize(std::integral_constant<int, 2>{});
+    if (!a.three_parts) finalize(std::integral_constant<int, 2>{});
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
@@ -1015,7 +1019,7 @@ static hipError_t launch_expand_matrix_t(const ExpandArgs* es, int n, bool direc
     }
   }
   if constexpr (R == 64) {
-    if (three_parts) {
+    if (a.three_parts) {
       launch(std::false_type{}, std::integral_constant<int, 3>{});
       return hipGetLastError();
     }
