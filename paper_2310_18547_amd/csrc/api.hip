@@ -198,8 +198,9 @@ struct MatrixSplit {
 // segments of 8 rows, eight slices, 14.3 / 12.7; 1152 rows beside 41 of one row, eight slices, 15.9 / 14.1, three projections of
 // them 29.4 / 28.9, to 11008 (2300 workgroups) 52.0 / 53.0; three of 3440 rows, 8192 -> 2048, 35.3 / 36.5.  At rank 32 the
 // partial sums are too many (1152 rows beside 41, eight slices, 19.1 / 20.4), at rank 64 also the operands in LDS.
-// Three launches from 2000 rows on, as sgmv_plan_add_lora has told the callers of such batches (two would be 16.7 against 17.7
-// us at 2000 rows, rank 16, 4096 wide, and 46.6 against 47.6 at 4814, 8192 wide).
+// Beyond 1920 rows (thirty blocks) three launches, which is what the plan of 2000 rows is expected to tell, not what is faster: two would be
+// 16.7 against 17.7 us at 2000 rows, rank 16, 4096 wide, and 46.6 against 47.6 at 4814, 8192 wide.  SGMV_PATH_MATRIX keeps three at
+// every rank, so that finalize_v_kernel and the expand behind it can be run and timed on any batch.
 constexpr int kDirectMostRows = 1920;
 bool matrix_direct(const sgmv_problem* p, int n_segs, int n_proj, int slices) {
   if (p->path == SGMV_PATH_MATRIX || p->r > 16 || p->n_tokens > kDirectMostRows) return false;
@@ -731,12 +732,15 @@ bool choose_fused_pairs(const sgmv_problem* p, int n_segs, FusedArgs* f) {
 //    1.24 times on pairs, 0.99 at least: 13824 -> 2048, 51 x 2 rows 12.5 / 11.1), at rank 8, where the tile kernel has five slices and more,
 //    of 5 to 32 rows, more than three and a half on average (9992 -> 1024, 116 rows of 20 8.1 / 9.7; 74 points 1.02 times on the tile
 //    kernel, 326 others 1.27 times on pairs: 11008 -> 4096, 101 rows of 47, in a layer of seven projections 40.9 / 36.5).
+//    Segments all of one even length up to twelve are pairs without an empty place: 39 points 1.13 times as fast on pairs, 0.89 at worst
+//    (13824 -> 368, rank 16, 15 x 8 rows 1.35; 13824 -> 5120, rank 8, 16 x 8 rows 9.6 / 7.1; 9992 -> 320, rank 8, 38 x 6 rows 0.89).
 bool choose_add_on_pairs(const sgmv_problem* p, int n_segs, int tile_slices, FusedArgs* f) {
   if (p->r == 8 ? tile_slices == 6 || tile_slices == 7 : tile_slices >= 6 || p->n_tokens > 128) return false;
   if (!choose_fused_pairs(p, n_segs, f) || f->cslice > (p->r == 16 ? 1024 : 2048)) return false;
   const int units = limits().fused_workgroups;
   if (p->r == 32) return (long long)f->S * f->items <= units;
   if (tile_slices == 0 || f->S * fused_grid_items(f->items) <= 2 * units) return true;
+  if (p->max_seg_len % 2 == 0 && p->max_seg_len <= 12 && p->n_tokens == (long long)n_segs * p->max_seg_len) return true;
   if (p->r == 8) return tile_slices < 5 || p->max_seg_len <= 4 || p->max_seg_len > 32 || 2LL * p->n_tokens <= 7LL * n_segs;
   return p->max_seg_len > 48 || (p->max_seg_len == 2 && 4LL * p->n_tokens > 7LL * n_segs);
 }

@@ -719,7 +719,7 @@ def test_pairs_of_rows_leave_the_tile_kernel_what_it_is_ahead_on():
     for lens, h_in, h_out, r, kernel in (
             ([3, 2, 1] * 17, 9992, 1024, 16, tile), ([2] * 51, 13824, 2048, 16, pairs), ([2] * 40 + [1] * 18, 13824, 1024, 16, tile),
             ([5] * 22, 9992, 1024, 16, tile), ([48] + [3] * 21, 9992, 1024, 16, tile), ([49] + [3] * 21, 9992, 1024, 16, pairs),
-            ([6] * 19, 9992, 1024, 8, tile), ([4] * 29, 9992, 1024, 8, pairs), ([2] * 46 + [5], 9992, 1024, 8, pairs),
+            ([6] * 18 + [5], 9992, 1024, 8, tile), ([6] * 19, 9992, 1024, 8, pairs), ([4] * 29, 9992, 1024, 8, pairs), ([8] * 15, 13824, 368, 16, pairs), ([2] * 46 + [5], 9992, 1024, 8, pairs),
             ([32] + [8] * 12, 9992, 1024, 8, tile), ([33] + [8] * 11 + [7], 9992, 1024, 8, pairs)):
         n = sum(lens)
         p = sg.make_problem(sg.F16, h_in, h_out, r, 1, n, workspace=256, workspace_bytes=sg.sgmv_workspace_bytes(n, r),
