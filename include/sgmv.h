@@ -49,7 +49,10 @@
  *     kernels (segments of several rows) feed v to the matrix cores as a high
  *     plus a low 16-bit part, which keeps 16 significant bits of v for
  *     bfloat16 and 22 for binary16 -- well inside the accuracy the 16-bit
- *     result can show.  Results are deterministic run to run (no
+ *     result can show -- down to |v| of 2^-3, below which binary16 keeps
+ *     what is above 2^-25.  Where several add-ons of rank 64 run on them
+ *     together that would run on the vector ALUs (or the tile kernel) one by
+ *     one, v is three parts, all 24 bits (sgmv_add_lora_multi).  Results are deterministic run to run (no
  *     floating-point atomics).
  *   - Supported shapes: r in {8, 16, 32, 64}; h_in and h_out positive
  *     multiples of 8.  Anything else returns SGMV_ERR_UNSUPPORTED; there is no
@@ -313,14 +316,18 @@ int sgmv_add_lora_static(const sgmv_problem* p, void* y, const void* x,
  * segments (per row, as under SGMV_PATH_ROWS) and segments of a few rows
  * (max_seg_len from 2 up to what the single-launch MFMA kernel takes) while the
  * workgroups of all add-ons fit on the chip together, and in groups of as many
- * as fit beyond that.  On long segments (the MFMA kernels) up to three add-ons
- * go into one launch of each kernel when the workspace has the size of
- * sgmv_workspace_bytes_multi, and those whose x_i are the same buffer share the
- * shrink's pass over x.  Otherwise the call is the same as n_proj calls of
+ * as fit beyond that.  On long segments, and at rank 64 on batches of 24 to 400
+ * rows, four per segment and more, that would otherwise take at least two launches
+ * for every three add-ons, up to three add-ons go into one launch of each of the
+ * MFMA kernels when the workspace has the size of sgmv_workspace_bytes_multi, and
+ * those whose x_i are the same buffer share the shrink's pass over x (up to rank
+ * 32).  Otherwise the call is the same as n_proj calls of
  * sgmv_add_lora in order (sgmv_plan_add_lora reports which).  The result of every add-on
  * equals that of a separate sgmv_add_lora call up to the order in which the
  * fp32 sums are taken (the single-launch kernels split the same sums over
- * lanes differently). */
+ * lanes differently) and, where a joint launch takes the matrix cores and a separate
+ * call would not or the other way round, up to the 16-bit parts of v (general
+ * conventions). */
 int sgmv_add_lora_multi(const sgmv_problem* p, int32_t n_proj, void* const* ys,
                         const void* const* xs, const void* const* const* A_ptrs,
                         const void* const* const* B_ptrs, const int32_t* seg_starts,
