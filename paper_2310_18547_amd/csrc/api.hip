@@ -204,7 +204,10 @@ struct MatrixSplit {
 constexpr int kDirectMostRows = 1920;
 bool matrix_direct(const sgmv_problem* p, int n_segs, int n_proj, int slices) {
   if (p->path == SGMV_PATH_MATRIX || p->r > 16 || p->n_tokens > kDirectMostRows) return false;
-  if (n_segs > 104) return false;  // every short segment is a block of its own (300 of 5 rows, 2048 -> 8192, rank 16: 39.6 / 52.0)
+  // every short segment is a block of its own (300 of 5 rows, 2048 -> 8192, rank 16: 39.6 / 52.0): beyond 104 of them two launches are ahead
+  // to narrow outputs only (up to 2048 / 4096 / 6144 columns / wider, times as fast: 105 to 124 segments 1.09 / 1.08 / 1.05 / 0.94, 200 to
+  // 224 1.06 / 0.95 / 0.96 / 0.93)
+  if (n_segs > 104) return false;
   const long long sums = (long long)p->n_tokens * n_proj * p->r * slices;
   const long long workgroups = (long long)ceil_div(p->n_tokens, 64) * ceil_div(p->h_out, 256) * n_proj;
   return p->r * slices <= 256 && sums * (workgroups > 1024 ? workgroups : 1024) <= (512LL << 10) * 1024;
@@ -1069,6 +1072,8 @@ int plan_multi(const sgmv_problem* p, int n_segs, int n_proj, FusedArgs* f, Tile
 //    kernel only from 50 rows on (45 rows of nine, 1736 -> 1024, 22.8 / 27.3);
 //  * fewer, in groups of the tile kernel, 152 points: 0.84 times (four in two launches 0.83, five in two and three 0.82 and 1.08, eight in two,
 //    three and four 0.60, 0.82 and 1.00: 4160 -> 2048, 30 rows of five, 21.5 / 52), so those stay.
+// Two or three add-ons outside these limits would mostly gain too (8 to 23 rows 1.20 times as fast, down to 0.80; two and three rows per
+// segment 1.35, down to 0.87; more than 400 rows 1.35, at two per segment down to 0.73) and are left where they are.
 bool multi_takes_matrix(const sgmv_problem* p, int n_segs, int n_proj, int kernel, const TileArgs& t) {
   if (n_proj < 2 || p->path != SGMV_PATH_AUTO || p->ksplit != 0 || p->r != 64 || p->max_seg_len == 1) return false;
   if (p->n_tokens < 24 || p->n_tokens > 400 || p->n_tokens < 4LL * n_segs || p->workspace == nullptr ||

@@ -31,7 +31,8 @@ def test_several_add_ons_of_rank_64(dtype, lens, P, matrix):
 # taken in another order, on the matrix cores in chains of up to h_in / 32 = 128 roundings of a running sum: sqrt(128 / 3) / 2 times 2^-24 as
 # a root mean square, 2^-22, for v and less for its 64 products: twice that, or a quarter more than the separate calls.
 @pytest.mark.parametrize("dtype,v_size", [("f16", -18), ("f16", 0), ("f16", 18), ("bf16", -18), ("bf16", 0)])
-@pytest.mark.parametrize("lens,h_in,h_out", [([4] * 100, 2048, 520), ([30], 4096, 1608), ([9, 0, 1, 17, 5, 33, 2, 61], 4096, 1024)])
+@pytest.mark.parametrize("lens,h_in,h_out", [([4] * 100, 2048, 520), ([30], 4096, 1608), ([9, 0, 1, 17, 5, 33, 2, 61], 4096, 1024),
+                                             ([1, 2] * 7 + [30, 13], 2048, 11008)])      # strips of one and two rows
 def test_no_bits_of_v_are_lost(dtype, v_size, lens, h_in, h_out):
     from paper_2310_18547_amd import binding as B
     P, scale = 3, 2.0 ** -v_size
